@@ -274,6 +274,68 @@ def run(st):
     return st["scores"]
 
 
+# ----------------------------------------------------------------------- the same in 64 bits
+def _attend(q, k, D, lse=None, first=0):
+    """Column sums of softmax(q k^T / sqrt(D)) under the causal mask, float64: q [n,D] are the rows
+    from `first` on, k [S,D]; `lse` [n]: the rows' normalisers, where the caller supplies them."""
+    out = torch.zeros(k.shape[0], dtype=torch.float64, device=k.device)
+    k = k.double()
+    for r0 in range(0, q.shape[0], 2048):
+        r1 = min(r0 + 2048, q.shape[0])
+        end = first + r1
+        x = (q[r0:r1].double() @ k[:end].t()) / math.sqrt(D)
+        late = torch.arange(end, device=k.device)[None, :] > torch.arange(first + r0, end, device=k.device)[:, None]
+        x.masked_fill_(late, -math.inf)
+        p = torch.softmax(x, dim=1) if lse is None else torch.exp(x - lse[r0:r1, None].double())
+        out[:end] += p.sum(dim=0)
+    return out
+
+
+def _add_heads(out, b, h, G, reduce, values):
+    out[b, h // G if reduce else h, : values.numel()] += values
+
+
+def exact(case, seed):
+    """What run() returns on a fresh state, its scores in 64 bits; selections and copied rows have no such value."""
+    c = case
+    if c["kind"] in ("select", "pages"):
+        return None
+    st = prepare(case, seed)
+    B, Hq, Hkv, D = c["B"], c["Hq"], c["Hkv"], c["D"]
+    G, reduce = Hq // Hkv, c["reduce"]
+    Hs = Hkv if reduce else Hq
+    if c["kind"] in ("layer", "scores", "window"):
+        q, k, S = st["q"], st["k"], c["S"]
+        first = max(0, S - c["window"]) if c["kind"] == "window" else 0
+        out = torch.zeros(B, Hs, S, dtype=torch.float64, device="cuda")
+        for b in range(B):
+            for h in range(Hq):
+                lse = st["lse"][b, h] if c.get("lse") else None
+                _add_heads(out, b, h, G, reduce, _attend(q[b, h, first:], k[b, h // G], D, lse, first))
+        if c["kind"] == "layer":
+            return {"scores": out, "idx": None, "k": None, "v": None}
+        if c["kind"] == "window":
+            pooled = torch.nn.functional.max_pool1d(out, c["pool"], stride=1, padding=c["pool"] // 2)
+            return {"scores": out, "pooled": pooled}
+        return out
+    q = st["q_new"][0].double()
+    if c["kind"] == "decode":                                        # the new key takes the first free slot
+        cache = st["cache"]
+        n = [cache.n + 1] * B
+        keys = cache.k[:, :, : cache.n + 1].double()
+        keys[:, :, cache.n] = st["k_new"][0].double()
+        out = cache.scores.double()
+    else:
+        n = st["lengths"].tolist()
+        keys = st["pool"][st["table"].long()].view(B, c["S"], Hkv, D).transpose(1, 2).double()
+        out = st["scores"].double()
+    for b in range(B):
+        out[b, :, n[b] - 1] = 0.0
+        for h in range(Hq):
+            _add_heads(out, b, h, G, reduce, torch.softmax(keys[b, h // G, : n[b]] @ q[b, h] / math.sqrt(D), dim=0))
+    return {"n": None, "scores": out, "k": None, "v": None} if c["kind"] == "decode" else out
+
+
 # ------------------------------------------------------------------- work and tolerances
 def work(case):
     c = case
