@@ -138,6 +138,25 @@ __device__ __forceinline__ void colsum_update(const f32x16& acc, f32x16& col, fl
   }
 }
 
+// Sums every register over the 32 lanes of each half wave: each exchange halves the registers a
+// lane is responsible for (16 exchanges instead of 80), and the additions pair up as in a plain
+// butterfly.  Lane l ends up with the total of register (l / 2) % 16.
+__device__ __forceinline__ float sum_over_lanes(const f32x16& v, int lane) {
+  float a[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) a[r] = v[r];
+#pragma unroll
+  for (int n = 8; n > 0; n >>= 1) {
+    const bool upper = (lane & (2 * n)) != 0;
+#pragma unroll
+    for (int r = 0; r < n; ++r) {
+      const float keep = upper ? a[r + n] : a[r], give = upper ? a[r] : a[r + n];
+      a[r] = keep + __shfl_xor(give, 2 * n);
+    }
+  }
+  return a[0] + __shfl_xor(a[0], 1);
+}
+
 // sched_group_barrier classes: matrix ops, LDS reads, vector ALU incl. transcendentals
 constexpr int kSchedMfma = 0x008, kSchedDsRead = 0x100, kSchedValu = 0x002 | 0x400;
 
@@ -698,6 +717,174 @@ __global__ __launch_bounds__(kKeysPerWg) void colsum_reduce_kernel(ScoreParams p
   p.scores[(size_t)bh * p.S + t] = acc;
 }
 
+// ------------------------------------------------- short prompts, both passes ------
+// The kernels above give a workgroup 64 stationary rows per wave and walk the other operand
+// through LDS: on a prompt of some hundred tokens that is a handful of workgroups, each a long
+// serial chain (pass B at B = 2, S = 700, 8 query heads: 12 workgroups of 44 steps).  Here the
+// unit is one 32x32 tile of one wave: a workgroup of eight waves owns 32 stationary rows, every
+// wave holds them in registers and takes every eighth tile of the other operand through its own
+// two LDS buffers (the next tile lands while this one is worked on; no barrier in the loop).  The waves' partial results meet in LDS once, at the end, in wave
+// order, so neither the slices' merge nor the partial sums' reduction needs a launch of its own.
+template <class C>
+constexpr int kShortWaves = C::kSubBytes > 8192 ? 4 : 8;  // (two tiles per wave in LDS: at most 128 KiB)
+
+// A wave's own 32-row tile in LDS: the image of one sub-tile (tiles.h), filled by this wave alone
+// with written-out copies, so that the wave's own vmcnt wait is all the synchronisation it needs.
+template <class C>
+struct WaveTile {
+  static constexpr int kLoads = C::kSubBytes / 1024;  // 1 KiB per wave instruction
+  uint32_t rel[kLoads];                               // lane's byte offset inside the tile, per copy
+  unsigned row_bytes;
+  int lane;
+
+  __device__ __forceinline__ WaveTile(int lane_, unsigned rb) : row_bytes(rb), lane(lane_) {
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) rel[j] = offset(j, 31);
+  }
+  // Byte offset of the 16-byte chunk this lane fills with copy j; rows beyond `last` read row `last`.
+  __device__ __forceinline__ uint32_t offset(int j, int last) const {
+    const int p = j * 64 + lane, line = p >> 4, q = line * 16 + ((p & 15) ^ (line & 15));
+    return (uint32_t)min(q / C::kChunksPerRow, last) * row_bytes + (uint32_t)(q % C::kChunksPerRow) * 16;
+  }
+  // Rows [row0, row0 + 32) of a head, clamped to the sequence; row0, head and dst are wave-uniform.
+  __device__ __forceinline__ void load(const char* head, int row0, int S, uint32_t dst) const {
+    const char* src = wave_uniform(head + (size_t)row0 * row_bytes);
+    const int last = S - 1 - row0;
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) wave_copy_unseen(src, last >= 31 ? rel[j] : offset(j, last), dst + j * 1024);
+  }
+};
+
+template <bool BF16, int D, bool F16 = false, bool STRIDED = false>
+__global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void lse_short_kernel(ScoreParams p) {
+  using C = Cfg<BF16, D>;
+  constexpr int W = kShortWaves<C>;
+  __shared__ __attribute__((aligned(1024))) char lds[W][2][C::kSubBytes];
+  __shared__ float2 part[W][32];
+  const int tid = threadIdx.x, lane = kvc::lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / KVC_WAVE);
+  const int S = p.S;
+  const int bh = (int)(blockIdx.x % p.n_bh), blk = p.n_blocks - 1 - (int)(blockIdx.x / p.n_bh);  // long rows first
+  const int b = bh / p.Hq, head = bh % p.Hq, kvh = head / p.G;
+  const int q0 = blk * 32;
+  const char* qh = STRIDED ? p.q + b * p.q_sb + head * p.q_sh : p.q + (size_t)bh * S * C::kRowBytes;
+  const char* kh = STRIDED ? p.k + b * p.k_sb + kvh * p.k_sh : p.k + ((size_t)b * p.Hkv + kvh) * S * C::kRowBytes;
+  const unsigned qrb = STRIDED ? p.q_rb : (unsigned)C::kRowBytes, krb = STRIDED ? p.k_rb : (unsigned)C::kRowBytes;
+
+  float m = kNegBig, l = 0.0f;
+  if (wave <= blk) {  // (key tile t holds keys 32 t .. 32 t + 31; tile blk is the diagonal one)
+    const WaveTile<C> tile(lane, krb);
+    const uint32_t dst = tile_wave_dst(&lds[wave][0][0], 0);
+    tile.load(kh, wave * 32, S, dst);
+    u32x4 qf[C::kSteps];
+    load_stationary<C>(qf, qh, q0, S, lane, qrb);
+    const int off0 = lds_frag_offset0<C>(lane);
+    int cur = 0;
+    for (int t = wave; t <= blk; t += W, cur ^= 1) {
+      wait_async_loads();
+      if (t + W <= blk) tile.load(kh, (t + W) * 32, S, dst + (cur ^ 1) * C::kSubBytes);
+      f32x16 acc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+      for (int s = 0; s < C::kSteps; ++s) mma_step<BF16, F16>(acc, lds_frag<C>(lds[wave][cur], off0, 0, s), qf[s]);
+      if (t == blk)
+        softmax_update<true>(acc, m, l, p.scale_log2, (lane & 31) - 4 * (lane >> 5));
+      else
+        softmax_update<false>(acc, m, l, p.scale_log2, 0);
+    }
+  }
+  // lanes l and l^32 saw disjoint keys of the same query, and so did the waves
+  {
+    const float mo = __shfl_xor(m, 32), lo = __shfl_xor(l, 32);
+    const float mt = fmaxf(m, mo);
+    const float lt = l * __builtin_amdgcn_exp2f(m - mt) + lo * __builtin_amdgcn_exp2f(mo - mt);
+    if (lane < 32) part[wave][lane] = make_float2(mt, lt);
+  }
+  __syncthreads();
+  if (tid < 32 && q0 + tid < S) {
+    float mt = part[0][tid].x;
+#pragma unroll
+    for (int w = 1; w < W; ++w) mt = fmaxf(mt, part[w][tid].x);
+    float lt = 0.0f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) lt += part[w][tid].y * __builtin_amdgcn_exp2f(part[w][tid].x - mt);
+    p.lse[(size_t)bh * S + q0 + tid] = (mt + __builtin_amdgcn_logf(lt)) * kLn2;
+  }
+}
+
+template <bool BF16, int D, bool F16 = false, bool STRIDED = false>
+__global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void colsum_short_kernel(ScoreParams p, const float* lse_in) {
+  using C = Cfg<BF16, D>;
+  constexpr int W = kShortWaves<C>;
+  __shared__ __attribute__((aligned(1024))) char lds[W][2][C::kSubBytes];
+  __shared__ float part[W][32];
+  const int tid = threadIdx.x, lane = kvc::lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / KVC_WAVE);
+  const int S = p.S;
+  const int bh = (int)(blockIdx.x % p.n_bh), kb = (int)(blockIdx.x / p.n_bh);  // keys with many queries first
+  const int rows = p.reduce_groups ? p.Hkv : p.Hq;
+  const int b = bh / rows, row = bh % rows;
+  const int kvh = p.reduce_groups ? row : row / p.G;
+  const int head0 = p.reduce_groups ? row * p.G : row, n_heads = p.reduce_groups ? p.G : 1;
+  const int k0 = kb * 32;
+  const char* kh = STRIDED ? p.k + b * p.k_sb + kvh * p.k_sh : p.k + ((size_t)b * p.Hkv + kvh) * S * C::kRowBytes;
+  const unsigned qrb = STRIDED ? p.q_rb : (unsigned)C::kRowBytes, krb = STRIDED ? p.k_rb : (unsigned)C::kRowBytes;
+
+  f32x16 col;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) col[r] = 0.0f;
+  // (head, query tile) pairs, tiles from the diagonal (or the window's first tile) on; wave w takes
+  // pairs w, w + 8, ... in head-major order
+  const int n_tiles = (S + 31) / 32, t_first = max(kb, p.tile0), nt = n_tiles - t_first;
+  const int n_pairs = nt * n_heads;
+  if (wave < n_pairs) {
+    const WaveTile<C> q_tile(lane, qrb);
+    const uint32_t dst = tile_wave_dst(&lds[wave][0][0], 0);
+    float raw = 0.0f;
+    int t = wave, h = 0;  // tile (counted from t_first) and head of the pair to load next
+    auto fetch = [&](int buf) {
+      while (t >= nt) {
+        t -= nt;
+        ++h;
+      }
+      const int head = head0 + h, q0 = (t_first + t) * 32;
+      const char* qh = STRIDED ? p.q + b * p.q_sb + head * p.q_sh : p.q + ((size_t)b * p.Hq + head) * S * C::kRowBytes;
+      raw = lse_in[((size_t)b * p.Hq + head) * S + min(q0 + (lane & 31), S - 1)];
+      q_tile.load(qh, q0, S, dst + buf * C::kSubBytes);
+    };
+    fetch(0);
+    u32x4 kf[C::kSteps];
+    load_stationary<C>(kf, kh, k0, S, lane, krb);
+    const int off0 = lds_frag_offset0<C>(lane);
+    int cur = 0;
+    for (int pair = wave; pair < n_pairs; pair += W, cur ^= 1) {
+      const int tile = t_first + t, qi = tile * 32 + (lane & 31);
+      wait_async_loads();
+      // rows past the end and rows before an observation window contribute nothing
+      const float lse2 = (qi < S && qi >= p.q_first) ? raw * kLog2e : INFINITY;
+      t += W;
+      if (pair + W < n_pairs) fetch(cur ^ 1);
+      f32x16 acc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+      for (int s = 0; s < C::kSteps; ++s) mma_step<BF16, F16>(acc, kf[s], lds_frag<C>(lds[wave][cur], off0, 0, s));
+      if (tile == kb)
+        colsum_update<true>(acc, col, p.scale_log2, lse2, (lane & 31) - 4 * (lane >> 5));
+      else
+        colsum_update<false>(acc, col, p.scale_log2, lse2, 0);
+    }
+  }
+  const float v = sum_over_lanes(col, lane);
+  if ((lane & 1) == 0) part[wave][acc_row((lane >> 1) & 15, lane)] = v;
+  __syncthreads();
+  if (tid < 32 && k0 + tid < S) {
+    float acc = 0.0f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) acc += part[w][tid];
+    p.scores[(size_t)bh * S + k0 + tid] = acc;
+  }
+}
+
 // Work pieces of pass B for a sequence of n_tiles query tiles.
 struct ColsumPlan {
   int n_kb, n_chunks, chunk_tiles;
@@ -795,6 +982,40 @@ kvcrush_status launch_lse(const ScoreParams& base, float2* split_ml, hipStream_t
   return kvc::launch(lse_combine_kernel, dim3((pl.split_rows + 3) / 4, a.B * a.Hq), dim3(256), 0, stream, a);
 }
 
+// Whether the short kernels serve the call: 32x32 tiles of the causal half, all heads together.
+// Below the line the chip is short of workgroups and the short kernels' finer cut wins (both passes,
+// us, tiled -> short): 1088 tiles (B 1, 8 heads, S 512, fp32) 90 -> 22; 4048 (B 2, 8 heads in 2
+// groups, S 700, bf16) 79 -> 25; 16128 (8 heads in 2 groups, S 2000) 103 -> 47; 16896 (32 heads, a
+// row each, S 1000) 53 -> 52.  Above it the tiled kernels' four times larger tile per wave, half the
+// LDS traffic per product, takes over: 66560 (32 heads, a row each, S 2048) 83 against 123; 135168
+// (B 8, 32 heads, S 1024) 125 against 284.
+constexpr long long kShortTiles = 16384;
+bool short_prompt(const ScoreParams& p) {
+  const long long n = (p.S + 31) / 32;
+  return p.q_first == 0 && (long long)p.B * p.Hq * n * (n + 1) / 2 <= kShortTiles;
+}
+
+template <bool BF16, int D, bool F16>
+kvcrush_status launch_short(ScoreParams p, const float* lse_user, bool lse_only, hipStream_t stream) {
+  constexpr int kShortThreads = kShortWaves<Cfg<BF16, D>> * KVC_WAVE;
+  p.n_blocks = (p.S + 31) / 32;
+  p.tile0 = p.q_first / 32;
+  if (!lse_user) {
+    p.n_bh = p.B * p.Hq;
+    const dim3 grid((unsigned)(p.n_blocks * p.n_bh));
+    const kvcrush_status st =
+        p.strided ? kvc::launch(lse_short_kernel<BF16, D, F16, true>, grid, dim3(kShortThreads), 0, stream, p)
+                  : kvc::launch(lse_short_kernel<BF16, D, F16, false>, grid, dim3(kShortThreads), 0, stream, p);
+    if (st != KVCRUSH_OK || lse_only) return st;
+  }
+  p.n_bh = p.B * (p.reduce_groups ? p.Hkv : p.Hq);
+  const dim3 grid((unsigned)(p.n_blocks * p.n_bh));
+  const float* lse_in = lse_user ? lse_user : p.lse;
+  return p.strided
+             ? kvc::launch(colsum_short_kernel<BF16, D, F16, true>, grid, dim3(kShortThreads), 0, stream, p, lse_in)
+             : kvc::launch(colsum_short_kernel<BF16, D, F16, false>, grid, dim3(kShortThreads), 0, stream, p, lse_in);
+}
+
 template <bool BF16, int D, bool F16 = false>
 kvcrush_status launch_scores(const ScoreParams& base, const float* lse_user, float2* split_ml,
                              bool lse_only, hipStream_t stream) {
@@ -803,6 +1024,7 @@ kvcrush_status launch_scores(const ScoreParams& base, const float* lse_user, flo
   const ColsumPlan pl = colsum_plan(p.S, C::kTile, chunk_tiles_for(C::kTile, p.reduce_groups ? p.G : 1), p.q_first);
   const long long rows = (long long)p.B * (p.reduce_groups ? p.Hkv : p.Hq);
   if (!lse_only && pl.pieces * rows > kMaxGridX) return KVCRUSH_ERR_UNSUPPORTED;  // before anything is enqueued
+  if (short_prompt(p)) return launch_short<BF16, D, F16>(p, lse_user, lse_only, stream);
   if (!lse_user) {
     const kvcrush_status st = launch_lse<BF16, D, F16>(p, split_ml, stream);
     if (st != KVCRUSH_OK) return st;

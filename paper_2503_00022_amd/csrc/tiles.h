@@ -171,6 +171,14 @@ __device__ __forceinline__ void tile_load_async_full_unseen(const char* tile, ui
                  : "s"(wave_dst), "v"(rel[j]), "s"(tile), "n"(kWaves * j * 1024)
                  : "m0", "scc");
 }
+// One copy of 1 KiB by one wave, issued the same way: 16 bytes per lane from tile + off to the LDS
+// byte address `dst` + 16 * lane (tile and dst uniform over the wave).
+__device__ __forceinline__ void wave_copy_unseen(const char* tile, uint32_t off, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(dst), "v"(off), "s"(tile)
+               : "m0");
+}
 // A pointer that is the same in every lane of the wave, moved to scalar registers.
 __device__ __forceinline__ const char* wave_uniform(const char* ptr) {
   const uint64_t v = (uint64_t)(uintptr_t)ptr;

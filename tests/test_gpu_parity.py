@@ -328,6 +328,42 @@ def test_scores_small(kv, oracle, B, Hq, Hkv, S, D, dtype, rg):
     check_scores(kv, oracle, w, seed=S + Hq, reduce_groups=rg)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype,rg,strided", [
+    (1, 4, 2, 32, 128, "bf16", True, False),      # one whole tile, one wave at work
+    (1, 4, 2, 33, 64, "f16", False, True),        # the second tile holds one row
+    (1, 3, 1, 255, 128, "bf16", True, True),      # eight tiles, the last one ragged
+    (2, 3, 1, 257, 64, "bf16", True, False),      # the ninth tile: a wave's second one
+    (1, 2, 2, 129, 128, "f32", False, True),      # four waves a workgroup
+    (1, 2, 1, 300, 64, "f32", True, False),
+    (1, 32, 8, 992, 128, "bf16", True, False),    # the last size of the short kernels at 32 heads
+    (1, 32, 8, 993, 128, "bf16", True, True),     # the first of the tiled ones
+    (1, 32, 32, 1100, 128, "f16", False, False),
+])
+def test_scores_on_both_sides_of_the_short_prompt_line(kv, oracle, B, Hq, Hkv, S, D, dtype, rg, strided):
+    """The short-prompt kernels at the edges of their 32-row tiles, and the sizes on either side of
+    the line to the tiled kernels; the last keys' logits ramp up and down by tens, so that references
+    have to move.  A logit of these inputs is below 64 and its fp32 dot product of up to 128 terms is
+    off by at most 128 * 2^-24 * 64 = 5e-4, which is also the relative error of its exponential; the
+    normaliser adds the same once more: 1e-3."""
+    say(f"short-prompt line B={B} Hq={Hq} Hkv={Hkv} S={S} D={D} {dtype} reduce={rg} strided={strided}")
+    w = inputs.Workload("t", B, Hq, Hkv, S, D, dtype, max(1, S // 4), 0.5, "alternating", rg)
+    q, k, _ = inputs.make_qkv(w, S + Hq, want_v=False)
+    ramp = 1.0 + 3.0 * torch.sin(torch.arange(S) * (3.0 / S)).abs()
+    k = (k.float() * ramp[None, None, :, None]).to(k.dtype)
+    assert (q.float().norm(dim=-1).max() * k.float().norm(dim=-1).max() / D ** 0.5).item() < 4 * 64  # (Cauchy bound)
+    ref, ref_lse = oracle.scores(q, k, rg, want_lse=True, threads=THREADS)
+    qg, kg = q.cuda(), k.cuda()
+    if strided:                                      # token-major projections, read in place
+        qg, kg = (x.transpose(1, 2).contiguous().transpose(1, 2) for x in (qg, kg))
+    sc, ws = kv.kvcrush_scores(qg, kg, rg)
+    again, _ = kv.kvcrush_scores(qg, kg, rg)
+    given, _ = kv.kvcrush_scores(qg, kg, rg, lse=ref_lse.cuda())
+    torch.cuda.synchronize()
+    assert torch.equal(sc, again)
+    assert rel_err(sc, ref) <= 1e-3 and rel_err(given, ref) <= 1e-3
+    assert (kv.lse_from_workspace(ws, B, Hq, S).cpu().double() - ref_lse.double()).abs().max().item() < 1e-3
+
+
 def test_scores_extreme_logits(kv, oracle):
     """Logits that grow by hundreds along the sequence: the exponentials' fixed
     reference has to be re-based on the fly (and early keys underflow to zero)."""
