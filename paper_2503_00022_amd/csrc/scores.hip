@@ -350,33 +350,31 @@ __global__ __launch_bounds__(kThreads, 2) void lse_kernel(ScoreParams p) {
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, acc0[t][r]);
         m[t] = mx * c;
       }
-      // The trip count is rounded up to a multiple of three; the padding
-      // iterations run on the last tile again with an infinite reference, so
-      // every exponential they produce is exactly zero.
+      // The last one or two tiles of a count that is no multiple of three run in copies of the body
+      // behind the loop (leaving it in the middle cost 1 % of the whole kernel, padding steps up to two
+      // tiles a workgroup: a window of 64 at S = 16384 walks 4 or 8).
       auto body = [&](auto P, int it) {
         constexpr int cur = decltype(P)::value, nxt = (cur + 1) % 3, ld = (cur + 2) % 3;
         constexpr int kT = C::kTileBytes, kU = C::kSubBytes;
         tile_load_async_full_unseen<C>(kh_u + (size_t)((f_begin + min(it + 2, n_full - 1)) * C::kTile) * krb,
                                        wave_dst + ld * kT, rel);
-        const bool live = it < n_full;
-        float sum[2], mref[2];
+        float sum[2];
         // block (it, sub 1) goes through the MFMAs while block (it, sub 0) is summed
-        mref[0] = live ? m[0] : INFINITY;
-        mref[1] = live ? m[1] : INFINITY;
-        lse_half<C, cur * kT + kU, nxt * kT, F16>(acc1, acc0, mref, sum, fr, qf[0], qf[1], lds_base, fo, c);
+        lse_half<C, cur * kT + kU, nxt * kT, F16>(acc1, acc0, m, sum, fr, qf[0], qf[1], lds_base, fo, c);
         lse_commit(acc0, m, l, sum, c);
-        mref[0] = live ? m[0] : INFINITY;
-        mref[1] = live ? m[1] : INFINITY;
-        lse_half<C, nxt * kT, nxt * kT + kU, F16>(acc0, acc1, mref, sum, fr, qf[0], qf[1], lds_base, fo, c);
+        lse_half<C, nxt * kT, nxt * kT + kU, F16>(acc0, acc1, m, sum, fr, qf[0], qf[1], lds_base, fo, c);
         lse_commit(acc1, m, l, sum, c);
         wait_async_loads();
         __syncthreads();
       };
-      for (int it = 0; it < n_full; it += 3) {
+      int it = 0;
+      for (; it + 3 <= n_full; it += 3) {
         body(IntC<0>{}, it);
         body(IntC<1>{}, it + 1);
         body(IntC<2>{}, it + 2);
       }
+      if (it < n_full) body(IntC<0>{}, it);
+      if (it + 1 < n_full) body(IntC<1>{}, it + 1);
     }
   }
 
@@ -604,9 +602,7 @@ __global__ __launch_bounds__(kThreads, 2) void colsum_kernel(ScoreParams p, cons
       mma_pair<C, BF16, false, F16>(acc0, lds[0], off0, 0, kf[0], kf[1]);
 #pragma unroll
       for (int s = 0; s < C::kSteps / 2; ++s) fr[s] = lds_frag<C>(lds[0], off0, 1, s);
-      // The trip count is rounded up to a multiple of three; the padding
-      // iterations run on the last tile again with lse = +inf, so every
-      // probability they produce is exactly zero.
+      // (the last one or two pairs behind the loop, as in pass A)
       auto body = [&](auto P, int it) {
         constexpr int cur = decltype(P)::value, nxt = (cur + 1) % 3, ld = (cur + 2) % 3;
         constexpr int kT = C::kTileBytes, kU = C::kSubBytes;
@@ -618,11 +614,14 @@ __global__ __launch_bounds__(kThreads, 2) void colsum_kernel(ScoreParams p, cons
         settle(ahead, lse_nxt);
         __syncthreads();
       };
-      for (int it = 0; it < n_fast; it += 3) {
+      int it = 0;
+      for (; it + 3 <= n_fast; it += 3) {
         body(IntC<0>{}, it);
         body(IntC<1>{}, it + 1);
         body(IntC<2>{}, it + 2);
       }
+      if (it < n_fast) body(IntC<0>{}, it);
+      if (it + 1 < n_fast) body(IntC<1>{}, it + 1);
     }
   }
 
@@ -912,11 +911,22 @@ ColsumPlan colsum_plan(int S, int tile, int chunk_tiles_wanted, int q_first) {
 
 // Pass-B work pieces run about 72 tile steps each (query tiles x the heads a piece walks): 18
 // tiles of 64 queries when a score row sums a KV group of four query heads, 72 when it is one
-// head.  The count is a multiple of three (the loop's unroll).
-constexpr int kPieceSteps = 72;
-int chunk_tiles_for(int tile, int heads_per_row) {
-  const int steps = kPieceSteps * 64 / tile;                       // (fp32 tiles hold 32 queries)
-  const int tiles = (steps + heads_per_row - 1) / heads_per_row;
+// head.  The count is a multiple of three (the loop's unroll).  Where pieces of that length would
+// leave compute units without one (medium prompts), they are a 384th of the launch's steps, but
+// not below 12.  Whole calls in us, 72 steps -> this rule, bf16 with D = 128: S = 2048, 32 heads in
+// 8 groups 111 -> 71; S = 6000, 4 heads 112 -> 77; B = 8, S = 1024, 32 heads in 8 groups 119 -> 107.
+// A share between half a piece and a whole one gains nothing by the cut and pays for its second
+// prologue: S = 4096, 32 heads in 8 groups 175 uncut, 181 to 199 in pieces of 34 to 54 steps.
+constexpr int kPieceSteps = 72, kMinPieceSteps = 12, kPiecesWanted = 384;
+int chunk_tiles_for(int tile, int heads_per_row, long long rows, int S, int q_first) {
+  const long long n_tiles = (S + tile - 1) / tile, tile0 = q_first / tile, n_kb = (S + kKeysPerWg - 1) / kKeysPerWg;
+  // tiles from an observation window's first on that the key blocks see: all for the first `whole`
+  // blocks, then from each block's own first tile on
+  const long long tpk = kKeysPerWg / tile, whole = std::min(n_kb, tile0 / tpk + 1);
+  const long long seen = whole * (n_tiles - tile0) + (n_kb - whole) * n_tiles - tpk * ((whole + n_kb - 1) * (n_kb - whole) / 2);
+  const long long fair = seen * heads_per_row * rows / kPiecesWanted * tile / 64;  // (fp32 tiles hold 32 queries)
+  const int steps64 = 2 * fair > kPieceSteps ? kPieceSteps : std::max((int)fair, kMinPieceSteps);
+  const int tiles = (steps64 * 64 / tile + heads_per_row - 1) / heads_per_row;
   return std::max(3, (tiles + 2) / 3 * 3);
 }
 
@@ -929,9 +939,13 @@ struct LsePlan {
   int heads_per_wg, n_blocks, n_bh, launched, n_split, split_q0, split_rows;
 };
 
-// Two per compute unit.  (With 512 whole blocks already, slices and their merge cost more than
-// they balance: 112 us against 97 us at S = 4096 with 32 heads.)
-constexpr int kWantedWorkgroups = 512;
+// One workgroup per compute unit; a second one shares the unit's matrix cores, so that cutting for
+// it pays only while the slices stay long.  Whole calls in us, cut for 512 workgroups -> this rule:
+// S = 2048, 32 heads in 8 groups (256 blocks of up to 31 tiles) 85 -> 76; S = 1500, B = 2, 16 heads,
+// D = 64 (192 blocks) 48 -> 44; window of 64 at S = 16384 (8 blocks of 255 tiles) 52 -> 47; S = 12000,
+// 8 heads in 2 groups (376 blocks of up to 187 tiles) 343, 365 uncut.
+constexpr int kWantedWorkgroups = 256;
+constexpr int kWantedLong = 512, kLongSlice = 64;
 constexpr int kMinTilesPerSlice = 4;
 constexpr int kMaxSplit = 64;
 static_assert(kMaxSplit <= KVC_WAVE, "lse_combine_kernel gives one lane to each slice");
@@ -949,10 +963,11 @@ LsePlan lse_plan(int B, int Hq, int Hkv, int S, bool bf16, int q_first, bool may
   pl.split_q0 = first_blk * qb;
   pl.split_rows = S - pl.split_q0;
   const long long wgs = (long long)pl.launched * pl.n_bh;
-  if (may_split && bf16 && wgs < kWantedWorkgroups) {
+  if (may_split && bf16 && wgs < kWantedLong) {
     const int tiles_last = (pl.n_blocks - 1) * qb / 64;  // unmasked key tiles of the last block
-    int n = (int)((kWantedWorkgroups + wgs - 1) / wgs);
-    n = std::min(n, std::min(kMaxSplit, tiles_last / kMinTilesPerSlice));
+    int n = std::min((int)(kWantedWorkgroups / wgs), tiles_last / kMinTilesPerSlice);
+    n = std::max(n, std::min((int)((kWantedLong + wgs - 1) / wgs), tiles_last / kLongSlice));
+    n = std::min(n, kMaxSplit);
     pl.n_split = std::max(n, 1);
   }
   return pl;
@@ -1021,8 +1036,9 @@ kvcrush_status launch_scores(const ScoreParams& base, const float* lse_user, flo
                              bool lse_only, hipStream_t stream) {
   using C = Cfg<BF16, D>;
   ScoreParams p = base;
-  const ColsumPlan pl = colsum_plan(p.S, C::kTile, chunk_tiles_for(C::kTile, p.reduce_groups ? p.G : 1), p.q_first);
   const long long rows = (long long)p.B * (p.reduce_groups ? p.Hkv : p.Hq);
+  const ColsumPlan pl =
+      colsum_plan(p.S, C::kTile, chunk_tiles_for(C::kTile, p.reduce_groups ? p.G : 1, rows, p.S, p.q_first), p.q_first);
   if (!lse_only && pl.pieces * rows > kMaxGridX) return KVCRUSH_ERR_UNSUPPORTED;  // before anything is enqueued
   if (short_prompt(p)) return launch_short<BF16, D, F16>(p, lse_user, lse_only, stream);
   if (!lse_user) {
@@ -1057,9 +1073,10 @@ size_t lse_bytes(const kvcrush_shape* s) {
 
 size_t partial_bytes(const kvcrush_shape* s) {
   const int tile = s->dtype != KVCRUSH_F32 ? 64 : 32;
-  const ColsumPlan pl = colsum_plan(s->S, tile, chunk_tiles_for(tile, s->reduce_groups ? s->Hq / s->Hkv : 1), first_query(s));
-  if (pl.n_chunks <= 1) return 0;
   const size_t rows = (size_t)s->B * (s->reduce_groups ? s->Hkv : s->Hq);
+  const int chunk = chunk_tiles_for(tile, s->reduce_groups ? s->Hq / s->Hkv : 1, (long long)rows, s->S, first_query(s));
+  const ColsumPlan pl = colsum_plan(s->S, tile, chunk, first_query(s));
+  if (pl.n_chunks <= 1) return 0;
   return kvc::align_up(rows * pl.n_kb * pl.n_chunks * kKeysPerWg * sizeof(float), 256);
 }
 

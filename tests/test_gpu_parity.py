@@ -364,6 +364,62 @@ def test_scores_on_both_sides_of_the_short_prompt_line(kv, oracle, B, Hq, Hkv, S
     assert (kv.lse_from_workspace(ws, B, Hq, S).cpu().double() - ref_lse.double()).abs().max().item() < 1e-3
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,capacity,rg", [
+    (2, 80, 1, 300, 300, True),          # more heads in a group than normalisers held at once
+    (1, 8, 8, 131073, 131080, True),     # 1032 workgroups of four keys a thread, the last with one key
+    (1, 8, 8, 130000, 130001, False),    # 1016: one key a thread
+])
+def test_append_update_launch_shapes(kv, oracle, B, Hq, Hkv, S, capacity, rg):
+    """Both widths of the update kernel.  The added probabilities are fp32 exponentials of logits below 16
+    (relative error 128 * 2^-24 * 16 = 1.2e-4 in the worst case, and the normaliser's once more: 2.5e-4)."""
+    say(f"append update B={B} Hq={Hq} Hkv={Hkv} S={S} capacity={capacity} reduce={rg}")
+    g = torch.Generator().manual_seed(S)
+    q = torch.randn(B, Hq, 64, generator=g).bfloat16()
+    k = torch.randn(B, Hkv, capacity, 64, generator=g).bfloat16()
+    assert (q.float().norm(dim=-1).max() * k.float().norm(dim=-1).max() / 8).item() < 2 * 16  # (Cauchy bound)
+    ref = torch.zeros(B, Hkv if rg else Hq, capacity)
+    got = ref.cuda()
+    oracle.scores_append(q, k, ref, S, rg)
+    kv.kvcrush_scores_append(q.cuda(), k.cuda(), got, S, rg)
+    torch.cuda.synchronize()
+    assert rel_err(got[:, :, :S], ref[:, :, :S]) <= 2.5e-4
+    assert got[:, :, S:].abs().max().item() == 0.0
+
+
+@pytest.mark.parametrize("rows,S,kernel", [(1, 1, 3), (2, 257, 5), (8, 16384, 7), (64, 2049, 1023), (600, 300, 63), (300, 2050, 9)])
+def test_pool_segments(kv, rows, S, kernel):
+    """Segments of 256 to 2048 tokens, whole and ragged: the maximum is exact."""
+    say(f"pool rows={rows} S={S} kernel={kernel}")
+    x = torch.rand(rows, S, generator=torch.Generator().manual_seed(S))
+    out = kv.kvcrush_pool_scores(x.cuda(), kernel)
+    torch.cuda.synchronize()
+    ref = torch.nn.functional.max_pool1d(x[:, None], kernel, stride=1, padding=kernel // 2)[:, 0]
+    assert torch.equal(out.cpu(), ref)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype,rg,window", [
+    (1, 8, 2, 2300, 128, "bf16", True, 0),      # pieces of three tiles, shorter than a key block's diagonal
+    (1, 4, 4, 3001, 64, "f16", True, 0),        # ragged end, one head a row: pieces of twelve tiles
+    (1, 4, 4, 4400, 128, "bf16", False, 0),     # the last size with a share below half a piece
+    (1, 32, 8, 2100, 128, "bf16", True, 0),     # 264 query blocks: not cut
+    (1, 32, 8, 5000, 128, "bf16", True, 200),   # a window of four tiles: two chunks
+    (2, 8, 8, 3500, 128, "bf16", True, 65),     # blocks cut for 256 workgroups
+    (1, 4, 2, 9000, 64, "f16", True, 0),        # blocks cut for 512: slices of 64 tiles and more
+])
+def test_scores_of_medium_prompts(kv, oracle, B, Hq, Hkv, S, D, dtype, rg, window):
+    """Sizes around the lines at which both passes are cut finer to fill the chip.  The fp32 sums of
+    at most S * Hq / Hkv exponentials, each off by no more than 1e-5 for these logits (below 8: 128 products of
+    2^-24 each, on either side of the normaliser), stay within 1e-4."""
+    say(f"medium prompt B={B} Hq={Hq} Hkv={Hkv} S={S} D={D} {dtype} reduce={rg} window={window}")
+    w = inputs.Workload("t", B, Hq, Hkv, S, D, dtype, max(1, S // 4), 0.5, "alternating", rg)
+    q, k, _ = inputs.make_qkv(w, S + Hq, want_v=False)
+    assert (q.float().norm(dim=-1).max() * k.float().norm(dim=-1).max() / D ** 0.5).item() < 4 * 8  # (Cauchy bound)
+    ref = oracle.scores(q, k, rg, window=window, threads=THREADS)
+    sc, _ = kv.kvcrush_scores(q.cuda(), k.cuda(), rg, window=window)
+    torch.cuda.synchronize()
+    assert rel_err(sc, ref) <= 1e-4
+
+
 def test_scores_extreme_logits(kv, oracle):
     """Logits that grow by hundreds along the sequence: the exponentials' fixed
     reference has to be re-based on the fly (and early keys underflow to zero)."""
