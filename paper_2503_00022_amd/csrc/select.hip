@@ -935,9 +935,10 @@ __global__ __launch_bounds__(kSelThreads) void emit_kernel(EmitParams p) {
   emit_sequence<kSelThreads>(p, blockIdx.x, sh);
 }
 
-// =========================================== token-level selection in three launches ==
-// The usual case (tokens, not units, as the selected items; at most 128 score rows; rows
-// that fit the LDS tables below).  Every step that needs a view of a whole row or a whole
+// =========================================== selection with the rows spread over the chip ==
+// The usual case (at most 128 score rows; rows that fit the tables below; units as well, with
+// unit_rows_kernel after F2 and medoid_units_emit_kernel as F3: 2048 pages of 16 tokens, 8 score
+// rows, 72 us through the general kernels and 46 us so).  Every step that needs a view of a whole row or a whole
 // sequence is a serial chain of short phases, so the stage is bound by how many such chains
 // follow each other and by the fixed cost of a launch.  Three launches:
 //
@@ -964,7 +965,7 @@ constexpr int kFastMaxTokens = 32768;  // a row's keys live in its workgroup's r
 
 struct FastParams {
   const float* scores;   // first selectable token of row 0 of sequence 0; rows are `ld` floats apart
-  float* imp;            // [B,S] token importances (F1 -> F2)
+  float* imp;            // [B,n_units] token (unit) importances (F1 -> F2)
   uint16_t* phist;       // [B,Hs+1,nsl,2048] slice histograms (F1 -> F2)
   uint32_t* counters;    // [B,4]: rows finished, bucket workgroups finished
   uint64_t* rowmask;     // [B,Hs+1,nw]; row Hs = important tokens
@@ -973,7 +974,8 @@ struct FastParams {
   size_t bits_stride;
   int32_t* order;        // [B,S]: first N entries = grouped tokens by (distance, token)
   int Hs, S, nw, ld, kbit, n_important;
-  int slice, nsl;        // tokens per slice, slices per row
+  int slice, nsl;        // tokens per slice (whole units), slices per row
+  int unit, n_units;     // tokens per unit ranked by the importance row, and how many
   int row0, rows;        // rows handled: all Hs + 1, or the importance row alone
   int W, N, Br;
   int tail;              // 1: the row's workgroup writes the index list (plain top-n: no representatives)
@@ -998,8 +1000,12 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, uint32_t bin, bool vali
   }
 }
 
+// UNITS: the importance row ranks units of p.unit tokens (an instantiation of its own: the token level
+// keeps its 8 KiB of LDS and its straight loop).
+template <bool UNITS>
 __global__ __launch_bounds__(kSliceThreads) void slice_hist_kernel(FastParams p) {
   __shared__ __align__(16) uint32_t hist[kRadixBins];
+  __shared__ float parked[UNITS ? kSliceTokens : 1];  // importance row of units: the slice's token importances
   const int s = blockIdx.x, row = p.row0 + blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
   const int Hs = p.Hs;
   for (int i = tid; i < kRadixBins; i += kSliceThreads) hist[i] = 0;
@@ -1008,6 +1014,7 @@ __global__ __launch_bounds__(kSliceThreads) void slice_hist_kernel(FastParams p)
   const float* __restrict__ sc = p.scores + (size_t)b * Hs * p.ld;
   const size_t ld = (size_t)p.ld;
   const int t0 = s * p.slice, t1 = min(p.S, t0 + p.slice);
+  const bool unit_row = UNITS && row == Hs;
   constexpr int kU = 8;  // tokens per thread in flight
   for (int base = t0 + tid; base < t1; base += kU * kSliceThreads) {
     float v[kU];
@@ -1048,9 +1055,15 @@ __global__ __launch_bounds__(kSliceThreads) void slice_hist_kernel(FastParams p)
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
         const int t = base + u * kSliceThreads;
-        if (t < t1) p.imp[(size_t)b * p.S + t] = v[u];
+        if (t < t1) {
+          if (unit_row)
+            parked[t - t0] = v[u];
+          else
+            p.imp[(size_t)b * p.S + t] = v[u];
+        }
       }
     }
+    if (unit_row) continue;  // uniform
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const int t = base + u * kSliceThreads;
@@ -1058,6 +1071,20 @@ __global__ __launch_bounds__(kSliceThreads) void slice_hist_kernel(FastParams p)
     }
   }
   __syncthreads();
+  if (unit_row) {
+    // unit importance: its tokens' importances added in token order (t0 and t1 are whole units)
+    const int n = (t1 - t0) / p.unit;
+    for (int u0 = 0; u0 < n; u0 += kSliceThreads) {
+      const int u = u0 + tid;
+      float acc = 0.0f;
+      if (u < n) {
+        for (int j = 0; j < p.unit; ++j) acc = acc + parked[u * p.unit + j];
+        p.imp[(size_t)b * p.n_units + t0 / p.unit + u] = acc;
+      }
+      hist_add(hist, float_key(acc) >> 21, u < n);
+    }
+    __syncthreads();
+  }
   // eight bins per thread, as 16-bit counts (a slice has fewer than 65536 tokens)
   uint16_t* __restrict__ out = p.phist + (((size_t)b * (Hs + 1) + row) * p.nsl + s) * kRadixBins;
   const uint4 a = *(const uint4*)&hist[8 * tid], c = *(const uint4*)&hist[8 * tid + 4];
@@ -1086,9 +1113,9 @@ __global__ __launch_bounds__(kSelThreads) void row_select_kernel(FastParams p) {
 
   const int row = p.row0 + blockIdx.x, b = blockIdx.y;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / KVC_WAVE;
-  const int Hs = p.Hs, S = p.S, nw = p.nw;
+  const int Hs = p.Hs, S = row < Hs ? p.S : p.n_units, nw = (S + 63) / 64;
   const int k = row < Hs ? p.kbit : p.n_important;
-  uint64_t* __restrict__ mask_out = p.rowmask + ((size_t)b * (Hs + 1) + row) * nw;
+  uint64_t* __restrict__ mask_out = p.rowmask + ((size_t)b * (Hs + 1) + row) * p.nw;
   const float* __restrict__ src =
       row < Hs ? p.scores + ((size_t)b * Hs + row) * p.ld : p.imp + (size_t)b * S;
 
@@ -1291,6 +1318,73 @@ __global__ __launch_bounds__(kSelThreads) void medoid_emit_kernel(FastParams p) 
   emit_sequence<kSelThreads>(p.emit, b, sh);
 }
 
+// The same for units, whose buckets are few and whose vectors are long (page level: 16 buckets of 125
+// pages with 128 bits).  One wave per bucket counted and priced 2 x 128 bits of every 64 members one
+// after the other (26.6 us); here `share` waves take `bits_per_wave` bits each (8 to 64, inside one
+// word), their costs meet in LDS, and the list follows in the same launch (with it 10 us).
+__global__ __launch_bounds__(kSelThreads) void medoid_units_emit_kernel(MedoidParams p, EmitParams e, uint32_t* counters,
+                                                                       int bits_per_wave, int share) {
+  __shared__ EmitScratch sh;
+  __shared__ uint32_t sh_last;
+  __shared__ unsigned int part[kSelWaves][KVC_WAVE];
+  const int b = blockIdx.y, lane = lane_id(), wave = threadIdx.x / KVC_WAVE;
+  const int sub = wave % share;
+  const int j = blockIdx.x * (kSelWaves / share) + wave / share;  // bucket of this wave
+  const bool live = j < p.Br;
+  const long long lo = live ? (long long)j * p.N / p.Br : 0, hi = live ? (long long)(j + 1) * p.N / p.Br : 0;
+  const int n = (int)(hi - lo);
+  const int longest = p.Br > 0 ? (p.N + p.Br - 1) / p.Br : 0;  // members of any bucket: the workgroup's common trip count
+  const int r0 = sub * bits_per_wave, nb = max(0, min(bits_per_wave, p.Hs - r0));  // this wave's bits
+  const int w = min(r0 >> 6, p.W - 1), shift = r0 & 63;
+  const int32_t* order = p.order + (size_t)b * p.S + lo;
+  const uint64_t* bits = p.bits + (size_t)b * p.bits_stride * p.W;
+  auto member = [&](int m, int& t) -> uint64_t {
+    t = m < n ? min(max(order[m], 0), p.S - 1) : 0;
+    return m < n ? bits[(size_t)t * p.W + w] >> shift : 0ull;
+  };
+  int cnt = 0;  // lane l: members with bit r0 + l set
+  for (int m0 = 0; m0 < n; m0 += KVC_WAVE) {
+    int t;
+    const uint64_t bw = member(m0 + lane, t);
+    for (int rr = 0; rr < nb; ++rr) {
+      const int c = __popcll(__ballot((bw >> rr) & 1ull));
+      if (lane == rr) cnt += c;
+    }
+  }
+  unsigned long long best = ~0ull;
+  for (int m0 = 0; m0 < longest; m0 += KVC_WAVE) {
+    int t;
+    const uint64_t bw = member(m0 + lane, t);
+    unsigned int cost = 0;
+    for (int rr = 0; rr < nb; ++rr) {
+      const int c = __builtin_amdgcn_readlane(cnt, rr);
+      cost += ((bw >> rr) & 1ull) ? (unsigned)(n - c) : (unsigned)c;
+    }
+    part[wave][lane] = cost;
+    __syncthreads();
+    if (sub == 0 && m0 + lane < n) {
+      unsigned int total = 0;
+      for (int i = 0; i < share; ++i) total += part[wave + i][lane];
+      const unsigned long long key = ((unsigned long long)total << 32) | (unsigned)t;
+      best = key < best ? key : best;
+    }
+    __syncthreads();
+  }
+  if (sub == 0 && n > 0) {
+#pragma unroll
+    for (int off = KVC_WAVE / 2; off > 0; off >>= 1) {
+      const unsigned long long o = __shfl_xor(best, off);
+      best = o < best ? o : best;
+    }
+    if (lane == 0) {
+      const int t = (int)(best & 0xFFFFFFFFull);
+      atomicOr((unsigned long long*)&p.repmask[(size_t)b * p.nw + (t >> 6)], 1ull << (t & 63));
+    }
+  }
+  if (!arrive_last(&counters[(size_t)b * 4 + 1], gridDim.x, &sh_last)) return;
+  emit_sequence<kSelThreads>(e, b, sh);
+}
+
 // ------------------------------------------------------------- host side ---
 // What the kernels work on.  K1 ranks TOKENS (the middle ones, when ends are
 // protected) per score row; the grouping, the representatives and the emitted
@@ -1302,7 +1396,7 @@ struct SelectPlan {
   int budget_items, imp_items; // kept / important items
   int cpw, n_wg, n_gw;         // chunks per grouping workgroup, workgroups / global waves per sequence
   bool keys_in_lds;
-  // three-launch path (tokens as items, few score rows, tables that fit LDS)
+  // short path (few score rows, rows that fit the tables)
   bool fast;
   int slice, nsl;              // tokens per histogram slice, slices per row
   // workspace offsets
@@ -1339,7 +1433,8 @@ bool select_args_supported(const kvcrush_select_args* a) {
   return a->Hs * unit <= kMaxHs;
 }
 
-SelectPlan select_plan(const kvcrush_select_args* a, bool need_bits_ws) {
+// units_fast: whether units may take the short path, which needs more scratch memory than the general one.
+SelectPlan select_plan(const kvcrush_select_args* a, bool need_bits_ws, bool units_fast = true) {
   SelectPlan P;
   P.unit = a->unit > 1 ? a->unit : 1;
   P.S_tok = a->S - a->n_sink - a->n_recent;
@@ -1380,12 +1475,13 @@ SelectPlan select_plan(const kvcrush_select_args* a, bool need_bits_ws) {
   if (need_bits_ws) off += kvc::align_up(B * P.n_items * P.W * 8, 256);
   P.keys = off;
   if (!P.keys_in_lds) off += kvc::align_up(B * (a->Hs + 1) * P.S_tok * 4, 256);
-  // the short path: per-slice histograms, token importances, arrival counters
-  P.slice = kSliceTokens;
+  // the short path: per-slice histograms, token or unit importances, arrival counters
+  // (whole units per slice; a unit has at most kMaxHs tokens)
+  P.slice = P.unit <= kSliceTokens ? kSliceTokens / P.unit * P.unit : kSliceTokens;
   P.nsl = P.S_tok > 0 ? (P.S_tok + P.slice - 1) / P.slice : 0;
-  P.fast = P.unit == 1 && a->Hs <= kFastMaxRows && P.S_tok > 0 && P.S_tok <= kFastMaxTokens;
+  P.fast = (P.unit == 1 || units_fast) && a->Hs <= kFastMaxRows && P.S_tok > 0 && P.S_tok <= kFastMaxTokens;
   P.imp = off;
-  if (P.fast) off += kvc::align_up(B * P.S_tok * 4, 256);
+  if (P.fast) off += kvc::align_up(B * P.n_items * 4, 256);
   P.phist = off;
   if (P.fast) off += kvc::align_up(B * (a->Hs + 1) * P.nsl * kRadixBins * 2, 256);
   P.counters = off;
@@ -1474,7 +1570,7 @@ extern "C" kvcrush_status kvcrush_select_static(const kvcrush_select_args* args,
   if (!select_args_supported(args)) return KVCRUSH_ERR_UNSUPPORTED;
   // (every buffer of the workspace, the arrival counters included, is written inside a call
   // before that call reads it, so the previous call's contents need no clearing)
-  const SelectPlan P = select_plan(args, bits == nullptr);
+  const SelectPlan P = select_plan(args, bits == nullptr, false);  // (the least a call can do with)
   if (!plan_fits_lds(P)) return KVCRUSH_ERR_UNSUPPORTED;
   if (P.total > (size_t)KVCRUSH_SELECT_STATIC_MAX_BYTES) return KVCRUSH_ERR_WORKSPACE;
   void* ptr = static_scratch_for_current_device();
@@ -1491,7 +1587,9 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
   if (!scores || (!idx && args->budget > 0)) return KVCRUSH_ERR_INVALID_ARG;
   if (!kvc::aligned16(scores) || !kvc::aligned16(workspace) || (bits && !kvc::aligned16(bits)))
     return KVCRUSH_ERR_INVALID_ARG;
-  const SelectPlan P = select_plan(args, bits == nullptr);
+  SelectPlan P = select_plan(args, bits == nullptr);
+  // units with less scratch memory than the short path needs take the general one
+  if (P.unit > 1 && P.total > workspace_bytes) P = select_plan(args, bits == nullptr, false);
   if (P.total > 0 && (!workspace || workspace_bytes < P.total)) return KVCRUSH_ERR_WORKSPACE;
   if (!plan_fits_lds(P)) return KVCRUSH_ERR_UNSUPPORTED;
 
@@ -1537,7 +1635,7 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
     f.imp = (float*)(ws + P.imp);
     f.phist = (uint16_t*)(ws + P.phist);
     f.counters = (uint32_t*)(ws + P.counters);
-    f.rowmask = rowmask;
+    f.rowmask = rowmask_tok;
     f.repmask = repmask;
     f.bits = bits_buf;
     f.bits_stride = bits_stride;
@@ -1550,6 +1648,8 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
     f.n_important = P.imp_items;
     f.slice = P.slice;
     f.nsl = P.nsl;
+    f.unit = P.unit;
+    f.n_units = P.n_items;
     f.row0 = plain_topk ? Hs : 0;
     f.rows = plain_topk ? 1 : Hs + 1;
     f.W = P.W;
@@ -1570,7 +1670,8 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
 
   // ---- per-row top-k -> row bitmaps
   if (fast) {
-    kvcrush_status st = kvc::launch(slice_hist_kernel, dim3(P.nsl, f.rows, B), dim3(kSliceThreads), 0, stream, f);
+    kvcrush_status st = token_level ? kvc::launch(slice_hist_kernel<false>, dim3(P.nsl, f.rows, B), dim3(kSliceThreads), 0, stream, f)
+                                    : kvc::launch(slice_hist_kernel<true>, dim3(P.nsl, f.rows, B), dim3(kSliceThreads), 0, stream, f);
     if (st != KVCRUSH_OK) return st;
     st = kpt16 ? kvc::launch(row_select_kernel<16>, dim3(f.rows, B), dim3(kSelThreads), row_lds, stream, f)
                : kvc::launch(row_select_kernel<32>, dim3(f.rows, B), dim3(kSelThreads), row_lds, stream, f);
@@ -1608,6 +1709,7 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
     if (st != KVCRUSH_OK) return st;
   }
   // ---- bit words, distances, stable order by (distance, item); representatives
+  MedoidParams m;
   if (P.n_items > 0 && !plain_topk) {
     GroupParams g;
     g.rowmask = rowmask;
@@ -1631,7 +1733,6 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
     while ((1 << dbits) <= P.Hv) ++dbits;  // distances range over 0..Hv
     g.dbits = dbits;
     g.n_gw = P.n_gw;
-    MedoidParams m;
     m.bits = bits_buf;
     m.bits_stride = bits_stride;
     m.order = order;
@@ -1647,14 +1748,26 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
       st = P.cpw == 4 ? launch_grouping<2, 4>(g, m, P, B, Br, !fast, stream)
                       : launch_grouping<2, kGsChunksPerWg>(g, m, P, B, Br, !fast, stream);
     else if (P.W <= 4)
-      st = P.cpw == 4 ? launch_grouping<4, 4>(g, m, P, B, Br, true, stream)
-                      : launch_grouping<4, kGsChunksPerWg>(g, m, P, B, Br, true, stream);
+      st = P.cpw == 4 ? launch_grouping<4, 4>(g, m, P, B, Br, !fast, stream)
+                      : launch_grouping<4, kGsChunksPerWg>(g, m, P, B, Br, !fast, stream);
     else
-      st = P.cpw == 4 ? launch_grouping<kMaxW, 4>(g, m, P, B, Br, true, stream)
-                      : launch_grouping<kMaxW, kGsChunksPerWg>(g, m, P, B, Br, true, stream);
+      st = P.cpw == 4 ? launch_grouping<kMaxW, 4>(g, m, P, B, Br, !fast, stream)
+                      : launch_grouping<kMaxW, kGsChunksPerWg>(g, m, P, B, Br, !fast, stream);
     if (st != KVCRUSH_OK) return st;
   }
   // ---- the ascending index list
+  if (fast && !token_level) {
+    // bits a wave takes of a bucket: as few as leave sixteen waves a compute unit, a power of two
+    int per = 8, share;
+    for (;; per *= 2) {
+      share = 1;
+      while (share * per < P.Hv) share *= 2;
+      if (per == 64 || (share <= kSelWaves && (long long)Br * B * share <= 4096)) break;
+    }
+    const int per_wg = kSelWaves / share;  // buckets of a workgroup (share <= 16: Hv is at most 1024)
+    return kvc::launch(medoid_units_emit_kernel, dim3(std::max(1, (Br + per_wg - 1) / per_wg), B), dim3(kSelThreads), 0,
+                       stream, m, ep, f.counters, per, share);
+  }
   if (fast)  // representatives and the list in one launch
     return kvc::launch(medoid_emit_kernel, dim3(std::max(1, (Br + kSelWaves - 1) / kSelWaves), B),
                        dim3(kSelThreads), 0, stream, f);
