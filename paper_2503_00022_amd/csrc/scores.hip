@@ -754,6 +754,9 @@ struct WaveTile {
   }
 };
 
+// This wave's tile has landed, and its reads of the buffer that is filled next are done.
+__device__ __forceinline__ void wait_own_tile() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
+
 template <bool BF16, int D, bool F16 = false, bool STRIDED = false>
 __global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void lse_short_kernel(ScoreParams p) {
   using C = Cfg<BF16, D>;
@@ -779,7 +782,7 @@ __global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void lse_sh
     const int off0 = lds_frag_offset0<C>(lane);
     int cur = 0;
     for (int t = wave; t <= blk; t += W, cur ^= 1) {
-      wait_async_loads();
+      wait_own_tile();
       if (t + W <= blk) tile.load(kh, (t + W) * 32, S, dst + (cur ^ 1) * C::kSubBytes);
       f32x16 acc;
 #pragma unroll
@@ -857,7 +860,7 @@ __global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void colsum
     int cur = 0;
     for (int pair = wave; pair < n_pairs; pair += W, cur ^= 1) {
       const int tile = t_first + t, qi = tile * 32 + (lane & 31);
-      wait_async_loads();
+      wait_own_tile();
       // rows past the end and rows before an observation window contribute nothing
       const float lse2 = (qi < S && qi >= p.q_first) ? raw * kLog2e : INFINITY;
       t += W;
