@@ -8,10 +8,10 @@
 // (B*Hkv*S*D*sizeof bytes); the exponentials and the fp32 dot products are far
 // below the VALU's rate at that pace.
 //
-//   append_logits_mfma_kernel  (bf16 / fp16) workgroup = 256 keys of one KV head
-//                          (dense cache or paged pool): four
+//   append_logits_mfma_kernel  (bf16 / fp16) workgroup = 128 keys of one KV head
+//                          (dense cache or paged pool): two
 //                          64-row K tiles go global -> LDS asynchronously, each
-//                          wave multiplies its tile with the query vectors of
+//                          wave multiplies half a tile with the query vectors of
 //                          the KV group's heads (the 32 columns of a 32x32x16
 //                          MFMA; unused columns are zero), so K is read once for
 //                          the whole group and the dot products cost the VALU
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void append_logits_kernel(AppendParams p)
   }
 }
 
-// bf16: logits of 256 keys x up to 32 heads per pass on the matrix cores.
+// bf16: logits of 64 * TPW keys x up to 32 heads per pass on the matrix cores.
 // TPW: 64-row tiles per workgroup (4: one tile per wave; 2: two waves share a tile, one 32-row half
 // each, which halves the LDS per workgroup so that more of them overlap their loads on a CU).
 template <int D, int TPW, bool F16>
@@ -355,9 +355,11 @@ size_t logits_bytes(const kvcrush_shape* s) {
   return kvc::align_up((size_t)s->B * s->Hq * s->S * sizeof(float), 256);
 }
 
-// Keys per workgroup of the logits kernel.  (Two tiles per workgroup on the matrix-core path, 128 keys,
-// measured no faster than four: the kernel is not short of loads in flight.)
-constexpr int kMfmaTilesPerWg = 4;
+// Keys per workgroup of the logits kernel.  Two 64-row tiles on the matrix-core path: half the LDS, so that
+// four workgroups instead of two share a compute unit and one's loads run under another's sums.  Four tiles ->
+// two, with D = 128: 4 sequences of up to 32768 keys, 218 MB of K in scattered blocks 55.9 -> 47.6 us
+// (4.6 TB/s); 8 sequences of 2048 keys 11.6 -> 9.8 us.
+constexpr int kMfmaTilesPerWg = 2;
 int logit_keys(const kvcrush_shape* s) { return s->dtype != KVCRUSH_F32 ? 64 * kMfmaTilesPerWg : kKeysPerWg; }
 
 int key_blocks(const kvcrush_shape* s) { return (s->S + logit_keys(s) - 1) / logit_keys(s); }
@@ -384,7 +386,8 @@ constexpr long long kUpdateWorkgroups = 1024;
 template <bool BF16, int D, bool F16 = false>
 kvcrush_status launch_append(const AppendParams& p, hipStream_t stream) {
   // (the heads of a KV cache run side by side: a paged pool holds a token's heads next to each other.
-  // 4 sequences of up to 32768 keys, 8 KV heads, 218 MB of K in 16-token blocks: 59.2 us head by head, 55.9 so)
+  // 4 sequences of up to 32768 keys, 8 KV heads, 218 MB of K in 16-token blocks, with 256 keys a
+  // workgroup: 59.2 us head by head, 55.9 so)
   if ((long long)p.n_kb * p.Hkv > 0x7FFFFFFFll) return KVCRUSH_ERR_UNSUPPORTED;
   const dim3 grid((unsigned)(p.n_kb * p.Hkv), p.B);
   kvcrush_status st;
