@@ -921,14 +921,15 @@ ColsumPlan colsum_plan(int S, int tile, int chunk_tiles_wanted, int q_first) {
 // A share between half a piece and a whole one gains nothing by the cut and pays for its second
 // prologue: S = 4096, 32 heads in 8 groups 175 uncut, 181 to 199 in pieces of 34 to 54 steps.
 constexpr int kPieceSteps = 72, kMinPieceSteps = 12, kPiecesWanted = 384;
-int chunk_tiles_for(int tile, int heads_per_row, long long rows, int S, int q_first) {
+// fine: false where the scratch memory at hand only holds the partial sums of whole pieces.
+int chunk_tiles_for(int tile, int heads_per_row, long long rows, int S, int q_first, bool fine) {
   const long long n_tiles = (S + tile - 1) / tile, tile0 = q_first / tile, n_kb = (S + kKeysPerWg - 1) / kKeysPerWg;
   // tiles from an observation window's first on that the key blocks see: all for the first `whole`
   // blocks, then from each block's own first tile on
   const long long tpk = kKeysPerWg / tile, whole = std::min(n_kb, tile0 / tpk + 1);
   const long long seen = whole * (n_tiles - tile0) + (n_kb - whole) * n_tiles - tpk * ((whole + n_kb - 1) * (n_kb - whole) / 2);
   const long long fair = seen * heads_per_row * rows / kPiecesWanted * tile / 64;  // (fp32 tiles hold 32 queries)
-  const int steps64 = 2 * fair > kPieceSteps ? kPieceSteps : std::max((int)fair, kMinPieceSteps);
+  const int steps64 = !fine || 2 * fair > kPieceSteps ? kPieceSteps : std::max((int)fair, kMinPieceSteps);
   const int tiles = (steps64 * 64 / tile + heads_per_row - 1) / heads_per_row;
   return std::max(3, (tiles + 2) / 3 * 3);
 }
@@ -1036,12 +1037,12 @@ kvcrush_status launch_short(ScoreParams p, const float* lse_user, bool lse_only,
 
 template <bool BF16, int D, bool F16 = false>
 kvcrush_status launch_scores(const ScoreParams& base, const float* lse_user, float2* split_ml,
-                             bool lse_only, hipStream_t stream) {
+                             bool lse_only, bool fine, hipStream_t stream) {
   using C = Cfg<BF16, D>;
   ScoreParams p = base;
   const long long rows = (long long)p.B * (p.reduce_groups ? p.Hkv : p.Hq);
   const ColsumPlan pl =
-      colsum_plan(p.S, C::kTile, chunk_tiles_for(C::kTile, p.reduce_groups ? p.G : 1, rows, p.S, p.q_first), p.q_first);
+      colsum_plan(p.S, C::kTile, chunk_tiles_for(C::kTile, p.reduce_groups ? p.G : 1, rows, p.S, p.q_first, fine), p.q_first);
   if (!lse_only && pl.pieces * rows > kMaxGridX) return KVCRUSH_ERR_UNSUPPORTED;  // before anything is enqueued
   if (short_prompt(p)) return launch_short<BF16, D, F16>(p, lse_user, lse_only, stream);
   if (!lse_user) {
@@ -1074,10 +1075,10 @@ size_t lse_bytes(const kvcrush_shape* s) {
   return kvc::align_up((size_t)s->B * s->Hq * s->S * sizeof(float), 256);
 }
 
-size_t partial_bytes(const kvcrush_shape* s) {
+size_t partial_bytes(const kvcrush_shape* s, bool fine) {
   const int tile = s->dtype != KVCRUSH_F32 ? 64 : 32;
   const size_t rows = (size_t)s->B * (s->reduce_groups ? s->Hkv : s->Hq);
-  const int chunk = chunk_tiles_for(tile, s->reduce_groups ? s->Hq / s->Hkv : 1, (long long)rows, s->S, first_query(s));
+  const int chunk = chunk_tiles_for(tile, s->reduce_groups ? s->Hq / s->Hkv : 1, (long long)rows, s->S, first_query(s), fine);
   const ColsumPlan pl = colsum_plan(s->S, tile, chunk, first_query(s));
   if (pl.n_chunks <= 1) return 0;
   return kvc::align_up(rows * pl.n_kb * pl.n_chunks * kKeysPerWg * sizeof(float), 256);
@@ -1129,7 +1130,7 @@ bool shape_ok(const kvcrush_shape* s) {
 
 kvcrush_status scores_entry(const kvcrush_shape* shape, const void* q, const void* k,
                             const float* lse, float* lse_out, float* partial, float2* split_ml,
-                            float* scores, bool lse_only, hipStream_t stream) {
+                            float* scores, bool lse_only, bool fine, hipStream_t stream) {
   const long long blocks_a = (long long)shape->B * shape->Hq * ((shape->S + 63) / 64);
   if (blocks_a > 0x3FFFFFFFll) return KVCRUSH_ERR_UNSUPPORTED;
   if ((long long)shape->B * shape->Hq > kMaxGridY) return KVCRUSH_ERR_UNSUPPORTED;  // second grid dimension
@@ -1166,21 +1167,21 @@ kvcrush_status scores_entry(const kvcrush_shape* shape, const void* q, const voi
   p.scale_log2 = (float)(1.4426950408889634 *
                          (shape->softmax_scale != 0.0f ? (double)shape->softmax_scale : 1.0 / sqrt((double)shape->D)));
   if (shape->dtype == KVCRUSH_F16) {
-    if (shape->D == 128) return launch_scores<true, 128, true>(p, lse, split_ml, lse_only, stream);
-    return launch_scores<true, 64, true>(p, lse, split_ml, lse_only, stream);
+    if (shape->D == 128) return launch_scores<true, 128, true>(p, lse, split_ml, lse_only, fine, stream);
+    return launch_scores<true, 64, true>(p, lse, split_ml, lse_only, fine, stream);
   }
   const bool bf16 = shape->dtype == KVCRUSH_BF16;
-  if (bf16 && shape->D == 128) return launch_scores<true, 128>(p, lse, split_ml, lse_only, stream);
-  if (bf16 && shape->D == 64) return launch_scores<true, 64>(p, lse, split_ml, lse_only, stream);
-  if (!bf16 && shape->D == 128) return launch_scores<false, 128>(p, lse, split_ml, lse_only, stream);
-  return launch_scores<false, 64>(p, lse, split_ml, lse_only, stream);
+  if (bf16 && shape->D == 128) return launch_scores<true, 128>(p, lse, split_ml, lse_only, fine, stream);
+  if (bf16 && shape->D == 64) return launch_scores<true, 64>(p, lse, split_ml, lse_only, fine, stream);
+  if (!bf16 && shape->D == 128) return launch_scores<false, 128>(p, lse, split_ml, lse_only, fine, stream);
+  return launch_scores<false, 64>(p, lse, split_ml, lse_only, fine, stream);
 }
 
 }  // namespace
 
 extern "C" size_t kvcrush_scores_workspace(const kvcrush_shape* shape) {
   if (!shape_ok(shape)) return 0;
-  return lse_bytes(shape) + partial_bytes(shape) + split_bytes(shape);
+  return lse_bytes(shape) + partial_bytes(shape, true) + split_bytes(shape);
 }
 
 extern "C" size_t kvcrush_row_lse_workspace(const kvcrush_shape* shape) {
@@ -1196,12 +1197,16 @@ extern "C" kvcrush_status kvcrush_scores(const kvcrush_shape* shape, const void*
   if (!q || !k || !scores) return KVCRUSH_ERR_INVALID_ARG;
   if (!kvc::aligned16(q) || !kvc::aligned16(k) || !kvc::aligned16(scores) || !kvc::aligned16(lse))
     return KVCRUSH_ERR_INVALID_ARG;
-  if (!workspace || !kvc::aligned16(workspace) || workspace_bytes < kvcrush_scores_workspace(shape))
-    return KVCRUSH_ERR_WORKSPACE;
+  // Finer pieces need more partial sums: a caller with less memory (one buffer sized for the longest of
+  // many prompts, which is cut less) gets whole pieces.
+  const size_t rest = lse_bytes(shape) + split_bytes(shape);
+  const bool fine = workspace_bytes >= rest + partial_bytes(shape, true);
+  const size_t partial_size = partial_bytes(shape, fine);
+  if (!workspace || !kvc::aligned16(workspace) || workspace_bytes < rest + partial_size) return KVCRUSH_ERR_WORKSPACE;
   float* partial = (float*)((char*)workspace + lse_bytes(shape));
   float2* split_ml =
-      split_bytes(shape) ? (float2*)((char*)workspace + lse_bytes(shape) + partial_bytes(shape)) : nullptr;
-  return scores_entry(shape, q, k, lse, (float*)workspace, partial, split_ml, scores, false,
+      split_bytes(shape) ? (float2*)((char*)workspace + lse_bytes(shape) + partial_size) : nullptr;
+  return scores_entry(shape, q, k, lse, (float*)workspace, partial, split_ml, scores, false, fine,
                       (hipStream_t)hip_stream);
 }
 
@@ -1218,7 +1223,7 @@ extern "C" kvcrush_status kvcrush_row_lse(const kvcrush_shape* shape, const void
     if (!kvc::aligned16(workspace) || workspace_bytes < split_bytes(shape)) return KVCRUSH_ERR_WORKSPACE;
     if (split_bytes(shape)) split_ml = (float2*)workspace;
   }
-  return scores_entry(shape, q, k, nullptr, lse_out, nullptr, split_ml, nullptr, true,
+  return scores_entry(shape, q, k, nullptr, lse_out, nullptr, split_ml, nullptr, true, true,
                       (hipStream_t)hip_stream);
 }
 
