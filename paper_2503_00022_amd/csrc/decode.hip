@@ -8,11 +8,11 @@
 // (B*Hkv*S*D*sizeof bytes); the exponentials and the fp32 dot products are far
 // below the VALU's rate at that pace.
 //
-//   append_logits_mfma_kernel  (bf16 / fp16) workgroup = 128 keys of one KV head
-//                          (dense cache or paged pool): two
+//   append_logits_mfma_kernel  (bf16 / fp16) workgroup = 256 keys of one KV head
+//                          (dense cache or paged pool), at once or in two steps:
 //                          64-row K tiles go global -> LDS asynchronously, each
-//                          wave multiplies half a tile with the query vectors of
-//                          the KV group's heads (the 32 columns of a 32x32x16
+//                          wave multiplies half a tile with the query
+//                          vectors of the KV group's heads (the 32 columns of a 32x32x16
 //                          MFMA; unused columns are zero), so K is read once for
 //                          the whole group and the dot products cost the VALU
 //                          nothing.  Leaves base-2 logits in the workspace and
@@ -48,7 +48,7 @@ struct AppendParams {
                            // [n_blocks,block_size,Hkv,D] and block_table [B,capacity/block_size]
   int block_size;
   int B, Hq, Hkv, S, capacity, G, reduce_groups;  // S: valid tokens, or their upper bound with lengths
-  int logit_keys, n_kb;  // keys per workgroup of the logits kernel, and how many such blocks S has
+  int n_kb;            // kKeysPerWg-key blocks of S
   float scale_log2;    // log2(e) x softmax scale (1 / sqrt(D) unless the caller set one)
 };
 
@@ -112,8 +112,8 @@ __global__ __launch_bounds__(kThreads) void append_logits_kernel(AppendParams p)
   __shared__ float red[kWaves];
 
   const int tid = threadIdx.x, lane = kvc::lane_id(), wave = tid / KVC_WAVE;
-  const int kb = blockIdx.x / p.Hkv, g = blockIdx.x % p.Hkv, b = blockIdx.y;
-  const int bg = b * p.Hkv + g;
+  const int kb = blockIdx.x, bg = blockIdx.y;  // bg = b * Hkv + kv head
+  const int b = bg / p.Hkv, g = bg % p.Hkv;
   const int S = p.lengths ? min(max(p.lengths[b], 1), p.S) : p.S;
   const int k0 = kb * kKeysPerWg;
   if (k0 >= S) return;  // this sequence is shorter than the launch's upper bound (uniform exit)
@@ -169,46 +169,51 @@ __global__ __launch_bounds__(kThreads) void append_logits_kernel(AppendParams p)
   }
 }
 
-// bf16: logits of 64 * TPW keys x up to 32 heads per pass on the matrix cores.
-// TPW: 64-row tiles per workgroup (4: one tile per wave; 2: two waves share a tile, one 32-row half
-// each, which halves the LDS per workgroup so that more of them overlap their loads on a CU).
-template <int D, int TPW, bool F16>
-__global__ __launch_bounds__(kThreads) void append_logits_mfma_kernel(AppendParams p) {
+// bf16 / fp16: logits of kKeysPerWg keys x up to 32 heads per pass on the matrix cores, 32 keys a wave.
+// Bound by reading K.  WAVES = 8: all keys at once.  WAVES = 4: two steps of half the keys through half the
+// LDS, for launches of many workgroups: four of them instead of two share a compute unit, so that more keys
+// are on their way while one workgroup multiplies and stores.  Either way one pair per 256 keys.
+template <int D, int WAVES, bool F16>
+__global__ __launch_bounds__(WAVES * KVC_WAVE, 4) void append_logits_mfma_kernel(AppendParams p) {
   using C = Cfg<true, D>;
-  constexpr int kSubs = 2 * TPW / kWaves;  // 32-row halves a wave multiplies: 2 or 1
-  __shared__ __attribute__((aligned(1024))) char lds[TPW][C::kTileBytes];
-  __shared__ float red[2][kWaves][32];
+  constexpr int kStepKeys = 32 * WAVES, kTiles = kStepKeys / C::kTile, kTeams = WAVES / kWaves;
+  static_assert(kKeysPerWg % kStepKeys == 0 && WAVES % kWaves == 0 && kTiles % kTeams == 0, "kWaves waves copy a tile");
+  __shared__ __attribute__((aligned(1024))) char lds[kTiles][C::kTileBytes];
+  __shared__ float red[2][WAVES][32];
 
   const int tid = threadIdx.x, lane = kvc::lane_id(), wave = tid / KVC_WAVE;
-  const int kb = blockIdx.x / p.Hkv, g = blockIdx.x % p.Hkv, b = blockIdx.y;
-  const int bg = b * p.Hkv + g;
+  const int team = wave / kWaves, load_wave = wave % kWaves;
+  const int kb = blockIdx.x, bg = blockIdx.y;  // bg = b * Hkv + kv head
+  const int b = bg / p.Hkv, g = bg % p.Hkv;
   const int S = p.lengths ? min(max(p.lengths[b], 1), p.S) : p.S;
-  const int k0 = kb * (C::kTile * TPW);
+  const int k0 = kb * kKeysPerWg;
   if (k0 >= S) return;  // this sequence is shorter than the launch's upper bound (uniform exit)
   const char* kh = p.k + (size_t)bg * p.capacity * C::kRowBytes;
 
   uint32_t rel[C::kLoadsPerWave];
-  tile_lane_offsets<C>(rel, wave, lane);
+  tile_lane_offsets<C>(rel, load_wave, lane);
+  auto load_keys = [&](int first) {
 #pragma unroll
-  for (int w = 0; w < TPW; ++w) {
-    const int row0 = k0 + C::kTile * w;
-    if (row0 >= S) continue;  // tiles past the end stay unread
-    if (!p.block_table) {
-      tile_load_async<C>(kh, row0, S, lds[w], rel, wave, lane);
-    } else {
-      // paged pool: the same LDS image, every 16-byte chunk fetched from its row's block
+    for (int w0 = 0; w0 < kTiles; w0 += kTeams) {
+      const int w = w0 + team, row0 = first + C::kTile * w;
+      if (row0 >= S) continue;  // tiles past the end stay unread
+      if (!p.block_table) {
+        tile_load_async<C>(kh, row0, S, lds[w], rel, load_wave, lane);
+      } else {
+        // paged pool: the same LDS image, every 16-byte chunk fetched from its row's block
 #pragma unroll
-      for (int j = 0; j < C::kLoadsPerWave; ++j) {
-        int row, chunk;
-        tile_lane_chunk<C>(wave, lane, j, row, chunk);
-        const int in_row = chunk * 16;
-        const char* src = key_row(p, b, g, bg, min(row0 + row, S - 1), C::kRowBytes) + in_row;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                         (__attribute__((address_space(3))) void*)(lds[w] + (wave + kWaves * j) * 1024),
-                                         16, 0, 0);
+        for (int j = 0; j < C::kLoadsPerWave; ++j) {
+          int row, chunk;
+          tile_lane_chunk<C>(load_wave, lane, j, row, chunk);
+          const int in_row = chunk * 16;
+          const char* src = key_row(p, b, g, bg, min(row0 + row, S - 1), C::kRowBytes) + in_row;
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                           (__attribute__((address_space(3))) void*)(lds[w] + (load_wave + kWaves * j) * 1024),
+                                           16, 0, 0);
+        }
       }
     }
-  }
+  };
   const int n = lane & 31;  // result column of this lane = head inside the chunk
   // query vectors of a chunk of up to 32 heads, as the MFMA's column operand (issued before the
   // wait for the tiles, so that the two latencies overlap)
@@ -223,64 +228,70 @@ __global__ __launch_bounds__(kThreads) void append_logits_mfma_kernel(AppendPara
       qf[s] = v;
     }
   };
-  load_q(0);
-  wait_async_loads();
-  __syncthreads();
-
   const int off0 = lds_frag_offset0<C>(lane);
-  const int my_tile = wave % TPW, sub0 = (wave / TPW) * kSubs;  // this wave's rows: tile, first half
-  const int key_base = k0 + C::kTile * my_tile + 32 * sub0 + 4 * (lane >> 5);  // + 32 * sub + 8 * (r / 4) + r % 4
-  for (int h0 = 0; h0 < p.G; h0 += 32) {
-    const int nh = min(32, p.G - h0);
-    const size_t bh = (size_t)b * p.Hq + g * p.G + h0 + min(n, nh - 1);
-    if (h0 > 0) load_q(h0);
-    f32x16 acc[kSubs];
+  const int my_tile = wave / 2, sub = wave % 2;  // this wave's rows: tile, half
+  float2* const pairs = p.part + ((size_t)b * p.Hq + g * p.G) * p.n_kb + kb;  // the group's heads are n_kb apart
+  float2 first_half = make_float2(kNegBig, 0.0f);  // thread i < nh: the first step's pair of head i
+#pragma unroll 1
+  for (int first = k0; first < min(k0 + kKeysPerWg, S); first += kStepKeys) {
+    // (past the previous step's second barrier every wave has its rows in registers)
+    load_keys(first);
+    load_q(0);
+    wait_async_loads();
+    __syncthreads();
+    const int key_base = first + 32 * wave + 4 * (lane >> 5);  // + 8 * (r / 4) + r % 4
+    for (int h0 = 0; h0 < p.G; h0 += 32) {
+      const int nh = min(32, p.G - h0);
+      const size_t bh = (size_t)b * p.Hq + g * p.G + h0 + min(n, nh - 1);
+      if (h0 > 0) load_q(h0);
+      f32x16 acc;
 #pragma unroll
-    for (int sub = 0; sub < kSubs; ++sub) {
+      for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[sub][r] = 0.0f;
-#pragma unroll
-      for (int s = 0; s < C::kSteps; ++s)
-        mma_step<true, F16>(acc[sub], lds_frag<C>(lds[my_tile], off0, sub0 + sub, s), qf[s]);
-    }
-    // this lane: 16 * kSubs keys of head n.  Keys past the end (and whole unread tiles) are masked here.
-    float m = kNegBig;
-#pragma unroll
-    for (int sub = 0; sub < kSubs; ++sub)
+      for (int s = 0; s < C::kSteps; ++s) mma_step<true, F16>(acc, lds_frag<C>(lds[my_tile], off0, sub, s), qf[s]);
+      // this lane: 16 keys of head n.  Keys past the end (and whole unread tiles) are masked here.
+      float m = kNegBig;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int key = key_base + 32 * sub + 8 * (r >> 2) + (r & 3);
-        const float x = key < S ? acc[sub][r] * p.scale_log2 : kNegBig;
-        acc[sub][r] = x;
+        const int key = key_base + 8 * (r >> 2) + (r & 3);
+        const float x = key < S ? acc[r] * p.scale_log2 : kNegBig;
+        acc[r] = x;
         m = fmaxf(m, x);
       }
-    m = fmaxf(m, __shfl_xor(m, 32));
-    if (lane < 32) red[0][wave][n] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(red[0][0][n], red[0][1][n]), fmaxf(red[0][2][n], red[0][3][n]));
-    float l = 0.0f;
+      m = fmaxf(m, __shfl_xor(m, 32));
+      if (lane < 32) red[0][wave][n] = m;
+      __syncthreads();
 #pragma unroll
-    for (int sub = 0; sub < kSubs; ++sub)
+      for (int w = 0; w < WAVES; ++w) m = fmaxf(m, red[0][w][n]);
+      float l = 0.0f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) l += __builtin_amdgcn_exp2f(acc[sub][r] - m);  // masked keys: 2^-huge = 0
-    l += __shfl_xor(l, 32);
-    if (lane < 32) red[1][wave][n] = l;
-    __syncthreads();
-    if (tid < nh) {
-      const float lt = (red[1][0][tid] + red[1][1][tid]) + (red[1][2][tid] + red[1][3][tid]);
-      p.part[((size_t)b * p.Hq + g * p.G + h0 + tid) * p.n_kb + kb] = make_float2(m, lt);
-    }
-    if (n < nh) {
-      float* dst = p.logits + bh * p.S;
-#pragma unroll
-      for (int sub = 0; sub < kSubs; ++sub)
+      for (int r = 0; r < 16; ++r) l += __builtin_amdgcn_exp2f(acc[r] - m);  // masked keys: 2^-huge = 0
+      l += __shfl_xor(l, 32);
+      if (lane < 32) red[1][wave][n] = l;
+      __syncthreads();
+      if (n < nh) {
+        float* dst = p.logits + bh * p.S;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int key = key_base + 32 * sub + 8 * (r >> 2) + (r & 3);
-          if (key < S) dst[key] = acc[sub][r];
+          const int key = key_base + 8 * (r >> 2) + (r & 3);
+          if (key < S) dst[key] = acc[r];
         }
+      }
+      if (tid < nh) {
+        float lt = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) lt += red[1][w][tid];
+        float2* const pair = pairs + (size_t)(h0 + tid) * p.n_kb;
+        if (first > k0) {  // merged with the first step's pair (of the heads beyond 32: this thread's own store)
+          const float2 a = h0 == 0 ? first_half : *pair;
+          const float mt = fmaxf(m, a.x);
+          lt = a.y * __builtin_amdgcn_exp2f(a.x - mt) + lt * __builtin_amdgcn_exp2f(m - mt);
+          m = mt;
+        }
+        if (h0 == 0) first_half = make_float2(m, lt);
+        *pair = make_float2(m, lt);
+      }
     }
-    __syncthreads();  // `red` is rewritten by the next chunk of heads
   }
 }
 
@@ -301,7 +312,7 @@ __global__ __launch_bounds__(kThreads) void append_update_kernel(AppendParams p)
   const int S = p.lengths ? min(max(p.lengths[b], 1), p.S) : p.S;
   const int key0 = blockIdx.x * (kThreads * KPT);
   if (key0 >= S) return;
-  const int n_kb = (S + p.logit_keys - 1) / p.logit_keys;  // blocks that wrote a pair for this sequence
+  const int n_kb = (S + kKeysPerWg - 1) / kKeysPerWg;  // blocks that wrote a pair for this sequence
   const float2* __restrict__ part = p.part;
   const float* __restrict__ logits = p.logits;
   float* __restrict__ dst = p.scores + (size_t)row * p.capacity;
@@ -319,10 +330,19 @@ __global__ __launch_bounds__(kThreads) void append_update_kernel(AppendParams p)
       // row normaliser from the per-workgroup pairs
       const float2* src = part + ((size_t)b * p.Hq + h_first + h0 + i) * p.n_kb;
       float m = kNegBig, l = 0.0f;
-      for (int j = lane; j < n_kb; j += KVC_WAVE) {
-        const float2 ml = src[j];
-        const float mn = fmaxf(m, ml.x);
-        l = l * __builtin_amdgcn_exp2f(m - mn) + ml.y * __builtin_amdgcn_exp2f(ml.x - mn);
+      constexpr int kAhead = 4;  // pairs of a lane in flight together
+      for (int j0 = lane; j0 < n_kb; j0 += kAhead * KVC_WAVE) {
+        float2 ml[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          const int j = j0 + u * KVC_WAVE;
+          ml[u] = src[min(j, n_kb - 1)];
+          if (j >= n_kb) ml[u] = make_float2(kNegBig, 0.0f);
+        }
+        const float mn = fmaxf(fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x)), m);
+        l *= __builtin_amdgcn_exp2f(m - mn);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) l += ml[u].y * __builtin_amdgcn_exp2f(ml[u].x - mn);
         m = mn;
       }
       float mt = m;
@@ -355,14 +375,7 @@ size_t logits_bytes(const kvcrush_shape* s) {
   return kvc::align_up((size_t)s->B * s->Hq * s->S * sizeof(float), 256);
 }
 
-// Keys per workgroup of the logits kernel.  Two 64-row tiles on the matrix-core path: half the LDS, so that
-// four workgroups instead of two share a compute unit and one's loads run under another's sums.  Four tiles ->
-// two, with D = 128: 4 sequences of up to 32768 keys, 218 MB of K in scattered blocks 55.9 -> 47.6 us
-// (4.6 TB/s); 8 sequences of 2048 keys 11.6 -> 9.8 us.
-constexpr int kMfmaTilesPerWg = 2;
-int logit_keys(const kvcrush_shape* s) { return s->dtype != KVCRUSH_F32 ? 64 * kMfmaTilesPerWg : kKeysPerWg; }
-
-int key_blocks(const kvcrush_shape* s) { return (s->S + logit_keys(s) - 1) / logit_keys(s); }
+int key_blocks(const kvcrush_shape* s) { return (s->S + kKeysPerWg - 1) / kKeysPerWg; }
 
 size_t part_bytes(const kvcrush_shape* s) {
   return kvc::align_up((size_t)s->B * s->Hq * key_blocks(s) * sizeof(float2), 256);
@@ -382,17 +395,20 @@ bool append_shape_ok(const kvcrush_shape* s, int capacity) {
 // Keys per thread of the update: four where that still leaves four workgroups to a compute unit.
 constexpr int kUpdateKeys = 4;
 constexpr long long kUpdateWorkgroups = 1024;
+// Workgroups of the matrix-core logits kernel from which on it runs its keys in two steps: four workgroups
+// to each of the 256 compute units.  Whole calls in us, one step -> two, D = 128: 512 workgroups (8 sequences
+// of 2048 keys, 8 KV heads) 13.2 -> 14.0; 1024 (16 of them) 20.6 -> 19.1; 4096 (4 sequences of 32768 keys,
+// 8 KV heads, paged) 79.0 -> 69.8.  (The one-step form with four waves, 64 keys a wave, takes 89.0 there.)
+constexpr long long kTwoStepWorkgroups = 1024;
 
 template <bool BF16, int D, bool F16 = false>
 kvcrush_status launch_append(const AppendParams& p, hipStream_t stream) {
-  // (the heads of a KV cache run side by side: a paged pool holds a token's heads next to each other.
-  // 4 sequences of up to 32768 keys, 8 KV heads, 218 MB of K in 16-token blocks, with 256 keys a
-  // workgroup: 59.2 us head by head, 55.9 so)
-  if ((long long)p.n_kb * p.Hkv > 0x7FFFFFFFll) return KVCRUSH_ERR_UNSUPPORTED;
-  const dim3 grid((unsigned)(p.n_kb * p.Hkv), p.B);
+  const dim3 grid(p.n_kb, p.B * p.Hkv);
   kvcrush_status st;
   if constexpr (BF16) {
-    st = kvc::launch(append_logits_mfma_kernel<D, kMfmaTilesPerWg, F16>, grid, dim3(kThreads), 0, stream, p);
+    st = (long long)p.n_kb * p.B * p.Hkv >= kTwoStepWorkgroups
+             ? kvc::launch(append_logits_mfma_kernel<D, 4, F16>, grid, dim3(4 * KVC_WAVE), 0, stream, p)
+             : kvc::launch(append_logits_mfma_kernel<D, 8, F16>, grid, dim3(8 * KVC_WAVE), 0, stream, p);
   } else {
     st = kvc::launch(append_logits_kernel<BF16, D>, grid, dim3(kThreads), 0, stream, p);
   }
@@ -442,7 +458,6 @@ extern "C" kvcrush_status kvcrush_scores_append(const kvcrush_shape* shape, int3
   p.capacity = capacity;
   p.G = shape->Hq / shape->Hkv;
   p.reduce_groups = shape->reduce_groups;
-  p.logit_keys = logit_keys(shape);
   p.n_kb = key_blocks(shape);
   p.scale_log2 = (float)(1.4426950408889634 *
                          (shape->softmax_scale != 0.0f ? (double)shape->softmax_scale : 1.0 / sqrt((double)shape->D)));

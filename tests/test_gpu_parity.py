@@ -413,6 +413,33 @@ def test_append_update_launch_shapes(kv, oracle, B, Hq, Hkv, S, capacity, rg):
     assert (got[:, :, S:] == 0.0).all()
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype", [
+    (16, 8, 8, 2049, 128, "bf16"),       # 1152 workgroups: two steps of 128 keys; the last block holds one key
+    (32, 160, 4, 2176, 64, "f16"),       # 40 heads a group: two chunks of heads; the last block is one whole step
+    (16, 16, 8, 2177, 64, "bf16"),       # ... and one key more
+    (15, 8, 8, 2049, 128, "bf16"),       # 1080: two steps still
+    (14, 8, 8, 2049, 128, "bf16"),       # 1008: one step
+])
+def test_append_logits_in_two_steps(kv, oracle, B, Hq, Hkv, S, D, dtype):
+    """Both forms of the matrix-core logits kernel.  tests/test_launches.py asserts which sizes take which."""
+    say(f"append logits B={B} Hq={Hq} Hkv={Hkv} S={S} D={D} {dtype}")
+    g = torch.Generator().manual_seed(S + B)
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    q, k = torch.randn(B, Hq, D, generator=g).to(dt), torch.randn(B, Hkv, S, D, generator=g).to(dt)
+    ref = torch.rand(B, Hkv, S, generator=g)
+    got = ref.cuda()
+    oracle.scores_append(q, k, ref, S, True)
+    kv.kvcrush_scores_append(q.cuda(), k.cuda(), got, S, True)
+    torch.cuda.synchronize()
+    # the same probabilities alone: added to scores of zero
+    alone, ref0 = torch.zeros(B, Hkv, S, device="cuda"), torch.zeros(B, Hkv, S)
+    oracle.scores_append(q, k, ref0, S, True)
+    kv.kvcrush_scores_append(q.cuda(), k.cuda(), alone, S, True)
+    torch.cuda.synchronize()
+    say(f"  errors {rel_err(got, ref):.2e} {rel_err(alone, ref0):.2e}")
+    assert rel_err(got, ref) <= 1e-5 and rel_err(alone, ref0) <= 1e-5
+
+
 @pytest.mark.parametrize("rows,S,kernel", [(1, 1, 3), (2, 257, 5), (8, 16384, 7), (64, 2049, 1023), (600, 300, 63), (300, 2050, 9)])
 def test_pool_segments(kv, rows, S, kernel):
     """Segments of 256 to 2048 tokens, whole and ragged: the maximum is exact."""
