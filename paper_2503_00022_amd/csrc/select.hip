@@ -477,12 +477,14 @@ __global__ __launch_bounds__(kSelThreads) void topk_mask_kernel(TopkParams p) {
 struct UnitRowsParams {
   const uint64_t* rowmask_tok;  // [B,Hs+1,nw_tok]; row Hs: important UNITS in its first nw_unit words
   uint64_t* rowmask_unit;       // [B,Hs*unit+1,nw_unit]
+  uint32_t* counters;           // null, or [B,4] arrival counters that medoid_units_emit_kernel finds at zero
   int Hs, unit, n_units, nw_tok, nw_unit;
 };
 
 __global__ __launch_bounds__(256) void unit_rows_kernel(UnitRowsParams p) {
   const int b = blockIdx.y, lane = lane_id();
   const int Hv = p.Hs * p.unit;
+  if (p.counters && blockIdx.x == 0 && threadIdx.x < 4) p.counters[(size_t)b * 4 + threadIdx.x] = 0;
   const uint64_t* __restrict__ src = p.rowmask_tok + (size_t)b * (p.Hs + 1) * p.nw_tok;
   uint64_t* __restrict__ dst = p.rowmask_unit + (size_t)b * (Hv + 1) * p.nw_unit;
   // one wave per output word
@@ -936,11 +938,11 @@ __global__ __launch_bounds__(kSelThreads) void emit_kernel(EmitParams p) {
 }
 
 // =========================================== selection with the rows spread over the chip ==
-// The usual case (at most 128 score rows; rows that fit the tables below; units as well, with
-// unit_rows_kernel after F2 and medoid_units_emit_kernel as F3: 2048 pages of 16 tokens, 8 score
-// rows, 72 us through the general kernels and 46 us so).  Every step that needs a view of a whole row or a whole
-// sequence is a serial chain of short phases, so the stage is bound by how many such chains
-// follow each other and by the fixed cost of a launch.  Three launches:
+// The usual case (at most 128 score rows; rows that fit the tables below; units where the rules of
+// select_plan say so, with unit_rows_kernel after F2 and medoid_units_emit_kernel as F3: 2048 pages
+// of 16 tokens, 8 score rows, 72 us through the general kernels and 46 us so).  Every step that needs
+// a view of a whole row or a whole sequence is a serial chain of short phases, so the stage is bound
+// by how many such chains follow each other and by the fixed cost of a launch.  Three launches:
 //
 //   F1 slice_hist_kernel   the data-parallel part, spread over the chip: per (row, slice
 //                          of 2048 tokens) the histogram of the keys' leading 11 bits; the
@@ -1321,7 +1323,8 @@ __global__ __launch_bounds__(kSelThreads) void medoid_emit_kernel(FastParams p) 
 // The same for units, whose buckets are few and whose vectors are long (page level: 16 buckets of 125
 // pages with 128 bits).  One wave per bucket counted and priced 2 x 128 bits of every 64 members one
 // after the other (26.6 us); here `share` waves take `bits_per_wave` bits each (8 to 64, inside one
-// word), their costs meet in LDS, and the list follows in the same launch (with it 10 us).
+// word), their costs meet in LDS, and the list follows in the same launch (with it 10 us).  (The arrival
+// counters are zeroed by unit_rows_kernel.)
 __global__ __launch_bounds__(kSelThreads) void medoid_units_emit_kernel(MedoidParams p, EmitParams e, uint32_t* counters,
                                                                        int bits_per_wave, int share) {
   __shared__ EmitScratch sh;
@@ -1396,8 +1399,8 @@ struct SelectPlan {
   int budget_items, imp_items; // kept / important items
   int cpw, n_wg, n_gw;         // chunks per grouping workgroup, workgroups / global waves per sequence
   bool keys_in_lds;
-  // short path (few score rows, rows that fit the tables)
-  bool fast;
+  // short path (few score rows, rows that fit the tables): F1 and F2 for the rows, F3 for the rest
+  bool fast_rows, fast_buckets;
   int slice, nsl;              // tokens per histogram slice, slices per row
   // workspace offsets
   size_t rowmask_tok, rowmask, repmask, bits, order, dist_rank, counts, keys, imp, phist, counters, total;
@@ -1431,6 +1434,29 @@ bool select_args_supported(const kvcrush_select_args* a) {
   const long long unit = a->unit > 1 ? a->unit : 1;
   if (a->B > 65535) return false;  // sequences are the second grid dimension
   return a->Hs * unit <= kMaxHs;
+}
+
+// Whether F1 and F2 rank the rows of units faster than the general kernel, and by how much.  They cost a
+// launch and a pass over memory more; they spread a row's passes over the chip, save the serial sum of the Hs
+// score rows in the general kernel's importance workgroup (which skips it when no unit is important) and, once
+// there are more rows than compute units, its second round over the rows' keys.  Linear fits, in us, to both
+// paths' times at 5624 problems (1 to 128 score rows, 1 to 64 sequences, 512 to 32768 tokens, units of 2 to 1024):
+// the choice is 3 % slower than the general kernel at 18 of them and 6 % at most, where always taking F1 and F2
+// was 46 % slower at most.  Measured, general / F1 + F2, units of 8, whole calls: 8 score rows, 4096 tokens
+// 38 / 41, 8192 41 / 43, 32768 66 / 59; 128 rows, 32768 tokens 422 / 322.
+double unit_rows_gain_us(const kvcrush_select_args* a, int S_tok) {
+  const double k = S_tok / 1024.0, rows = (a->Hs + 1.0) * a->B / 256;  // rows per compute unit
+  const double summed = a->n_important > 0 ? a->Hs : 0;
+  if (rows <= 1) return -3.2 + k * (0.34 + 0.019 * summed - 0.59 * rows) - 0.13 * a->Hs;
+  return summed > 0 ? -1.6 + k * (-0.40 + 0.022 * summed + 0.65 * rows) - 0.12 * a->Hs : -1;
+}
+
+// Whether medoid_units_emit_kernel serves the buckets: few long vectors, which it spreads over up to sixteen
+// waves.  General kernels / this one, whole calls in us by bits a vector and buckets of all sequences: 32 bits, 16
+// to 1000 buckets 1 to 7 less, 2000 0 more; 128 bits, up to 500 buckets 10 less, 2000 1 less, 8000 14 more; 1024
+// bits, up to 250 buckets 17 less, 1000 1 more.  16 bits and fewer gain nothing, nor does a call without buckets.
+bool unit_buckets_short(const kvcrush_select_args* a, int bits, int buckets) {
+  return bits >= 32 && buckets > 0 && (long long)buckets * a->B < (bits <= 128 ? 2048 : 1024);
 }
 
 // units_fast: whether units may take the short path, which needs more scratch memory than the general one.
@@ -1477,15 +1503,18 @@ SelectPlan select_plan(const kvcrush_select_args* a, bool need_bits_ws, bool uni
   if (!P.keys_in_lds) off += kvc::align_up(B * (a->Hs + 1) * P.S_tok * 4, 256);
   // the short path: per-slice histograms, token or unit importances, arrival counters
   // (whole units per slice; a unit has at most kMaxHs tokens)
-  P.slice = P.unit <= kSliceTokens ? kSliceTokens / P.unit * P.unit : kSliceTokens;
+  static_assert(kMaxHs <= kSliceTokens, "a slice holds a unit");
+  P.slice = kSliceTokens / P.unit * P.unit;
   P.nsl = P.S_tok > 0 ? (P.S_tok + P.slice - 1) / P.slice : 0;
-  P.fast = (P.unit == 1 || units_fast) && a->Hs <= kFastMaxRows && P.S_tok > 0 && P.S_tok <= kFastMaxTokens;
+  const bool fits = (P.unit == 1 || units_fast) && a->Hs <= kFastMaxRows && P.S_tok > 0 && P.S_tok <= kFastMaxTokens;
+  P.fast_rows = fits && (P.unit == 1 || unit_rows_gain_us(a, P.S_tok) > 0);
+  P.fast_buckets = fits && (P.unit == 1 || unit_buckets_short(a, P.Hv, P.budget_items - P.imp_items));
   P.imp = off;
-  if (P.fast) off += kvc::align_up(B * P.n_items * 4, 256);
+  if (fits) off += kvc::align_up(B * P.n_items * 4, 256);
   P.phist = off;
-  if (P.fast) off += kvc::align_up(B * (a->Hs + 1) * P.nsl * kRadixBins * 2, 256);
+  if (fits) off += kvc::align_up(B * (a->Hs + 1) * P.nsl * kRadixBins * 2, 256);
   P.counters = off;
-  if (P.fast) off += kvc::align_up(B * 16, 256);
+  if (fits) off += kvc::align_up(B * 16, 256);
   P.total = off;
   return P;
 }
@@ -1628,13 +1657,14 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
   ep.W = P.W;
   ep.unit = P.unit;
 
-  const bool fast = P.fast && args->budget > 0;
+  const bool fast = P.fast_rows && args->budget > 0, fast_buckets = P.fast_buckets && args->budget > 0;
+  uint32_t* counters = (uint32_t*)(ws + P.counters);
   FastParams f;
   if (fast) {
     f.scores = scores + args->n_sink;
     f.imp = (float*)(ws + P.imp);
     f.phist = (uint16_t*)(ws + P.phist);
-    f.counters = (uint32_t*)(ws + P.counters);
+    f.counters = counters;
     f.rowmask = rowmask_tok;
     f.repmask = repmask;
     f.bits = bits_buf;
@@ -1698,6 +1728,7 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
     UnitRowsParams p;
     p.rowmask_tok = rowmask_tok;
     p.rowmask_unit = rowmask;
+    p.counters = fast_buckets ? counters : nullptr;
     p.Hs = Hs;
     p.unit = P.unit;
     p.n_units = P.n_items;
@@ -1745,18 +1776,18 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
     m.Br = Br;
     kvcrush_status st;
     if (P.W <= 2)
-      st = P.cpw == 4 ? launch_grouping<2, 4>(g, m, P, B, Br, !fast, stream)
-                      : launch_grouping<2, kGsChunksPerWg>(g, m, P, B, Br, !fast, stream);
+      st = P.cpw == 4 ? launch_grouping<2, 4>(g, m, P, B, Br, !fast_buckets, stream)
+                      : launch_grouping<2, kGsChunksPerWg>(g, m, P, B, Br, !fast_buckets, stream);
     else if (P.W <= 4)
-      st = P.cpw == 4 ? launch_grouping<4, 4>(g, m, P, B, Br, !fast, stream)
-                      : launch_grouping<4, kGsChunksPerWg>(g, m, P, B, Br, !fast, stream);
+      st = P.cpw == 4 ? launch_grouping<4, 4>(g, m, P, B, Br, !fast_buckets, stream)
+                      : launch_grouping<4, kGsChunksPerWg>(g, m, P, B, Br, !fast_buckets, stream);
     else
-      st = P.cpw == 4 ? launch_grouping<kMaxW, 4>(g, m, P, B, Br, !fast, stream)
-                      : launch_grouping<kMaxW, kGsChunksPerWg>(g, m, P, B, Br, !fast, stream);
+      st = P.cpw == 4 ? launch_grouping<kMaxW, 4>(g, m, P, B, Br, !fast_buckets, stream)
+                      : launch_grouping<kMaxW, kGsChunksPerWg>(g, m, P, B, Br, !fast_buckets, stream);
     if (st != KVCRUSH_OK) return st;
   }
   // ---- the ascending index list
-  if (fast && !token_level) {
+  if (fast_buckets && !token_level) {
     // bits a wave takes of a bucket: as few as leave sixteen waves a compute unit, a power of two
     int per = 8, share;
     for (;; per *= 2) {
@@ -1766,9 +1797,9 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
     }
     const int per_wg = kSelWaves / share;  // buckets of a workgroup (share <= 16: Hv is at most 1024)
     return kvc::launch(medoid_units_emit_kernel, dim3(std::max(1, (Br + per_wg - 1) / per_wg), B), dim3(kSelThreads), 0,
-                       stream, m, ep, f.counters, per, share);
+                       stream, m, ep, counters, per, share);
   }
-  if (fast)  // representatives and the list in one launch
+  if (fast_buckets)  // representatives and the list in one launch
     return kvc::launch(medoid_emit_kernel, dim3(std::max(1, (Br + kSelWaves - 1) / kSelWaves), B),
                        dim3(kSelThreads), 0, stream, f);
   if (args->budget > 0) return kvc::launch(emit_kernel, dim3(B), dim3(kSelThreads), 0, stream, ep);

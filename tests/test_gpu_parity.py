@@ -141,14 +141,20 @@ def test_select_units_matches_oracle(kv, oracle, B, Hs, S, unit, budget, n_imp, 
 
 
 @pytest.mark.parametrize("B,Hs,S,unit,budget,n_imp,anchor", [
-    (1, 8, 32768, 16, 1024, 768, "alternating"),    # the longest rows of the short path; eight bits a wave
-    (1, 8, 32784, 16, 1024, 768, "mean"),           # one page more: the general path
-    (2, 3, 30 * 48 + 48, 48, 960, 480, "random"),   # slices of 42 units; 144 bits: 16 a wave, 32 waves' worth cut to 16
-    (1, 128, 2056, 8, 512, 256, "alternating"),     # the most score rows, 1024 bits: 64 a wave
-    (1, 129, 700, 7, 140, 70, "mean"),              # one row more: the general path
-    (4, 8, 16000, 8, 8000, 4000, "random"),         # many small buckets, 64 bits
-    (1, 1, 4096, 1024, 2048, 1024, "random"),       # four units of 1024 tokens, one bucket
-    (1, 2, 600, 2, 600, 600, "random"),             # everything kept, no representatives
+    # (rows / buckets: the kernels that serve them, as tests/test_launches.py asserts for sizes like these)
+    (1, 8, 32768, 16, 1024, 768, "alternating"),    # short / short: the longest rows; eight bits a wave
+    (1, 8, 32784, 16, 1024, 768, "mean"),           # one page more: general / general
+    (2, 3, 30 * 48 + 48, 48, 960, 480, "random"),   # general / short; 144 bits: 16 a wave, 32 waves' worth cut to 16
+    (1, 128, 2056, 8, 512, 256, "alternating"),     # general / short: 1024 bits, 64 a wave
+    (1, 129, 700, 7, 140, 70, "mean"),              # more score rows than the short path takes: general / general
+    (4, 8, 16000, 8, 8000, 4000, "random"),         # short / short: 500 small buckets a sequence, 64 bits
+    (1, 1, 4096, 1024, 2048, 1024, "random"),       # general / short: four units of 1024 tokens, one bucket
+    (1, 2, 600, 2, 600, 600, "random"),             # general / general: everything kept, no representatives
+    (1, 128, 16384, 8, 4096, 2048, "mean"),         # short / short: the most score rows
+    (2, 3, 20016, 48, 4800, 2400, "random"),        # short / short: slices of 42 units
+    (1, 2, 32768, 2, 4096, 0, "alternating"),       # short / general: nothing important, 4-bit vectors
+    (8, 64, 4096, 8, 1024, 1024, "random"),         # short / general: more rows than compute units, no buckets
+    (8, 4, 8192, 8, 4096, 2048, "mean"),            # general / general: 2048 buckets in all
 ])
 def test_select_units_on_both_paths(kv, oracle, B, Hs, S, unit, budget, n_imp, anchor):
     """Units on the short path and just beyond it, and with less scratch memory than it asks for

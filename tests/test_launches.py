@@ -41,3 +41,37 @@ def test_append_logits_in_two_steps_from_1024_workgroups_on(record):
         (16, 8, 8, 2049, 128, 1), (32, 160, 4, 2176, 64, 2), (16, 16, 8, 2177, 64, 1), (15, 8, 8, 2049, 128, 1), (14, 8, 8, 2049, 128, 1)]]
     blocks = [ran[0].block for _, ran in record(calls)]
     assert blocks == [256, 256, 256, 256, 512]
+
+
+def kernels(ran):
+    """The names of the launched kernels, without their template arguments."""
+    import re
+    return [re.search(r"(?<=\d)[a-z][a-z_]*_kernel", l.kernel).group(0) for l in ran]
+
+
+@pytest.mark.parametrize("Hs,unit,B,S,budget,n_imp,rows,buckets", [
+    # where the general kernels measured less, in whole or for one of the two steps (us, general / short)
+    (1, 16, 64, 32768, 16384, 8192, "general", "general"),   # 86 / 148: 512 short vectors in each of 64 sequences
+    (8, 2, 16, 8192, 2048, 1536, "general", "general"),      # 16-bit vectors
+    (128, 2, 1, 2048, 512, 512, "general", "general"),       # 48 / 68: no representatives
+    (128, 2, 1, 2048, 256, 0, "general", "short"),           # no importance to add up
+    (8, 16, 1, 2048, 512, 384, "general", "short"),          # few tokens, few long vectors
+    (4, 8, 4, 8192, 4096, 2048, "general", "short"),         # 256 buckets a sequence, 1024 in all
+    (4, 8, 8, 8192, 4096, 2048, "general", "general"),       # 2048 in all
+    # where the short path does
+    (8, 16, 1, 32768, 1024, 768, "short", "short"),          # 72 / 46
+    (128, 8, 1, 32768, 8192, 6144, "short", "short"),        # 422 / 312
+    (1, 8, 1, 32768, 4096, 0, "short", "general"),           # 47 / 39
+    (64, 8, 8, 8192, 2048, 2048, "short", "general"),        # more rows than compute units
+])
+def test_units_take_the_path_that_measured_less(record, Hs, unit, B, S, budget, n_imp, rows, buckets):
+    a = kv.make_select_args(B, Hs, S, budget, n_imp, 0, "mean", 1, unit=unit)
+    need = kv.kvcrush_select_workspace(a)
+    (st, ran), (st2, less), (st3, static) = record([L.select(a, need), L.select(a, need - 1), L.select_static(a)])
+    names = kernels(ran)
+    assert st == kv.OK and ("row_select_kernel" in names) == (rows == "short")
+    assert ("topk_mask_kernel" in names) == (rows == "general")
+    assert ("medoid_units_emit_kernel" in names) == (buckets == "short") and ("emit_kernel" in names) == (buckets == "general")
+    # with a byte less than is asked for: the general kernels, which need less
+    assert st2 == kv.OK and kernels(less)[0] == "topk_mask_kernel" and kernels(less)[-1] == "emit_kernel"
+    assert st3 in (kv.OK, kv.ERR_WORKSPACE)
