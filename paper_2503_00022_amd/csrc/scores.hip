@@ -42,6 +42,7 @@
 // exp / max / sum work on the PREVIOUS block's accumulators (so the matrix core
 // and the VALU run side by side inside one wave).
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "tiles.h"
@@ -912,6 +913,30 @@ ColsumPlan colsum_plan(int S, int tile, int chunk_tiles_wanted, int q_first) {
   return pl;
 }
 
+// ---- launch shapes: estimates that the rules below compare ----
+// The chip as they see it: 256 compute units, two workgroups of a tiled kernel on each.
+constexpr int kUnits = 256, kSlots = 2 * kUnits;
+
+// What a launch walks: its workgroups, the tile steps of the longest one and those of all together.
+struct Walk {
+  double wgs, longest, total;
+  // 0: all workgroups are alike, 1: their steps fall evenly from the longest to nothing
+  double uneven() const { return longest > 0 ? std::min(1.0, std::max(0.0, 2 * (1 - total / wgs / longest))) : 0.0; }
+  double per_unit() const { return std::ceil(wgs / kUnits); }
+};
+
+// How long it runs, in steps of a workgroup that has its compute unit for itself: two that share one take
+// `pair` times as long as one; behind two full rounds of uneven ones `tail` of the longest runs alone.
+double makespan(const Walk& w, double pair, double tail) {
+  if (w.longest <= 0 || w.wgs <= kUnits) return w.longest;
+  if (w.wgs <= kSlots) {  // heavy first: a unit's second workgroup is at most as long as the launch's 257th
+    const double last = std::max(0.0, 2 * w.total / w.wgs - w.longest);
+    return w.longest + (pair - 1) * (w.longest - (w.longest - last) * kUnits / w.wgs);
+  }
+  const double rounds = w.per_unit(), alike = w.longest * (std::floor(rounds / 2) * pair + std::fmod(rounds, 2.0));
+  return (1 - w.uneven()) * alike + w.uneven() * (w.total * pair / kSlots + tail * w.longest);
+}
+
 // Pass-B work pieces run about 72 tile steps each (query tiles x the heads a piece walks): 18
 // tiles of 64 queries when a score row sums a KV group of four query heads, 72 when it is one
 // head.  The count is a multiple of three (the loop's unroll).  Where pieces of that length would
@@ -943,13 +968,16 @@ struct LsePlan {
   int heads_per_wg, n_blocks, n_bh, launched, n_split, split_q0, split_rows;
 };
 
-// One workgroup per compute unit; a second one shares the unit's matrix cores, so that cutting for
-// it pays only while the slices stay long.  Whole calls in us, cut for 512 workgroups -> this rule:
-// S = 2048, 32 heads in 8 groups (256 blocks of up to 31 tiles) 85 -> 76; S = 1500, B = 2, 16 heads,
-// D = 64 (192 blocks) 48 -> 44; window of 64 at S = 16384 (8 blocks of 255 tiles) 52 -> 47; S = 12000,
-// 8 heads in 2 groups (376 blocks of up to 187 tiles) 343, 365 uncut.
-constexpr int kWantedWorkgroups = 256;
-constexpr int kWantedLong = 512, kLongSlice = 64;
+// The slices that are tried: as many as give one workgroup to every compute unit, two, or two and a bit.
+// What is compared is in tile steps: the makespan, what every further workgroup of a unit costs beside its
+// steps (its start; between unlike blocks the diagonal tiles as well) and the launch that merges slices.  The
+// figures are fitted to pass A's times with 1 to 64 slices at 713 shapes (S 300 to 16000, 4 to 256 heads, both
+// D, windows of 32 and 200); the choice is within 5 % of the best of them at two thirds and 22 % at most.
+// Cutting always for two a unit, or always for one while slices are below 64 tiles, were 101 % and 69 % off
+// at most.  In us, one a unit / two a unit: S = 2048, 32 heads in 8 groups (256 blocks of up to 31 tiles) 33 / 40;
+// S = 6000, 8 heads (192 blocks of up to 92) 76 / 63; window of 32 at S = 16000, 12 heads (12 blocks of 248)
+// 28 / 27.
+constexpr double kSlicePair = 1.9, kSliceTail = 0.7, kSliceMore = 0.5, kSliceUneven = 3.6, kSliceMerge = 7.7;
 constexpr int kMinTilesPerSlice = 4;
 constexpr int kMaxSplit = 64;
 static_assert(kMaxSplit <= KVC_WAVE, "lse_combine_kernel gives one lane to each slice");
@@ -967,12 +995,21 @@ LsePlan lse_plan(int B, int Hq, int Hkv, int S, bool bf16, int q_first, bool may
   pl.split_q0 = first_blk * qb;
   pl.split_rows = S - pl.split_q0;
   const long long wgs = (long long)pl.launched * pl.n_bh;
-  if (may_split && bf16 && wgs < kWantedLong) {
-    const int tiles_last = (pl.n_blocks - 1) * qb / 64;  // unmasked key tiles of the last block
-    int n = std::min((int)(kWantedWorkgroups / wgs), tiles_last / kMinTilesPerSlice);
-    n = std::max(n, std::min((int)((kWantedLong + wgs - 1) / wgs), tiles_last / kLongSlice));
-    n = std::min(n, kMaxSplit);
-    pl.n_split = std::max(n, 1);
+  // key tiles of 64 before a block (unmasked), first and last block
+  const int tiles_first = first_blk * (qb / 64), tiles_last = (pl.n_blocks - 1) * (qb / 64);
+  const double sum = (double)wgs * ((double)tiles_first + tiles_last) / 2;
+  if (may_split && bf16 && wgs < kSlots) {
+    double best = HUGE_VAL;
+    for (const long long wanted : {1ll, kUnits / wgs, kSlots / wgs, (kSlots + wgs - 1) / wgs}) {
+      const int n = (int)std::max(1ll, std::min(wanted, (long long)std::min(kMaxSplit, tiles_last / kMinTilesPerSlice)));
+      const Walk w = {(double)wgs * n, (double)tiles_last / n, sum};
+      const double steps = makespan(w, kSlicePair, kSliceTail) + (kSliceMore + kSliceUneven * w.uneven()) * (w.per_unit() - 1) +
+                           (n > 1 ? kSliceMerge : 0);
+      if (steps < best) {
+        best = steps;
+        pl.n_split = n;
+      }
+    }
   }
   return pl;
 }

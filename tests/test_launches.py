@@ -75,3 +75,21 @@ def test_units_take_the_path_that_measured_less(record, Hs, unit, B, S, budget, 
     # with a byte less than is asked for: the general kernels, which need less
     assert st2 == kv.OK and kernels(less)[0] == "topk_mask_kernel" and kernels(less)[-1] == "emit_kernel"
     assert st3 in (kv.OK, kv.ERR_WORKSPACE)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,window,slices", [
+    # pass A in us with that many slices a query block (one slice where it is not the choice)
+    (1, 8, 2, 7000, 64, 0, 3),         # 56 (80): 220 blocks of up to 109 tiles
+    (1, 8, 8, 6000, 128, 0, 3),        # 60 (76)
+    (1, 4, 4, 11000, 128, 0, 3),       # 86 (134)
+    (1, 32, 8, 2048, 128, 0, 1),       # 33 (40 with two): 256 blocks of up to 31 tiles
+    (2, 24, 8, 16000, 128, 32, 10),    # 59 (183; 63 with five): a window, 48 blocks of 248 tiles
+    (1, 12, 4, 16000, 128, 32, 42),    # 28 (182)
+    (1, 32, 8, 16384, 128, 0, 1),      # more blocks than the chip takes at once
+])
+def test_slices_of_the_normaliser_pass(record, B, Hq, Hkv, S, D, window, slices):
+    sh = kv.Shape(B, Hq, Hkv, S, D, 1, 1, window)
+    (st, ran), (st2, bare) = record([L.row_lse(sh), L.row_lse(sh, 0)])
+    assert st == st2 == kv.OK and kernels(bare) == ["lse_kernel"]
+    assert ran[0].grid[0] == slices * bare[0].grid[0]
+    assert kernels(ran) == ["lse_kernel"] + (["lse_combine_kernel"] if slices > 1 else [])
