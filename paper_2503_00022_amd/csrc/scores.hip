@@ -941,22 +941,45 @@ double makespan(const Walk& w, double pair, double tail) {
 // tiles of 64 queries when a score row sums a KV group of four query heads, 72 when it is one
 // head.  The count is a multiple of three (the loop's unroll).  Where pieces of that length would
 // leave compute units without one (medium prompts), they are a 384th of the launch's steps, but
-// not below 12.  Whole calls in us, 72 steps -> this rule, bf16 with D = 128: S = 2048, 32 heads in
-// 8 groups 111 -> 71; S = 6000, 4 heads 112 -> 77; B = 8, S = 1024, 32 heads in 8 groups 119 -> 107.
+// not below 12.  Pass B alone in us, 72 steps -> this rule, bf16 with D = 128: S = 2048, 32 heads in
+// 8 groups 65 -> 41; S = 6000, 4 heads 64 -> 41; B = 8, S = 1024, 32 heads in 8 groups 61 -> 51.
 // A share between half a piece and a whole one gains nothing by the cut and pays for its second
-// prologue: S = 4096, 32 heads in 8 groups 175 uncut, 181 to 199 in pieces of 34 to 54 steps.
+// prologue: S = 4096, 32 heads in 8 groups 175 uncut (both passes), 181 to 199 in pieces of 34 to 54
+// steps.  Nor does a cut pay where the whole pieces are resident together already: 64 score rows of
+// one head, S = 2048, are 512 pieces of up to 32 steps, 58 us, and 896 of up to 24, 65 us.
 constexpr int kPieceSteps = 72, kMinPieceSteps = 12, kPiecesWanted = 384;
+constexpr double kPiecePair = 1.1, kPieceTail = 0.6, kPieceMore = 2.2, kPieceCut = 1.0;  // in steps, fitted to
+// whole and cut times of 1518 shapes (S 300 to 16000, 4 to 256 heads, windows): the cut is nowhere the slower one by 2 %
+
+struct ColsumChoice {
+  ColsumPlan plan;
+  Walk walk;  // steps in tiles of the query axis
+};
+
 // fine: false where the scratch memory at hand only holds the partial sums of whole pieces.
-int chunk_tiles_for(int tile, int heads_per_row, long long rows, int S, int q_first, bool fine) {
+ColsumChoice plan_colsum(int tile, int heads_per_row, long long rows, int S, int q_first, bool fine) {
   const long long n_tiles = (S + tile - 1) / tile, tile0 = q_first / tile, n_kb = (S + kKeysPerWg - 1) / kKeysPerWg;
   // tiles from an observation window's first on that the key blocks see: all for the first `whole`
   // blocks, then from each block's own first tile on
   const long long tpk = kKeysPerWg / tile, whole = std::min(n_kb, tile0 / tpk + 1);
   const long long seen = whole * (n_tiles - tile0) + (n_kb - whole) * n_tiles - tpk * ((whole + n_kb - 1) * (n_kb - whole) / 2);
-  const long long fair = seen * heads_per_row * rows / kPiecesWanted * tile / 64;  // (fp32 tiles hold 32 queries)
-  const int steps64 = !fine || 2 * fair > kPieceSteps ? kPieceSteps : std::max((int)fair, kMinPieceSteps);
-  const int tiles = (steps64 * 64 / tile + heads_per_row - 1) / heads_per_row;
-  return std::max(3, (tiles + 2) / 3 * 3);
+  auto cut_at = [&](int steps64) {  // pieces of that many steps of 64 queries (fp32 tiles hold 32)
+    const int tiles = (steps64 * 64 / tile + heads_per_row - 1) / heads_per_row;
+    ColsumChoice c;
+    c.plan = colsum_plan(S, tile, std::max(3, (tiles + 2) / 3 * 3), q_first);
+    c.walk.wgs = (double)c.plan.pieces * rows;
+    c.walk.longest = (double)std::min<long long>(c.plan.chunk_tiles, n_tiles - tile0) * heads_per_row;
+    c.walk.total = (double)seen * heads_per_row * rows;
+    return c;
+  };
+  const ColsumChoice uncut = cut_at(kPieceSteps);
+  const long long fair = seen * heads_per_row * rows / kPiecesWanted * tile / 64;
+  if (!fine || 2 * fair > kPieceSteps) return uncut;
+  const ColsumChoice cut = cut_at(std::max((int)fair, kMinPieceSteps));
+  auto steps = [](const ColsumChoice& c) {
+    return makespan(c.walk, kPiecePair, kPieceTail) + kPieceMore * (c.walk.per_unit() - 1) + (c.plan.n_chunks > 1 ? kPieceCut : 0);
+  };
+  return tile == 64 && steps(uncut) <= steps(cut) ? uncut : cut;
 }
 
 // Launch shape of pass A.  Query blocks are numbered from the end of the
@@ -1078,8 +1101,7 @@ kvcrush_status launch_scores(const ScoreParams& base, const float* lse_user, flo
   using C = Cfg<BF16, D>;
   ScoreParams p = base;
   const long long rows = (long long)p.B * (p.reduce_groups ? p.Hkv : p.Hq);
-  const ColsumPlan pl =
-      colsum_plan(p.S, C::kTile, chunk_tiles_for(C::kTile, p.reduce_groups ? p.G : 1, rows, p.S, p.q_first, fine), p.q_first);
+  const ColsumPlan pl = plan_colsum(C::kTile, p.reduce_groups ? p.G : 1, rows, p.S, p.q_first, fine).plan;
   if (!lse_only && pl.pieces * rows > kMaxGridX) return KVCRUSH_ERR_UNSUPPORTED;  // before anything is enqueued
   if (short_prompt(p)) return launch_short<BF16, D, F16>(p, lse_user, lse_only, stream);
   if (!lse_user) {
@@ -1115,8 +1137,8 @@ size_t lse_bytes(const kvcrush_shape* s) {
 size_t partial_bytes(const kvcrush_shape* s, bool fine) {
   const int tile = s->dtype != KVCRUSH_F32 ? 64 : 32;
   const size_t rows = (size_t)s->B * (s->reduce_groups ? s->Hkv : s->Hq);
-  const int chunk = chunk_tiles_for(tile, s->reduce_groups ? s->Hq / s->Hkv : 1, (long long)rows, s->S, first_query(s), fine);
-  const ColsumPlan pl = colsum_plan(s->S, tile, chunk, first_query(s));
+  const ColsumPlan pl =
+      plan_colsum(tile, s->reduce_groups ? s->Hq / s->Hkv : 1, (long long)rows, s->S, first_query(s), fine).plan;
   if (pl.n_chunks <= 1) return 0;
   return kvc::align_up(rows * pl.n_kb * pl.n_chunks * kKeysPerWg * sizeof(float), 256);
 }

@@ -93,3 +93,18 @@ def test_slices_of_the_normaliser_pass(record, B, Hq, Hkv, S, D, window, slices)
     assert st == st2 == kv.OK and kernels(bare) == ["lse_kernel"]
     assert ran[0].grid[0] == slices * bare[0].grid[0]
     assert kernels(ran) == ["lse_kernel"] + (["lse_combine_kernel"] if slices > 1 else [])
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,rg,cut", [
+    (2, 32, 32, 2048, 0, False),       # 512 whole pieces of up to 32 steps: 58 us, 65 in pieces of up to 24
+    (1, 32, 8, 2048, 1, True),         # 65 uncut, 41
+    (8, 32, 8, 1024, 1, True),         # 61 uncut, 51
+    (1, 32, 8, 5000, 1, True),         # pieces of 72 steps: more than one a key block
+])
+def test_pieces_of_the_column_sums(record, B, Hq, Hkv, S, rg, cut):
+    sh = kv.Shape(B, Hq, Hkv, S, 128, 1, rg)
+    (st, ran), = record([L.scores(sh)])
+    assert st == kv.OK and ("colsum_reduce_kernel" in kernels(ran)) == cut
+    rows = B * (Hkv if rg else Hq)
+    if not cut:
+        assert [l.grid[0] for l in ran if "colsum_kernel" in l.kernel] == [rows * ((S + 255) // 256)]
