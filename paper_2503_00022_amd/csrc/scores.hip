@@ -989,6 +989,7 @@ ColsumChoice plan_colsum(int tile, int heads_per_row, long long rows, int S, int
 // block are cut into n_split slices, one workgroup each.
 struct LsePlan {
   int heads_per_wg, n_blocks, n_bh, launched, n_split, split_q0, split_rows;
+  Walk walk, masked;  // unmasked tiles (of one slice the longest), diagonal tiles
 };
 
 // The slices that are tried: as many as give one workgroup to every compute unit, two, or two and a bit.
@@ -1018,9 +1019,16 @@ LsePlan lse_plan(int B, int Hq, int Hkv, int S, bool bf16, int q_first, bool may
   pl.split_q0 = first_blk * qb;
   pl.split_rows = S - pl.split_q0;
   const long long wgs = (long long)pl.launched * pl.n_bh;
-  // key tiles of 64 before a block (unmasked), first and last block
+  // key tiles of 64 before a block (unmasked), first and last block (fp32: every tile of 32 is masked)
   const int tiles_first = first_blk * (qb / 64), tiles_last = (pl.n_blocks - 1) * (qb / 64);
   const double sum = (double)wgs * ((double)tiles_first + tiles_last) / 2;
+  if (bf16) {
+    pl.walk = {(double)wgs, (double)tiles_last, sum};
+    pl.masked = {(double)wgs, (double)std::min(qb / 64, (S + 63) / 64), (double)pl.n_bh * ((S + 63) / 64 - tiles_first)};
+  } else {
+    pl.walk = {(double)wgs, (S + 31) / 32.0, 2 * sum + (double)wgs * (qb / 32)};
+    pl.masked = {(double)wgs, 0, 0};
+  }
   if (may_split && bf16 && wgs < kSlots) {
     double best = HUGE_VAL;
     for (const long long wanted : {1ll, kUnits / wgs, kSlots / wgs, (kSlots + wgs - 1) / wgs}) {
@@ -1031,6 +1039,7 @@ LsePlan lse_plan(int B, int Hq, int Hkv, int S, bool bf16, int q_first, bool may
       if (steps < best) {
         best = steps;
         pl.n_split = n;
+        pl.walk = w;
       }
     }
   }
@@ -1061,35 +1070,100 @@ kvcrush_status launch_lse(const ScoreParams& base, float2* split_ml, hipStream_t
   return kvc::launch(lse_combine_kernel, dim3((pl.split_rows + 3) / 4, a.B * a.Hq), dim3(256), 0, stream, a);
 }
 
-// Whether the short kernels serve the call: 32x32 tiles of the causal half, all heads together.
-// Below the line the chip is short of workgroups and the short kernels' finer cut wins (both passes,
-// us, tiled -> short): 1088 tiles (B 1, 8 heads, S 512, fp32) 90 -> 22; 4048 (B 2, 8 heads in 2
-// groups, S 700, bf16) 79 -> 25; 16128 (8 heads in 2 groups, S 2000) 103 -> 47; 16896 (32 heads, a
-// row each, S 1000) 53 -> 52.  Above it the tiled kernels' four times larger tile per wave, half the
-// LDS traffic per product, takes over: 66560 (32 heads, a row each, S 2048) 83 against 123; 135168
-// (B 8, 32 heads, S 1024) 125 against 284.
-constexpr long long kShortTiles = 16384;
-bool short_prompt(const ScoreParams& p) {
-  const long long n = (p.S + 31) / 32;
-  return p.q_first == 0 && (long long)p.B * p.Hq * n * (n + 1) / 2 <= kShortTiles;
+// Which of the two kernels of a pass serves a whole sequence: the one whose estimated time is less.  A short
+// kernel's workgroup takes a whole compute unit (D = 64 with 16-bit operands: half of one) and cuts finer, so it
+// wins while the chip is short of workgroups; the tiled kernels' four times larger tile per wave and two
+// workgroups a unit win where there are many, which may as well be many short prompts as few long ones.  The
+// times are linear in the rounds of workgroups and in the steps a unit walks; `lone` is what a step costs a
+// workgroup alone on its unit, in steps of one in company.  Fitted, in us, to both kernels' times at 439 shapes a
+// row (S 16 to 7000, 4 to 4096 heads): the choice is more than 5 % off the faster at 0 to 20 of them.  Measured,
+// tiled / short: pass A, S = 512, 8 heads, fp32 43 / 10; pass B, B = 2, S = 700, 8 heads in 2 groups 32 / 17; 32
+// heads a row each, B = 32, S = 128 19 / 40 (A) and 29 / 87 (B); 4 heads, fp32, S = 3000 397 / 68 and 122 / 72.
+struct PassCost {
+  double short_fixed, short_wg, short_step, short_lone;
+  double wg, step, masked, second, lone;  // second: the launch that merges slices or adds partial sums
+};
+enum { kWide16, kNarrow16, kWide32, kNarrow32 };  // D = 128 / 64, operands of 16 / 32 bits
+constexpr PassCost kLseCost[] = {{2.6, 1.6, 1.1, 0.6, 6.0, 1.7, 3.0, 10.2, 0.4},
+                                 {1.3, 2.6, 0.6, 1.3, 5.1, 0.6, 0.9, 6.4, 1.0},
+                                 {0.5, 2.8, 2.4, 1.3, 1.7, 5.0, 0.0, 0.0, 1.0},
+                                 {1.3, 1.5, 2.3, 1.3, 1.9, 2.9, 0.0, 0.0, 1.0}};
+constexpr PassCost kColsumCost[] = {{2.0, 5.1, 1.2, 0.8, 9.3, 1.7, 2.4, 0.0, 0.6},
+                                    {0.9, 7.4, 0.8, 0.8, 9.1, 1.2, 1.9, 0.0, 0.6},
+                                    {1.6, 6.9, 2.2, 1.0, 18.1, 7.6, 0.0, 43.1, 0.4},
+                                    {0.6, 7.4, 1.4, 1.3, 7.3, 3.6, 0.0, 0.0, 0.8}};
+
+template <class C>
+constexpr int kShortSlots = kShortWaves<C> * 2 * C::kSubBytes <= 64 * 1024 ? kSlots : kUnits;
+
+double busiest(const Walk& w, double slots, double lone) { return std::max(lone * w.longest, w.total / slots); }
+
+// n 32-row tiles a sequence, `heads` of them walked by each of `rows` workgroups a tile, `waves` at a time.
+double short_us(const PassCost& c, double n, double heads, double rows, int waves, int slots) {
+  const double pairs = heads * n * (n + 1) / 2;
+  const Walk w = {rows * n, std::ceil(n * heads / waves), rows * (pairs + n * (waves - 1) / 2) / waves};
+  return c.short_fixed + c.short_wg * std::max(1.0, w.wgs / slots) + c.short_step * busiest(w, slots, c.short_lone);
+}
+
+double tiled_us(const PassCost& c, const Walk& plain, const Walk& masked, bool second) {
+  return c.wg * std::max(1.0, plain.wgs / kSlots) + c.step * busiest(plain, kSlots, c.lone) +
+         c.masked * busiest(masked, kSlots, c.lone) + (second ? c.second : 0.0);
+}
+
+// 32x32 tiles, all heads together, up to which the estimates were compared with measured times; beyond, the
+// tiled kernels.  (It also keeps the short kernels' grids far below 2^32 threads.)
+constexpr double kShortTiles = 150000;
+bool short_candidate(const ScoreParams& p) {
+  const double n = (p.S + 31) / 32;
+  return p.q_first == 0 && (double)p.B * p.Hq * n * (n + 1) / 2 <= kShortTiles;
+}
+
+// (the same with and without scratch memory, so that a call's kernels do not depend on it)
+template <bool BF16, int D>
+bool short_lse(const ScoreParams& p) {
+  using C = Cfg<BF16, D>;
+  if (!short_candidate(p)) return false;
+  const LsePlan pl = lse_plan(p.B, p.Hq, p.Hkv, p.S, BF16, 0, true);
+  const PassCost& c = kLseCost[BF16 ? (D == 128 ? kWide16 : kNarrow16) : (D == 128 ? kWide32 : kNarrow32)];
+  const double n = (p.S + 31) / 32;
+  return short_us(c, n, 1, (double)p.B * p.Hq, kShortWaves<C>, kShortSlots<C>) < tiled_us(c, pl.walk, pl.masked, pl.n_split > 1);
+}
+
+template <bool BF16, int D>
+bool short_colsum(const ScoreParams& p) {
+  using C = Cfg<BF16, D>;
+  if (!short_candidate(p)) return false;
+  const int heads = p.reduce_groups ? p.G : 1;
+  const long long rows = (long long)p.B * (p.reduce_groups ? p.Hkv : p.Hq);
+  const ColsumChoice ch = plan_colsum(C::kTile, heads, rows, p.S, 0, true);
+  const PassCost& c = kColsumCost[BF16 ? (D == 128 ? kWide16 : kNarrow16) : (D == 128 ? kWide32 : kNarrow32)];
+  const double n = (p.S + 31) / 32, n_tiles = (p.S + C::kTile - 1) / C::kTile, tpk = kKeysPerWg / C::kTile;
+  Walk plain = ch.walk, masked = {plain.wgs, 0, 0};
+  if (BF16) {  // every query tile touches the diagonal of one key block
+    masked.longest = std::min(tpk, n_tiles) * heads;
+    masked.total = n_tiles * heads * rows;
+    plain.longest = std::min(plain.longest, std::max(0.0, n_tiles - tpk) * heads);
+    plain.total -= masked.total;
+  }
+  return short_us(c, n, heads, (double)rows, kShortWaves<C>, kShortSlots<C>) < tiled_us(c, plain, masked, ch.plan.n_chunks > 1);
 }
 
 template <bool BF16, int D, bool F16>
-kvcrush_status launch_short(ScoreParams p, const float* lse_user, bool lse_only, hipStream_t stream) {
+kvcrush_status launch_lse_short(ScoreParams p, hipStream_t stream) {
   constexpr int kShortThreads = kShortWaves<Cfg<BF16, D>> * KVC_WAVE;
   p.n_blocks = (p.S + 31) / 32;
-  p.tile0 = p.q_first / 32;
-  if (!lse_user) {
-    p.n_bh = p.B * p.Hq;
-    const dim3 grid((unsigned)(p.n_blocks * p.n_bh));
-    const kvcrush_status st =
-        p.strided ? kvc::launch(lse_short_kernel<BF16, D, F16, true>, grid, dim3(kShortThreads), 0, stream, p)
-                  : kvc::launch(lse_short_kernel<BF16, D, F16, false>, grid, dim3(kShortThreads), 0, stream, p);
-    if (st != KVCRUSH_OK || lse_only) return st;
-  }
+  p.n_bh = p.B * p.Hq;
+  const dim3 grid((unsigned)(p.n_blocks * p.n_bh));
+  return p.strided ? kvc::launch(lse_short_kernel<BF16, D, F16, true>, grid, dim3(kShortThreads), 0, stream, p)
+                   : kvc::launch(lse_short_kernel<BF16, D, F16, false>, grid, dim3(kShortThreads), 0, stream, p);
+}
+
+template <bool BF16, int D, bool F16>
+kvcrush_status launch_colsum_short(ScoreParams p, const float* lse_in, hipStream_t stream) {
+  constexpr int kShortThreads = kShortWaves<Cfg<BF16, D>> * KVC_WAVE;
+  p.n_blocks = (p.S + 31) / 32;
   p.n_bh = p.B * (p.reduce_groups ? p.Hkv : p.Hq);
   const dim3 grid((unsigned)(p.n_blocks * p.n_bh));
-  const float* lse_in = lse_user ? lse_user : p.lse;
   return p.strided
              ? kvc::launch(colsum_short_kernel<BF16, D, F16, true>, grid, dim3(kShortThreads), 0, stream, p, lse_in)
              : kvc::launch(colsum_short_kernel<BF16, D, F16, false>, grid, dim3(kShortThreads), 0, stream, p, lse_in);
@@ -1103,19 +1177,20 @@ kvcrush_status launch_scores(const ScoreParams& base, const float* lse_user, flo
   const long long rows = (long long)p.B * (p.reduce_groups ? p.Hkv : p.Hq);
   const ColsumPlan pl = plan_colsum(C::kTile, p.reduce_groups ? p.G : 1, rows, p.S, p.q_first, fine).plan;
   if (!lse_only && pl.pieces * rows > kMaxGridX) return KVCRUSH_ERR_UNSUPPORTED;  // before anything is enqueued
-  if (short_prompt(p)) return launch_short<BF16, D, F16>(p, lse_user, lse_only, stream);
   if (!lse_user) {
-    const kvcrush_status st = launch_lse<BF16, D, F16>(p, split_ml, stream);
+    const kvcrush_status st = short_lse<BF16, D>(p) ? launch_lse_short<BF16, D, F16>(p, stream)
+                                                    : launch_lse<BF16, D, F16>(p, split_ml, stream);
     if (st != KVCRUSH_OK) return st;
   }
   if (lse_only) return KVCRUSH_OK;
+  const float* lse_in = lse_user ? lse_user : p.lse;
+  if (short_colsum<BF16, D>(p)) return launch_colsum_short<BF16, D, F16>(p, lse_in, stream);
   p.tile0 = p.q_first / C::kTile;
   p.n_blocks = pl.n_kb;
   p.n_chunks = pl.n_chunks;
   p.chunk_tiles = pl.chunk_tiles;
   p.n_bh = p.B * (p.reduce_groups ? p.Hkv : p.Hq);
   const dim3 grid((unsigned)(pl.pieces * p.n_bh));
-  const float* lse_in = lse_user ? lse_user : p.lse;
   const kvcrush_status st =
       p.strided ? kvc::launch(colsum_kernel<BF16, D, F16, true>, grid, dim3(kThreads), 0, stream, p, lse_in)
                 : kvc::launch(colsum_kernel<BF16, D, F16, false>, grid, dim3(kThreads), 0, stream, p, lse_in);

@@ -77,6 +77,52 @@ def test_units_take_the_path_that_measured_less(record, Hs, unit, B, S, budget, 
     assert st3 in (kv.OK, kv.ERR_WORKSPACE)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype,rg,window,lse,colsum", [
+    # (us, tiled / short, pass A and pass B)
+    (32, 32, 8, 128, 128, 1, 1, 0, "tiled", "tiled"),     # 13 / 41, 25 / 33: many sequences of short prompts
+    (128, 4, 4, 200, 128, 1, 1, 0, "tiled", "tiled"),     # 18 / 38, 23 / 83
+    (8, 32, 32, 256, 64, 2, 0, 0, "tiled", "tiled"),      # 10 / 12, 15 / 31
+    (2, 32, 8, 700, 128, 1, 1, 0, "tiled", "short"),      # 15 / 25, 33 / 22
+    (1, 8, 8, 512, 64, 0, 0, 0, "short", "short"),        # 43 / 10, 50 / 14
+    (2, 8, 2, 700, 128, 1, 1, 0, "short", "short"),       # 15 / 9, 32 / 17
+    (1, 4, 4, 3000, 128, 0, 1, 0, "short", "short"),      # 399 / 69, 123 / 73
+    (1, 4, 4, 4000, 64, 0, 1, 0, "short", "short"),       # 299 / 51, 75 / 61
+    (8, 32, 8, 1024, 128, 1, 1, 0, "tiled", "tiled"),     # 44 / 177, 67 / 115
+    (1, 32, 8, 16384, 128, 1, 1, 0, "tiled", "tiled"),
+    (1, 4, 2, 700, 128, 1, 1, 64, "tiled", "tiled"),      # an observation window
+    (1, 1, 1, 17600, 64, 0, 0, 0, "tiled", "tiled"),      # 151525 tiles: beyond what was measured
+])
+def test_scores_take_the_kernels_that_measured_less(record, B, Hq, Hkv, S, D, dtype, rg, window, lse, colsum):
+    sh = kv.Shape(B, Hq, Hkv, S, D, dtype, rg, window)
+    need = kv.kvcrush_scores_workspace(sh)
+    other = kv.Shape(B, Hq, Hkv, S, D, dtype, 1 - rg, window)
+    calls = [L.scores(sh, ws_bytes=need), L.scores(sh, lse=True, ws_bytes=need), L.row_lse(sh), L.row_lse(other), L.row_lse(sh, 0)]
+    out = record(calls)
+    assert all(st == kv.OK for st, _ in out)
+    both, given, alone, alone2, bare = (kernels(ran) for _, ran in out)
+    assert both[0] == alone[0] == alone2[0] == bare[0] == {"short": "lse_short_kernel", "tiled": "lse_kernel"}[lse]
+    assert given[0] == {"short": "colsum_short_kernel", "tiled": "colsum_kernel"}[colsum] and given[0] in both
+    # the normalisers do not depend on how the score rows are reduced, nor on who asks for them
+    assert out[2][1] == out[3][1] == out[0][1][:len(out[2][1])]
+
+
+def test_no_short_kernel_beyond_the_measured_sizes(record):
+    """Of many sizes up to the largest that a call accepts: the short kernels' grids stay below 2^32 threads
+    (the recorder refuses more, as the runtime does) and no prompt of 150000 tiles or more takes them."""
+    import random
+    rng = random.Random(4)
+    shapes = []
+    for _ in range(400):
+        G, Hkv = rng.choice([1, 2, 3, 4, 8]), rng.choice([1, 2, 8, 32])
+        B = rng.choice([1, 8, 64, 2000])
+        shapes.append(kv.Shape(B, Hkv * G, Hkv, int(2 ** rng.uniform(0, 22)), rng.choice([64, 128]), rng.randint(0, 2), rng.randint(0, 1)))
+    for sh, (st, ran) in zip(shapes, record([L.scores(sh) for sh in shapes])):
+        n = (sh.S + 31) // 32
+        short = any("short" in k for k in kernels(ran))
+        assert not (short and sh.B * sh.Hq * n * (n + 1) // 2 > 150000)
+        assert st == kv.OK or any(l.grid[0] * l.block > 0xFFFFFFFF for l in ran) or not ran
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,window,slices", [
     # pass A in us with that many slices a query block (one slice where it is not the choice)
     (1, 8, 2, 7000, 64, 0, 3),         # 56 (80): 220 blocks of up to 109 tiles
@@ -108,3 +154,18 @@ def test_pieces_of_the_column_sums(record, B, Hq, Hkv, S, rg, cut):
     rows = B * (Hkv if rg else Hq)
     if not cut:
         assert [l.grid[0] for l in ran if "colsum_kernel" in l.kernel] == [rows * ((S + 255) // 256)]
+
+
+def test_the_sizes_of_the_tiled_tests_are_tiled(record):
+    """test_gpu_parity.py's cases for the tiled kernels run those, whatever the rules become."""
+    from test_gpu_parity import EXTREME_TILED, TILED_CASES
+    code = {"f32": kv.F32, "bf16": kv.BF16, "f16": kv.F16}
+    cases = [(c[:7], c[7:]) for c in TILED_CASES]
+    cases += [((1, Hq, Hkv, S, D, dt, rg), None) for Hq, Hkv, S, D, dt in EXTREME_TILED for rg in (0, 1)]
+    cases.append(((1, 8, 2, 7000, 128, "bf16", True), (True, True)))       # test_scores_deterministic
+    out = record([L.scores(kv.Shape(B, Hq, Hkv, S, D, code[dt], int(rg))) for (B, Hq, Hkv, S, D, dt, rg), _ in cases])
+    for (shape, expected), (st, ran) in zip(cases, out):
+        names = kernels(ran)
+        assert st == kv.OK and {"lse_kernel", "colsum_kernel"} <= set(names), shape
+        if expected:
+            assert ("lse_combine_kernel" in names, "colsum_reduce_kernel" in names) == expected, shape

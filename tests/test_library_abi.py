@@ -152,6 +152,23 @@ def test_score_kernels_keep_their_registers():
         assert r["LDS Size"] <= 80 * 1024, (name, r)   # two workgroups share a compute unit's 160 KiB
 
 
+def test_short_prompt_and_decoding_kernels_keep_their_registers():
+    """The same for the short-prompt kernels, whose stationary rows and closing sums are arrays that only
+    stay in registers while every index is known, and for the decoding step's matrix-core kernel."""
+    from paper_2503_00022_amd import build
+    short = {n: r for n, r in build.resource_usage("scores.hip").items() if "_short_kernel" in n}
+    assert len(short) == 24, sorted(short)         # {lse, colsum} x {bf16, fp16, fp32} x {D = 64, 128} x {packed, strided}
+    for name, r in short.items():
+        assert r["VGPRs Spill"] == 0 and r["SGPRs Spill"] == 0 and r["ScratchSize"] == 0, (name, r)
+        assert r["LDS Size"] <= 160 * 1024, (name, r)       # one workgroup of eight (fp32, D = 128: four) waves a compute unit
+        assert r["Occupancy"] >= 1, (name, r)
+    append = {n: r for n, r in build.resource_usage("decode.hip").items() if "append_" in n}
+    assert len([n for n in append if "mfma" in n]) == 8, sorted(append)   # {bf16, fp16} x {D = 64, 128} x {four, eight waves}
+    for name, r in append.items():
+        assert r["VGPRs Spill"] == 0 and r["SGPRs Spill"] == 0 and r["ScratchSize"] == 0, (name, r)
+        assert "mfma" not in name or (r["Occupancy"] >= 4 and r["LDS Size"] <= 80 * 1024), (name, r)
+
+
 def test_struct_layouts_match_the_header(tmp_path):
     """The ctypes mirrors of the header's structs have the C compiler's sizes and
     field offsets (a C program that includes the header prints them)."""
