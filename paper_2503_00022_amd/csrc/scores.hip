@@ -723,8 +723,10 @@ __global__ __launch_bounds__(kKeysPerWg) void colsum_reduce_kernel(ScoreParams p
 // serial chain (pass B at B = 2, S = 700, 8 query heads: 12 workgroups of 44 steps).  Here the
 // unit is one 32x32 tile of one wave: a workgroup of eight waves owns 32 stationary rows, every
 // wave holds them in registers and takes every eighth tile of the other operand through its own
-// two LDS buffers (the next tile lands while this one is worked on; no barrier in the loop).  The waves' partial results meet in LDS once, at the end, in wave
-// order, so neither the slices' merge nor the partial sums' reduction needs a launch of its own.
+// two LDS buffers (the next tile lands while this one is worked on; no barrier in the loop).  The
+// waves' partial results meet in LDS once, at the end, in wave order, so neither the slices' merge
+// nor the partial sums' reduction needs a launch of its own.  (Whole sequences only: an observation
+// window always takes the tiled kernels.)
 template <class C>
 constexpr int kShortWaves = C::kSubBytes > 8192 ? 4 : 8;  // (two tiles per wave in LDS: at most 128 KiB)
 
@@ -835,21 +837,20 @@ __global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void colsum
   f32x16 col;
 #pragma unroll
   for (int r = 0; r < 16; ++r) col[r] = 0.0f;
-  // (head, query tile) pairs, tiles from the diagonal (or the window's first tile) on; wave w takes
-  // pairs w, w + 8, ... in head-major order
-  const int n_tiles = (S + 31) / 32, t_first = max(kb, p.tile0), nt = n_tiles - t_first;
-  const int n_pairs = nt * n_heads;
+  // (head, query tile) pairs, tiles from the diagonal one (kb) on; wave w takes pairs w, w + W, ...
+  // in head-major order
+  const int nt = (S + 31) / 32 - kb, n_pairs = nt * n_heads;
   if (wave < n_pairs) {
     const WaveTile<C> q_tile(lane, qrb);
     const uint32_t dst = tile_wave_dst(&lds[wave][0][0], 0);
     float raw = 0.0f;
-    int t = wave, h = 0;  // tile (counted from t_first) and head of the pair to load next
+    int t = wave, h = 0;  // tile (counted from kb) and head of the pair to load next
     auto fetch = [&](int buf) {
       while (t >= nt) {
         t -= nt;
         ++h;
       }
-      const int head = head0 + h, q0 = (t_first + t) * 32;
+      const int head = head0 + h, q0 = (kb + t) * 32;
       const char* qh = STRIDED ? p.q + b * p.q_sb + head * p.q_sh : p.q + ((size_t)b * p.Hq + head) * S * C::kRowBytes;
       raw = lse_in[((size_t)b * p.Hq + head) * S + min(q0 + (lane & 31), S - 1)];
       q_tile.load(qh, q0, S, dst + buf * C::kSubBytes);
@@ -860,10 +861,9 @@ __global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void colsum
     const int off0 = lds_frag_offset0<C>(lane);
     int cur = 0;
     for (int pair = wave; pair < n_pairs; pair += W, cur ^= 1) {
-      const int tile = t_first + t, qi = tile * 32 + (lane & 31);
+      const int tile = kb + t, qi = tile * 32 + (lane & 31);
       wait_own_tile();
-      // rows past the end and rows before an observation window contribute nothing
-      const float lse2 = (qi < S && qi >= p.q_first) ? raw * kLog2e : INFINITY;
+      const float lse2 = qi < S ? raw * kLog2e : INFINITY;  // rows past the end contribute nothing
       t += W;
       if (pair + W < n_pairs) fetch(cur ^ 1);
       f32x16 acc;
