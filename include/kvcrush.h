@@ -125,8 +125,18 @@ typedef struct {
  *           NULL: computed here (one more pass over Q K^T) and left in the
  *           first B*Hq*S floats of the workspace.
  *   scores  [B, Hs, S] fp32, fully overwritten
- *   workspace  kvcrush_scores_workspace(shape) bytes, always required: the
- *           row log-sum-exps first, then partial column sums of long sequences
+ *   workspace  kvcrush_scores_workspace(shape) bytes: the row log-sum-exps
+ *           first (room for them is required with lse given as well), then
+ *           partial column sums of long sequences, then the slices' sums that
+ *           kvcrush_row_lse describes.  The size does not only grow with S:
+ *           medium prompts are cut into more pieces to fill the chip.  A buffer
+ *           that has no room for those pieces' sums but for those of whole
+ *           pieces (one sized for a longer prompt, say) is accepted, and whole
+ *           pieces are taken; with less, KVCRUSH_ERR_WORKSPACE.  So the order
+ *           in which column sums are added depends on workspace_bytes being
+ *           the returned size or less: scores of the two orders agree to
+ *           rounding (a few units of 2^-24 relative), and calls with the same
+ *           arguments repeat each other bit for bit.
  * Accuracy: exact bf16 / fp16 (or fp32) products, fp32 accumulation; each score is within
  * 2e-3 relative of the exact value.
  */
@@ -211,7 +221,10 @@ typedef struct {
 } kvcrush_select_args;
 
 size_t kvcrush_select_workspace(const kvcrush_select_args* args);
-/*   scores  [B, Hs, S] fp32 (rows score_stride floats apart when that is set)
+/*   workspace  kvcrush_select_workspace(args) bytes.  With unit = P > 1 that counts the
+ *           tables of the faster kernels for units; a smaller buffer that holds what the
+ *           general kernels need is accepted and gives the same result.
+ *   scores  [B, Hs, S] fp32 (rows score_stride floats apart when that is set)
  *   idx     [B, budget] int32, ascending token positions
  *   kind    nullable [B, budget] uint8: 0 kept as important, 1 as representative,
  *           2 protected (n_sink / n_recent)
@@ -232,8 +245,10 @@ kvcrush_status kvcrush_select(const kvcrush_select_args* args, const float* scor
  * The call allocates and frees nothing.  The first call on a device looks up the
  * array's address (do that first call outside a capture).
  *   - KVCRUSH_ERR_WORKSPACE when the problem needs more scratch than the array
- *     holds, i.e. when kvcrush_select_workspace(args) exceeds
- *     KVCRUSH_SELECT_STATIC_MAX_BYTES; nothing is enqueued then.
+ *     holds; nothing is enqueued then.  For tokens (unit 0 or 1) that is when
+ *     kvcrush_select_workspace(args) exceeds KVCRUSH_SELECT_STATIC_MAX_BYTES (less the
+ *     bit words, if the caller takes them).  Units are refused only when the general
+ *     kernels' share exceeds it: a call whose queried size is larger may succeed.
  *   - All calls on one GPU share the array: calls that overlap in time on one GPU
  *     (different streams, different host threads) race.  Calls on one stream, or
  *     otherwise ordered, are safe; nothing needs clearing between them. */

@@ -77,6 +77,18 @@ def test_units_take_the_path_that_measured_less(record, Hs, unit, B, S, budget, 
     assert st3 in (kv.OK, kv.ERR_WORKSPACE)
 
 
+def test_units_on_the_static_scratch_array(record):
+    """kvcrush_select_static takes units whose queried size, which counts the faster kernels' tables, exceeds the
+    array as long as the general kernels fit; tokens of that size are refused."""
+    a = kv.make_select_args(8, 8, 32768, 4096, 3072, 0, "mean", 1, unit=16)
+    tokens = kv.make_select_args(16, 8, 32768, 4096, 3072, 0, "mean", 1)
+    large = kv.make_select_args(32, 8, 32768, 4096, 3072, 0, "mean", 1, unit=16)
+    assert min(kv.kvcrush_select_workspace(x) for x in (a, tokens, large)) > kv.SELECT_STATIC_MAX_BYTES
+    (st, ran), (st2, none), (st3, none3) = record([L.select_static(x) for x in (a, tokens, large)])
+    assert st == kv.OK and kernels(ran)[0] == "topk_mask_kernel"
+    assert st2 == st3 == kv.ERR_WORKSPACE and not none and not none3
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype,rg,window,lse,colsum", [
     # (us, tiled / short, pass A and pass B)
     (32, 32, 8, 128, 128, 1, 1, 0, "tiled", "tiled"),     # 13 / 41, 25 / 33: many sequences of short prompts
@@ -169,3 +181,20 @@ def test_the_sizes_of_the_tiled_tests_are_tiled(record):
         assert st == kv.OK and {"lse_kernel", "colsum_kernel"} <= set(names), shape
         if expected:
             assert ("lse_combine_kernel" in names, "colsum_reduce_kernel" in names) == expected, shape
+
+
+def test_scores_with_less_scratch_than_the_finer_pieces_need(record):
+    """One buffer for prompts of several lengths, sized for the longest: a shorter prompt that asks for more is
+    cut coarser, with the same kernels otherwise; what even that needs is the limit."""
+    for B, Hq, Hkv, S in [(1, 32, 8, 2100), (1, 32, 8, 1500), (2, 8, 8, 3500), (1, 4, 4, 4400)]:
+        sh = kv.Shape(B, Hq, Hkv, S, 128, kv.BF16, 1)
+        need = kv.kvcrush_scores_workspace(sh)
+        (st, fine), (st2, coarse) = record([L.scores(sh, ws_bytes=need), L.scores(sh, ws_bytes=need - 1)])
+        assert st == st2 == kv.OK and len({k for k in kernels(fine) + kernels(coarse) if k.startswith("lse")} & {"lse_kernel", "lse_short_kernel"}) == 1
+        if "colsum_kernel" in kernels(fine):
+            grid = lambda ran: [l.grid[0] for l in ran if "colsum_kernel" in l.kernel][0]
+            assert grid(coarse) < grid(fine)
+        else:
+            assert fine == coarse
+        (st3, none), = record([L.scores(sh, ws_bytes=B * Hq * S * 4 - 1)])
+        assert st3 == kv.ERR_WORKSPACE and not none

@@ -45,6 +45,20 @@ def test_static_scratch_selection_equals_the_workspace_one_twice_in_a_row(kv):
     both_ways(kv, 1, 8, 4096, 1024, 768, "random", seed=3, unit=16)
 
 
+def test_static_scratch_selection_of_units_beyond_the_queried_size(kv):
+    """Units whose queried size counts the faster kernels' tables: the static call takes the general kernels."""
+    print("static-scratch select: units whose queried size exceeds the array", flush=True)
+    B, Hs, S, budget, n_imp = 8, 8, 32768, 4096, 3072
+    args = kv.make_select_args(B, Hs, S, budget, n_imp, 0, "mean", 5, unit=16)
+    assert kv.kvcrush_select_workspace(args) > kv.SELECT_STATIC_MAX_BYTES
+    sc = inputs.make_scores(B, Hs, S, seed=4, ties=True).cuda()
+    ref, _, _ = kv.kvcrush_select(sc, budget, n_imp, 0, "mean", 5, unit=16)
+    idx = torch.full_like(ref, -7)
+    kv.kvcrush_select_static(args, sc, idx)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, ref)
+
+
 def test_static_scratch_selection_rejects_what_does_not_fit(kv):
     print("static-scratch select: a problem beyond the array's size", flush=True)
     B, Hs, S, budget = 16, 8, 32768, 1024
