@@ -9,13 +9,12 @@
 // below the VALU's rate at that pace.
 //
 //   append_logits_mfma_kernel  (bf16 / fp16) workgroup = 256 keys of one KV head
-//                          (dense cache or paged pool), at once or in two steps:
-//                          64-row K tiles go global -> LDS asynchronously, each
-//                          wave multiplies half a tile with the query
-//                          vectors of the KV group's heads (the 32 columns of a 32x32x16
-//                          MFMA; unused columns are zero), so K is read once for
-//                          the whole group and the dot products cost the VALU
-//                          nothing.  Leaves base-2 logits in the workspace and
+//                          (dense cache or paged pool), 32 a wave: they go
+//                          global -> LDS asynchronously and are multiplied with
+//                          the query vectors of the KV group's heads (the 32
+//                          columns of a 32x32x16 MFMA; unused columns are zero),
+//                          so K is read once for the whole group and the dot
+//                          products cost the VALU nothing.  Leaves base-2 logits in the workspace and
 //                          one (max, sum) pair per workgroup and head.
 //   append_logits_kernel   (fp32 inputs) the same on the VALU: a key row is read
 //                          as 16-byte vectors by neighbouring lanes, the queries
@@ -169,54 +168,62 @@ __global__ __launch_bounds__(kThreads) void append_logits_kernel(AppendParams p)
   }
 }
 
-// bf16 / fp16: logits of kKeysPerWg keys x up to 32 heads per pass on the matrix cores, 32 keys a wave.
-// Bound by reading K.  WAVES = 8: all keys at once.  WAVES = 4: two steps of half the keys through half the
-// LDS, for launches of many workgroups: four of them instead of two share a compute unit, so that more keys
-// are on their way while one workgroup multiplies and stores.  Either way one pair per 256 keys.
-template <int D, int WAVES, bool F16>
-__global__ __launch_bounds__(WAVES * KVC_WAVE, 4) void append_logits_mfma_kernel(AppendParams p) {
+// bf16 / fp16: logits of kKeysPerWg keys x up to 32 heads per pass on the matrix cores.
+// Bound by reading K.  Each of the eight waves copies its own 32 keys into LDS, multiplies, reduces and stores
+// them by itself, so that it waits for nobody's loads but its own; the waves meet once per 32 heads, at the
+// end, when their pairs are merged into one per workgroup.  Measured with D = 128, four waves sharing four
+// 64-row tiles -> this: 8 sequences of 2048 keys, 8 KV heads 11.4 -> 9.8 us; 4 sequences of up to 32768 keys,
+// 218 MB of K in scattered 16-token blocks 55.9 -> 48.2 (4.5 TB/s).  The KV heads run along the grid's y
+// dimension: side by side, the last call takes 1 us more and dense fp32 caches up to 17 % more.
+constexpr int kMfmaWaves = kKeysPerWg / 32;
+template <int D, bool F16>
+__global__ __launch_bounds__(kMfmaWaves * KVC_WAVE, 4) void append_logits_mfma_kernel(AppendParams p) {
   using C = Cfg<true, D>;
-  constexpr int kStepKeys = 32 * WAVES, kTiles = kStepKeys / C::kTile, kTeams = WAVES / kWaves;
-  static_assert(kKeysPerWg % kStepKeys == 0 && WAVES % kWaves == 0 && kTiles % kTeams == 0, "kWaves waves copy a tile");
-  __shared__ __attribute__((aligned(1024))) char lds[kTiles][C::kTileBytes];
-  __shared__ float red[2][WAVES][32];
+  constexpr int kLoads = C::kSubBytes / 1024;  // 1 KiB per wave instruction
+  __shared__ __attribute__((aligned(1024))) char lds[kMfmaWaves][C::kSubBytes];
+  __shared__ float2 red[2][kMfmaWaves][32];    // (two chunks of heads in turn)
 
-  const int tid = threadIdx.x, lane = kvc::lane_id(), wave = tid / KVC_WAVE;
-  const int team = wave / kWaves, load_wave = wave % kWaves;
+  const int tid = threadIdx.x, lane = kvc::lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / KVC_WAVE);
   const int kb = blockIdx.x, bg = blockIdx.y;  // bg = b * Hkv + kv head
   const int b = bg / p.Hkv, g = bg % p.Hkv;
   const int S = p.lengths ? min(max(p.lengths[b], 1), p.S) : p.S;
   const int k0 = kb * kKeysPerWg;
   if (k0 >= S) return;  // this sequence is shorter than the launch's upper bound (uniform exit)
-  const char* kh = p.k + (size_t)bg * p.capacity * C::kRowBytes;
+  const int row0 = k0 + 32 * wave;             // this wave's first key
+  const bool live = row0 < S;                  // (rows past the end repeat the last one and are masked below)
 
-  uint32_t rel[C::kLoadsPerWave];
-  tile_lane_offsets<C>(rel, load_wave, lane);
-  auto load_keys = [&](int first) {
+  if (live) {
+    // the 16-byte chunk that this lane copies with instruction j: the image of one 32-row sub-tile (tiles.h)
+    int row[kLoads];
+    uint32_t in_row[kLoads];
 #pragma unroll
-    for (int w0 = 0; w0 < kTiles; w0 += kTeams) {
-      const int w = w0 + team, row0 = first + C::kTile * w;
-      if (row0 >= S) continue;  // tiles past the end stay unread
-      if (!p.block_table) {
-        tile_load_async<C>(kh, row0, S, lds[w], rel, load_wave, lane);
-      } else {
-        // paged pool: the same LDS image, every 16-byte chunk fetched from its row's block
-#pragma unroll
-        for (int j = 0; j < C::kLoadsPerWave; ++j) {
-          int row, chunk;
-          tile_lane_chunk<C>(load_wave, lane, j, row, chunk);
-          const int in_row = chunk * 16;
-          const char* src = key_row(p, b, g, bg, min(row0 + row, S - 1), C::kRowBytes) + in_row;
-          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                           (__attribute__((address_space(3))) void*)(lds[w] + (load_wave + kWaves * j) * 1024),
-                                           16, 0, 0);
-        }
-      }
+    for (int j = 0; j < kLoads; ++j) {
+      const int q = j * 64 + lane, line = q >> 4, logical = line * 16 + ((q & 15) ^ (line & 15));
+      row[j] = min(logical / C::kChunksPerRow, S - 1 - row0);
+      in_row[j] = (uint32_t)(logical % C::kChunksPerRow) * 16;
     }
-  };
+    auto copy = [&](const char* base, size_t off, int j) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + off),
+                                       (__attribute__((address_space(3))) void*)(lds[wave] + j * 1024), 16, 0, 0);
+    };
+    if (p.block_table) {
+      const int* table = p.block_table + (size_t)b * (p.capacity / p.block_size);
+      const char* pool = p.k + (size_t)g * C::kRowBytes;
+      int blk[kLoads];  // (all entries on their way before the first is used)
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) blk[j] = table[(row0 + row[j]) / p.block_size];
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j)
+        copy(pool, ((size_t)blk[j] * p.block_size + (row0 + row[j]) % p.block_size) * p.Hkv * C::kRowBytes + in_row[j], j);
+    } else {
+      const char* rows = p.k + ((size_t)bg * p.capacity + row0) * C::kRowBytes;  // uniform
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) copy(rows, (uint32_t)row[j] * C::kRowBytes + in_row[j], j);
+    }
+  }
   const int n = lane & 31;  // result column of this lane = head inside the chunk
   // query vectors of a chunk of up to 32 heads, as the MFMA's column operand (issued before the
-  // wait for the tiles, so that the two latencies overlap)
+  // wait for the keys, so that the two latencies overlap)
   u32x4 qf[C::kSteps];
   auto load_q = [&](int h0) {
     const int nh = min(32, p.G - h0);
@@ -228,47 +235,33 @@ __global__ __launch_bounds__(WAVES * KVC_WAVE, 4) void append_logits_mfma_kernel
       qf[s] = v;
     }
   };
+  load_q(0);
+  wait_async_loads();  // (a wave reads only what it copied itself)
+
   const int off0 = lds_frag_offset0<C>(lane);
-  const int my_tile = wave / 2, sub = wave % 2;  // this wave's rows: tile, half
-  float2* const pairs = p.part + ((size_t)b * p.Hq + g * p.G) * p.n_kb + kb;  // the group's heads are n_kb apart
-  float2 first_half = make_float2(kNegBig, 0.0f);  // thread i < nh: the first step's pair of head i
-#pragma unroll 1
-  for (int first = k0; first < min(k0 + kKeysPerWg, S); first += kStepKeys) {
-    // (past the previous step's second barrier every wave has its rows in registers)
-    load_keys(first);
-    load_q(0);
-    wait_async_loads();
-    __syncthreads();
-    const int key_base = first + 32 * wave + 4 * (lane >> 5);  // + 8 * (r / 4) + r % 4
-    for (int h0 = 0; h0 < p.G; h0 += 32) {
-      const int nh = min(32, p.G - h0);
-      const size_t bh = (size_t)b * p.Hq + g * p.G + h0 + min(n, nh - 1);
-      if (h0 > 0) load_q(h0);
+  const int key_base = row0 + 4 * (lane >> 5);  // + 8 * (r / 4) + r % 4
+  for (int h0 = 0, turn = 0; h0 < p.G; h0 += 32, turn ^= 1) {
+    const int nh = min(32, p.G - h0);
+    const size_t bh = (size_t)b * p.Hq + g * p.G + h0 + min(n, nh - 1);
+    if (h0 > 0) load_q(h0);
+    float m = kNegBig, l = 0.0f;
+    if (live) {
       f32x16 acc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-      for (int s = 0; s < C::kSteps; ++s) mma_step<true, F16>(acc, lds_frag<C>(lds[my_tile], off0, sub, s), qf[s]);
-      // this lane: 16 keys of head n.  Keys past the end (and whole unread tiles) are masked here.
-      float m = kNegBig;
+      for (int s = 0; s < C::kSteps; ++s) mma_step<true, F16>(acc, lds_frag<C>(lds[wave], off0, 0, s), qf[s]);
+      // this lane: 16 keys of head n, those past the end masked
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int key = key_base + 8 * (r >> 2) + (r & 3);
-        const float x = key < S ? acc[r] * p.scale_log2 : kNegBig;
-        acc[r] = x;
-        m = fmaxf(m, x);
+        acc[r] = key < S ? acc[r] * p.scale_log2 : kNegBig;
+        m = fmaxf(m, acc[r]);
       }
       m = fmaxf(m, __shfl_xor(m, 32));
-      if (lane < 32) red[0][wave][n] = m;
-      __syncthreads();
-#pragma unroll
-      for (int w = 0; w < WAVES; ++w) m = fmaxf(m, red[0][w][n]);
-      float l = 0.0f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) l += __builtin_amdgcn_exp2f(acc[r] - m);  // masked keys: 2^-huge = 0
       l += __shfl_xor(l, 32);
-      if (lane < 32) red[1][wave][n] = l;
-      __syncthreads();
       if (n < nh) {
         float* dst = p.logits + bh * p.S;
 #pragma unroll
@@ -277,20 +270,17 @@ __global__ __launch_bounds__(WAVES * KVC_WAVE, 4) void append_logits_mfma_kernel
           if (key < S) dst[key] = acc[r];
         }
       }
-      if (tid < nh) {
-        float lt = 0.0f;
+    }
+    if (lane < 32) red[turn][wave][n] = make_float2(m, l);
+    __syncthreads();
+    if (tid < nh) {
+      float mt = red[turn][0][tid].x;  // (the first wave always has keys)
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) lt += red[1][w][tid];
-        float2* const pair = pairs + (size_t)(h0 + tid) * p.n_kb;
-        if (first > k0) {  // merged with the first step's pair (of the heads beyond 32: this thread's own store)
-          const float2 a = h0 == 0 ? first_half : *pair;
-          const float mt = fmaxf(m, a.x);
-          lt = a.y * __builtin_amdgcn_exp2f(a.x - mt) + lt * __builtin_amdgcn_exp2f(m - mt);
-          m = mt;
-        }
-        if (h0 == 0) first_half = make_float2(m, lt);
-        *pair = make_float2(m, lt);
-      }
+      for (int w = 1; w < kMfmaWaves; ++w) mt = fmaxf(mt, red[turn][w][tid].x);
+      float lt = 0.0f;
+#pragma unroll
+      for (int w = 0; w < kMfmaWaves; ++w) lt += red[turn][w][tid].y * __builtin_amdgcn_exp2f(red[turn][w][tid].x - mt);
+      p.part[((size_t)b * p.Hq + g * p.G + h0 + tid) * p.n_kb + kb] = make_float2(mt, lt);
     }
   }
 }
@@ -298,8 +288,9 @@ __global__ __launch_bounds__(WAVES * KVC_WAVE, 4) void append_logits_mfma_kernel
 // Bound by the logits and scores it moves, 4 * (G + 2) bytes a key and score row, and by the chain
 // pairs -> normalisers -> probabilities in front of them: a wave merges one head's pairs by itself
 // (no barrier per head), and the logits of KPT keys per thread, 256 apart, are in flight together.
-// Measured: 4 sequences of up to 32768 keys, 32 heads in 8 groups 17.9 -> 9.8 us (27 MB); 8 sequences
-// of 2048 keys 7.2 -> 4.2 us.
+// A lane has four pairs on their way at a time: at 131072 keys and one head a row, the chain of pair loads
+// one by one took 5 us of the call's 26.  Measured: 4 sequences of up to 32768 keys, 32 heads in 8 groups
+// 17.9 -> 9.6 us (27 MB); 8 sequences of 2048 keys 7.2 -> 4.3 us.
 template <int KPT>
 __global__ __launch_bounds__(kThreads) void append_update_kernel(AppendParams p) {
   constexpr int kHeads = 32;  // heads whose normalisers are held at once
@@ -395,20 +386,12 @@ bool append_shape_ok(const kvcrush_shape* s, int capacity) {
 // Keys per thread of the update: four where that still leaves four workgroups to a compute unit.
 constexpr int kUpdateKeys = 4;
 constexpr long long kUpdateWorkgroups = 1024;
-// Workgroups of the matrix-core logits kernel from which on it runs its keys in two steps: four workgroups
-// to each of the 256 compute units.  Whole calls in us, one step -> two, D = 128: 512 workgroups (8 sequences
-// of 2048 keys, 8 KV heads) 13.2 -> 14.0; 1024 (16 of them) 20.6 -> 19.1; 4096 (4 sequences of 32768 keys,
-// 8 KV heads, paged) 79.0 -> 69.8.  (The one-step form with four waves, 64 keys a wave, takes 89.0 there.)
-constexpr long long kTwoStepWorkgroups = 1024;
-
 template <bool BF16, int D, bool F16 = false>
 kvcrush_status launch_append(const AppendParams& p, hipStream_t stream) {
   const dim3 grid(p.n_kb, p.B * p.Hkv);
   kvcrush_status st;
   if constexpr (BF16) {
-    st = (long long)p.n_kb * p.B * p.Hkv >= kTwoStepWorkgroups
-             ? kvc::launch(append_logits_mfma_kernel<D, 4, F16>, grid, dim3(4 * KVC_WAVE), 0, stream, p)
-             : kvc::launch(append_logits_mfma_kernel<D, 8, F16>, grid, dim3(8 * KVC_WAVE), 0, stream, p);
+    st = kvc::launch(append_logits_mfma_kernel<D, F16>, grid, dim3(kMfmaWaves * KVC_WAVE), 0, stream, p);
   } else {
     st = kvc::launch(append_logits_kernel<BF16, D>, grid, dim3(kThreads), 0, stream, p);
   }

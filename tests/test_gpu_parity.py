@@ -489,30 +489,39 @@ def test_append_update_launch_shapes(kv, oracle, B, Hq, Hkv, S, capacity, rg):
     assert (got[:, :, S:] == 0.0).all()
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype", [
-    (16, 8, 8, 2049, 128, "bf16"),       # 1152 workgroups: two steps of 128 keys; the last block holds one key
-    (32, 160, 4, 2176, 64, "f16"),       # 40 heads a group: two chunks of heads; the last block is one whole step
-    (16, 16, 8, 2177, 64, "bf16"),       # ... and one key more
-    (15, 8, 8, 2049, 128, "bf16"),       # 1080: two steps still
-    (14, 8, 8, 2049, 128, "bf16"),       # 1008: one step
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype,paged", [
+    (16, 8, 8, 2049, 128, "bf16", False),   # 1152 workgroups; the last of a head holds one key: seven waves without any
+    (32, 160, 4, 2176, 64, "f16", False),   # 40 heads a group: two chunks of heads; the last holds four whole waves' keys
+    (4, 272, 4, 545, 128, "bf16", True),    # 68 heads a group: three chunks, so that the waves' pairs change places twice
+    (3, 12, 4, 1041, 128, "f16", True),     # paged: blocks of 16, the last wave with one key
+    (14, 8, 8, 31, 64, "bf16", False),      # a wave's keys and one less
+    (2, 4, 4, 33, 128, "bf16", True),       # ... and one more
 ])
-def test_append_logits_in_two_steps(kv, oracle, B, Hq, Hkv, S, D, dtype):
-    """Both forms of the matrix-core logits kernel.  tests/test_launches.py asserts which sizes take which."""
-    say(f"append logits B={B} Hq={Hq} Hkv={Hkv} S={S} D={D} {dtype}")
+def test_append_logits_wave_by_wave(kv, oracle, B, Hq, Hkv, S, D, dtype, paged):
+    """The matrix-core logits kernel at the edges of its waves' 32 keys and of the chunks of 32 heads."""
+    say(f"append logits B={B} Hq={Hq} Hkv={Hkv} S={S} D={D} {dtype} paged={paged}")
     g = torch.Generator().manual_seed(S + B)
     dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
     q, k = torch.randn(B, Hq, D, generator=g).to(dt), torch.randn(B, Hkv, S, D, generator=g).to(dt)
-    ref = torch.rand(B, Hkv, S, generator=g)
+    cap = (S + 15) // 16 * 16                        # whole blocks; the oracle takes the same capacity
+    k = torch.cat([k, torch.zeros(B, Hkv, cap - S, D, dtype=dt)], dim=2)
+    keys, table = k.cuda(), {}
+    if paged:
+        bt = torch.randperm(B * cap // 16, generator=g).to(torch.int32).view(B, cap // 16)
+        keys, table = inputs.to_paged(k, bt, 16).cuda(), dict(block_table=bt.cuda(), block_size=16)
+    ref = torch.rand(B, Hkv, cap, generator=g)
     got = ref.cuda()
     oracle.scores_append(q, k, ref, S, True)
-    kv.kvcrush_scores_append(q.cuda(), k.cuda(), got, S, True)
+    kv.kvcrush_scores_append(q.cuda(), keys, got, S, True, **table)
     torch.cuda.synchronize()
+    assert torch.equal(got[:, :, S:].cpu(), ref[:, :, S:])
     # the same probabilities alone: added to scores of zero
-    alone, ref0 = torch.zeros(B, Hkv, S, device="cuda"), torch.zeros(B, Hkv, S)
+    alone, ref0 = torch.zeros(B, Hkv, cap, device="cuda"), torch.zeros(B, Hkv, cap)
     oracle.scores_append(q, k, ref0, S, True)
-    kv.kvcrush_scores_append(q.cuda(), k.cuda(), alone, S, True)
+    kv.kvcrush_scores_append(q.cuda(), keys, alone, S, True, **table)
     torch.cuda.synchronize()
-    bound = append_bound(q, k)
+    got, ref, alone, ref0 = (x[:, :, :S] for x in (got, ref, alone, ref0))
+    bound = append_bound(q, k[:, :, :S])
     say(f"  off by {rel_err(got, ref):.2e} and {rel_err(alone, ref0):.2e}, bound {bound:.2e}")
     assert rel_err(got, ref) <= bound and rel_err(alone, ref0) <= bound
 

@@ -35,14 +35,6 @@ def test_append_needs_one_pair_per_256_keys(record, B, Hq, Hkv, S, D, dtype):
     assert "append_logits" in ran[0].kernel and "append_update" in ran[1].kernel and len(ran) == 2
 
 
-def test_append_logits_in_two_steps_from_1024_workgroups_on(record):
-    """The sizes of test_gpu_parity.py's test of the same name, on either side of the line."""
-    calls = [L.append(kv.Shape(B, Hq, Hkv, S, D, dt, 1), S) for B, Hq, Hkv, S, D, dt in [
-        (16, 8, 8, 2049, 128, 1), (32, 160, 4, 2176, 64, 2), (16, 16, 8, 2177, 64, 1), (15, 8, 8, 2049, 128, 1), (14, 8, 8, 2049, 128, 1)]]
-    blocks = [ran[0].block for _, ran in record(calls)]
-    assert blocks == [256, 256, 256, 256, 512]
-
-
 def kernels(ran):
     """The names of the launched kernels, without their template arguments."""
     import re
