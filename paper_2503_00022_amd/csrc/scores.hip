@@ -942,11 +942,11 @@ double makespan(const Walk& w, double pair, double tail) {
 // head.  The count is a multiple of three (the loop's unroll).  Where pieces of that length would
 // leave compute units without one (medium prompts), they are a 384th of the launch's steps, but
 // not below 12.  Pass B alone in us, 72 steps -> this rule, bf16 with D = 128: S = 2048, 32 heads in
-// 8 groups 65 -> 41; S = 6000, 4 heads 64 -> 41; B = 8, S = 1024, 32 heads in 8 groups 61 -> 51.
+// 8 groups 84 -> 44; S = 6000, 4 heads 73 -> 38; B = 8, S = 1024, 32 heads in 8 groups 84 -> 71.
 // A share between half a piece and a whole one gains nothing by the cut and pays for its second
 // prologue: S = 4096, 32 heads in 8 groups 175 uncut (both passes), 181 to 199 in pieces of 34 to 54
 // steps.  Nor does a cut pay where the whole pieces are resident together already: 64 score rows of
-// one head, S = 2048, are 512 pieces of up to 32 steps, 58 us, and 896 of up to 24, 65 us.
+// one head, S = 2048, are 512 pieces of up to 32 steps, 57 us, and 896 of up to 24, 66 us.
 constexpr int kPieceSteps = 72, kMinPieceSteps = 12, kPiecesWanted = 384;
 constexpr double kPiecePair = 1.1, kPieceTail = 0.6, kPieceMore = 2.2, kPieceCut = 1.0;  // in steps, fitted to
 // whole and cut times of 1518 shapes (S 300 to 16000, 4 to 256 heads, windows): the cut is nowhere the slower one by 2 %
@@ -999,8 +999,8 @@ struct LsePlan {
 // D, windows of 32 and 200); the choice is within 5 % of the best of them at two thirds and 22 % at most.
 // Cutting always for two a unit, or always for one while slices are below 64 tiles, were 101 % and 69 % off
 // at most.  In us, one a unit / two a unit: S = 2048, 32 heads in 8 groups (256 blocks of up to 31 tiles) 33 / 40;
-// S = 6000, 8 heads (192 blocks of up to 92) 76 / 63; window of 32 at S = 16000, 12 heads (12 blocks of 248)
-// 28 / 27.
+// S = 6000, 8 heads (192 blocks of up to 92) 76 / 63; window of 200 at S = 16000, 24 heads in 8 groups (48
+// blocks of 248, 4 and 8 slices) 66 / 64.
 constexpr double kSlicePair = 1.9, kSliceTail = 0.7, kSliceMore = 0.5, kSliceUneven = 3.6, kSliceMerge = 7.7;
 constexpr int kMinTilesPerSlice = 4;
 constexpr int kMaxSplit = 64;

@@ -1452,9 +1452,10 @@ double unit_rows_gain_us(const kvcrush_select_args* a, int S_tok) {
 }
 
 // Whether medoid_units_emit_kernel serves the buckets: few long vectors, which it spreads over up to sixteen
-// waves.  General kernels / this one, whole calls in us by bits a vector and buckets of all sequences: 32 bits, 16
-// to 1000 buckets 1 to 7 less, 2000 0 more; 128 bits, up to 500 buckets 10 less, 2000 1 less, 8000 14 more; 1024
-// bits, up to 250 buckets 17 less, 1000 1 more.  16 bits and fewer gain nothing, nor does a call without buckets.
+// waves.  What it takes from a whole call or adds to it, medians in us by bits a vector and buckets of all sequences:
+// 32 bits, up to 500 buckets 1 to 2 less, 1000 to 2000 within 1; 128 bits, up to 500 buckets 8 to 10 less, 1000 to
+// 2000 1 less, 4000 to 8000 14 more; 1024 bits, up to 250 buckets 16 to 17 less, 500 to 1000 2 more.  16 bits and
+// fewer gain nothing, nor does a call without buckets.
 bool unit_buckets_short(const kvcrush_select_args* a, int bits, int buckets) {
   return bits >= 32 && buckets > 0 && (long long)buckets * a->B < (bits <= 128 ? 2048 : 1024);
 }

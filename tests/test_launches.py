@@ -133,8 +133,8 @@ def test_no_short_kernel_beyond_the_measured_sizes(record):
     (1, 8, 8, 6000, 128, 0, 3),        # 60 (76)
     (1, 4, 4, 11000, 128, 0, 3),       # 86 (134)
     (1, 32, 8, 2048, 128, 0, 1),       # 33 (40 with two): 256 blocks of up to 31 tiles
-    (2, 24, 8, 16000, 128, 32, 10),    # 59 (183; 63 with five): a window, 48 blocks of 248 tiles
-    (1, 12, 4, 16000, 128, 32, 42),    # 28 (182)
+    (2, 24, 8, 16000, 128, 32, 10),    # 59 (183; 61 with four): a window, 48 blocks of 248 tiles
+    (1, 12, 4, 16000, 128, 32, 42),    # 27 (182)
     (1, 32, 8, 16384, 128, 0, 1),      # more blocks than the chip takes at once
 ])
 def test_slices_of_the_normaliser_pass(record, B, Hq, Hkv, S, D, window, slices):
@@ -146,9 +146,9 @@ def test_slices_of_the_normaliser_pass(record, B, Hq, Hkv, S, D, window, slices)
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,S,rg,cut", [
-    (2, 32, 32, 2048, 0, False),       # 512 whole pieces of up to 32 steps: 58 us, 65 in pieces of up to 24
-    (1, 32, 8, 2048, 1, True),         # 65 uncut, 41
-    (8, 32, 8, 1024, 1, True),         # 61 uncut, 51
+    (2, 32, 32, 2048, 0, False),       # 512 whole pieces of up to 32 steps: 57 us, 66 in pieces of up to 24
+    (1, 32, 8, 2048, 1, True),         # 84 in pieces of 72 steps, 44
+    (8, 32, 8, 1024, 1, True),         # 84, 71
     (1, 32, 8, 5000, 1, True),         # pieces of 72 steps: more than one a key block
 ])
 def test_pieces_of_the_column_sums(record, B, Hq, Hkv, S, rg, cut):
