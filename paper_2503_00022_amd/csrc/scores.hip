@@ -603,7 +603,8 @@ __global__ __launch_bounds__(kThreads, 2) void colsum_kernel(ScoreParams p, cons
       mma_pair<C, BF16, false, F16>(acc0, lds[0], off0, 0, kf[0], kf[1]);
 #pragma unroll
       for (int s = 0; s < C::kSteps / 2; ++s) fr[s] = lds_frag<C>(lds[0], off0, 1, s);
-      // (the last one or two pairs behind the loop, as in pass A)
+      // The last one or two pairs behind the loop, as in pass A.  Against a loop padded to a multiple of three,
+      // D = 64, LSE given: windows of 200 over 16000 keys 56 -> 49 us, but 16 rows of 6000 tokens 71 -> 75.
       auto body = [&](auto P, int it) {
         constexpr int cur = decltype(P)::value, nxt = (cur + 1) % 3, ld = (cur + 2) % 3;
         constexpr int kT = C::kTileBytes, kU = C::kSubBytes;
