@@ -3,7 +3,7 @@
 // bucket (Alg. 2, Sec. 3.2), merged ascending index list.
 //
 // All integer / compare work on at most a few MiB, so the stage is bound by
-// latency, not bandwidth: five short launches on one stream, no host round
+// latency, not bandwidth: one to five short launches on one stream, no host round
 // trip, no floating-point atomics (every tie is broken by token index, so the
 // result is a pure function of the score tensor).
 //
@@ -1105,7 +1105,9 @@ __global__ __launch_bounds__(kSliceThreads) void slice_hist_kernel(FastParams p)
 // every wave keeps its own candidates in its own stretch of LDS (64 * KPT entries, enough
 // for all of its keys).  One compute unit issues every instruction of the row's keys, about
 // 0.1 us per instruction and key at 16 K keys, so the per-key loops are kept short.
-template <int KPT>
+// OWN: no slice histograms; the workgroup counts its keys' leading digits itself (the importance row's adds the
+// score rows up first) and clears the arrival counters.
+template <int KPT, bool OWN = false>
 __global__ __launch_bounds__(kSelThreads) void row_select_kernel(FastParams p) {
   extern __shared__ __align__(16) uint32_t cand[];  // [kSelWaves][64 * KPT] low 21 key bits of each wave's candidates
   __shared__ uint32_t hist[kRadixBins];
@@ -1119,7 +1121,8 @@ __global__ __launch_bounds__(kSelThreads) void row_select_kernel(FastParams p) {
   const int k = row < Hs ? p.kbit : p.n_important;
   uint64_t* __restrict__ mask_out = p.rowmask + ((size_t)b * (Hs + 1) + row) * p.nw;
   const float* __restrict__ src =
-      row < Hs ? p.scores + ((size_t)b * Hs + row) * p.ld : p.imp + (size_t)b * S;
+      row < Hs ? p.scores + ((size_t)b * Hs + row) * p.ld : (OWN ? p.scores + (size_t)b * Hs * p.ld : p.imp + (size_t)b * S);
+  if (OWN && row == 0 && tid < 4) p.counters[(size_t)b * 4 + tid] = 0;  // (for launches behind this one)
 
   if (k == 0 || k == S) {  // nothing or everything: no search needed
     for (int c = tid; c < nw; c += kSelThreads) {
@@ -1140,15 +1143,50 @@ __global__ __launch_bounds__(kSelThreads) void row_select_kernel(FastParams p) {
       const int t = tid + u * kSelThreads;
       v[u] = t < S ? src[t] : 0.0f;
     }
-    // leading digit: the slices' histograms added up.  Thread i owns bins 2047 - 2i and 2046 - 2i,
-    // one 32-bit word of two 16-bit counts per slice.
-    const uint32_t* __restrict__ ph =
-        (const uint32_t*)(p.phist + ((size_t)b * (Hs + 1) + row) * p.nsl * kRadixBins);
+    // leading digit: thread i owns bins 2047 - 2i and 2046 - 2i
     uint32_t c_hi = 0, c_lo = 0;
-    for (int s = 0; s < p.nsl; ++s) {
-      const uint32_t w = ph[(size_t)s * (kRadixBins / 2) + (kRadixBins / 2 - 1 - tid)];
-      c_lo += w & 0xFFFFu;
-      c_hi += w >> 16;
+    if constexpr (OWN) {
+      if (row == Hs) {  // token importance: fp32 sum of the score rows, taken in row order
+        int r = 1;
+        for (; r + 4 <= Hs; r += 4) {  // four rows' loads in flight
+          float x[4][KPT];
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+            for (int u = 0; u < KPT; ++u) {
+              const int t = tid + u * kSelThreads;
+              x[rr][u] = t < S ? src[(size_t)(r + rr) * p.ld + t] : 0.0f;
+            }
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+            for (int u = 0; u < KPT; ++u) v[u] = v[u] + x[rr][u];
+        }
+        for (; r < Hs; ++r)
+#pragma unroll
+          for (int u = 0; u < KPT; ++u) {
+            const int t = tid + u * kSelThreads;
+            v[u] = v[u] + (t < S ? src[(size_t)r * p.ld + t] : 0.0f);
+          }
+      }
+      hist[2 * tid] = 0;
+      hist[2 * tid + 1] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < KPT; ++u) hist_add(hist, float_key(v[u]) >> 21, tid + u * kSelThreads < S);
+      __syncthreads();
+      c_hi = hist[kRadixBins - 1 - 2 * tid];
+      c_lo = hist[kRadixBins - 2 - 2 * tid];
+      __syncthreads();
+    } else {
+      // the slices' histograms added up: one 32-bit word of two 16-bit counts per slice
+      const uint32_t* __restrict__ ph =
+          (const uint32_t*)(p.phist + ((size_t)b * (Hs + 1) + row) * p.nsl * kRadixBins);
+      for (int s = 0; s < p.nsl; ++s) {
+        const uint32_t w = ph[(size_t)s * (kRadixBins / 2) + (kRadixBins / 2 - 1 - tid)];
+        c_lo += w & 0xFFFFu;
+        c_hi += w >> 16;
+      }
     }
     hist[2 * tid] = 0;
     hist[2 * tid + 1] = 0;
@@ -1254,7 +1292,11 @@ __global__ __launch_bounds__(kSelThreads) void row_select_kernel(FastParams p) {
 
   // ---- plain top-n: the only row of the sequence goes straight on to the index list
   if (p.tail == 0) return;
-  if (!arrive_last(&p.counters[(size_t)b * 4 + 0], (uint32_t)p.rows, &sh_last)) return;
+  if (OWN) {  // (its words went through memory: written and acknowledged before the workgroup reads them back)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  } else if (!arrive_last(&p.counters[(size_t)b * 4 + 0], (uint32_t)p.rows, &sh_last)) return;
   emit_sequence<kSelThreads>(p.emit, b, *reinterpret_cast<EmitScratch*>(cand));  // (the candidates are no longer needed)
 }
 
@@ -1386,6 +1428,287 @@ __global__ __launch_bounds__(kSelThreads) void medoid_units_emit_kernel(MedoidPa
   }
   if (!arrive_last(&counters[(size_t)b * 4 + 1], gridDim.x, &sh_last)) return;
   emit_sequence<kSelThreads>(e, b, sh);
+}
+
+// ============================================ short prompts: a sequence in one workgroup ==
+// Up to 4096 selectable tokens with up to 32 score rows the grouping, the representatives and the list of a
+// sequence fit one workgroup's registers and LDS: three launches above, each a latency chain of 2 to 7 us behind
+// a launch boundary, become one (ROWS = false).  Up to 2048 tokens the rows may be ranked there as well
+// (ROWS = true), and nothing goes through memory but the scores and the list.  512 tokens, 8 rows: 21.0 -> 8.2 us.
+//   rows      a wave ranks a row on its own: the row's keys in registers (KPT a lane), the k-th key bit by
+//             bit from counts of the keys above (left as soon as a count is exactly k), no barrier; the
+//             waves take the Hs + 1 rows in turn
+//   grouping  a thread per token: bit word, distance, rank among equal distances by ballot; one table of
+//             (distance, chunk) counts gives the stable order
+//   buckets   a thread per member adds up its own Hamming distances to its bucket (at most 128 members; the
+//             bit counts of medoid_emit_kernel cost a wave a bucket whatever its size), then one LDS
+//             minimum over (cost, token) per bucket
+constexpr int kOneMaxTokens = 2048, kTailMaxTokens = 4096, kTailMaxRows = 32, kTailMaxBucket = 128;
+constexpr int kTokenBits = 12;  // of a (cost, token) pair: costs are at most 32 x 128
+
+struct OneParams {
+  const float* scores;          // first selectable token of row 0 of sequence 0; rows are `ld` floats apart
+  uint64_t* bits;               // null, or the caller's words [B,S_full] (protected tokens get zero words)
+  const uint64_t* anchor_bits;  // [B] explicit anchor or null
+  uint64_t anchor_seed;
+  int32_t* idx;                 // [B,budget_full]
+  uint8_t* kind;                // nullable
+  int Hs, S, ld, kbit, n_important, anchor_mode, dbits;
+  int N, Br, budget, n_sink, n_recent, S_full, budget_full;
+  int rows0;                    // first row that is ranked (Hs: the importance row alone)
+  const uint64_t* rowmask;      // ROWS = false: the rows' bitmaps [B,Hs+1,nw]
+  int nw;
+};
+
+// v_writelane_b32 (clang has no builtin for it): `old` with lane `lane` replaced by the uniform `v`.
+extern "C" __device__ __attribute__((const)) uint32_t write_lane(uint32_t v, uint32_t lane, uint32_t old) __asm(
+    "llvm.amdgcn.writelane.i32");
+
+template <int KPT, bool ROWS>
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))) void select_one_kernel(OneParams p) {
+  constexpr int kTokens = KPT * KVC_WAVE, kTpt = (kTokens + kSelThreads - 1) / kSelThreads;  // tokens a thread groups
+  constexpr int kTable = (kTailMaxRows + 1) * KPT, kPer = (kTable + kSelThreads - 1) / kSelThreads;
+  __shared__ float imp[ROWS ? kTokens : 1];
+  __shared__ uint64_t rm[kTailMaxRows + 1][KPT];  // row bitmaps; row Hs: important tokens
+  __shared__ int table[kTable];                  // grouped tokens per (distance, chunk), then their first ranks
+  __shared__ uint32_t member_bits[kTokens];      // by rank in (distance, token) order
+  __shared__ uint16_t member[kTokens];
+  __shared__ uint32_t best[kTokens];             // per bucket: cost << kTokenBits | token
+  __shared__ uint32_t rep[2 * KPT];
+  __shared__ uint32_t sh_anchor;
+  __shared__ int wave_tot[kSelWaves];
+
+  const int b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / KVC_WAVE);
+  const int S = p.S, Hs = p.Hs;
+  const float* __restrict__ sc = p.scores + (size_t)b * Hs * p.ld;
+
+  for (int i = tid; i < kTable; i += kSelThreads) table[i] = 0;
+  for (int i = tid; i < p.Br; i += kSelThreads) best[i] = ~0u;
+  if (tid < 2 * KPT) rep[tid] = 0;
+  // ---- the rows' k largest
+  if constexpr (ROWS) {
+    // the wave's first row is on its way while the importances are added up
+    int row = p.rows0 + wave;
+    uint32_t key[KPT];
+    auto load_keys = [&](int r) {
+      const float* src = r < Hs ? sc + (size_t)r * p.ld : nullptr;
+      int end = S;  // (opaque: the chunks' offsets and masks are not to be kept in registers from row to row)
+      asm volatile("" : "+s"(end));
+#pragma unroll
+      for (int u = 0; u < KPT; ++u) {
+        const int t = u * KVC_WAVE + lane, tc = min(t, end - 1);
+        const float v = src ? src[tc] : imp[tc];
+        key[u] = float_key(v) & (uint32_t)((t - end) >> 31);  // (zero past the end: no threshold below is zero, and
+                                                            // among equal keys real tokens come first)
+      }
+    };
+    if (row < Hs) load_keys(row);
+    // token importance: fp32 sum of the score rows, taken in row order
+#pragma unroll
+    for (int i = 0; i < kTpt; ++i) {
+      const int t = i * kSelThreads + tid;
+      if (t < S) {
+        float sum = 0.0f;
+        int r = 0;
+        for (; r + 8 <= Hs; r += 8) {  // eight rows' loads in flight
+          float x[8];
+#pragma unroll
+          for (int rr = 0; rr < 8; ++rr) x[rr] = sc[(size_t)(r + rr) * p.ld + t];
+#pragma unroll
+          for (int rr = 0; rr < 8; ++rr) sum = sum + x[rr];
+        }
+        for (; r < Hs; ++r) sum = sum + sc[(size_t)r * p.ld + t];
+        imp[t] = sum;
+      }
+    }
+    __syncthreads();
+
+      for (; row <= Hs; row += kSelWaves) {
+      const int k = row < Hs ? p.kbit : p.n_important;
+      uint32_t word_lo = 0, word_hi = 0;  // lane u ends up with the word of chunk u
+      if (k == 0 || k == S) {
+        const int rem = S - lane * 64;
+        const uint64_t all = rem >= 64 ? ~0ull : ((1ull << max(rem, 0)) - 1ull);
+        if (k == S) {
+          word_lo = (uint32_t)all;
+          word_hi = (uint32_t)(all >> 32);
+        }
+      } else {
+        if (row == Hs || row >= kSelWaves) load_keys(row);
+        uint32_t T = 0;
+        bool exact = false;
+        for (int bit = 31; bit >= 0; --bit) {
+          const uint32_t cand = T | (1u << bit);
+          int n = 0;
+          if constexpr (KPT <= 12) {
+#pragma unroll
+            for (int u = 0; u < KPT; ++u) n += __popcll(__ballot(key[u] >= cand));
+          } else {
+#pragma unroll
+            for (int u = 0; u < KPT; ++u) {
+              n += key[u] >= cand ? 1 : 0;
+              if (u % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+            }
+            n = wave_sum(n);
+          }
+          if (n >= k) T = cand;
+          if (n == k) {
+            exact = true;
+            break;
+          }
+        }
+        int left = 0;  // keys equal to T that are taken, lowest tokens first
+        if (!exact) {
+          int above = 0;
+#pragma unroll
+          for (int u = 0; u < KPT; ++u) above += key[u] > T ? 1 : 0;
+          left = k - wave_sum(above);
+        }
+#pragma unroll
+        for (int u = 0; u < KPT; ++u) {
+          uint64_t w;
+          if (exact) {
+            w = __ballot(key[u] >= T);
+          } else {
+            const bool eq = key[u] == T;
+            const uint64_t m = __ballot(eq);
+            w = __ballot(key[u] > T || (eq && (int)__popcll(m & lanemask_lt()) < left));
+            left = max(0, left - (int)__popcll(m));
+          }
+          word_lo = write_lane((uint32_t)w, u, word_lo);
+          word_hi = write_lane((uint32_t)(w >> 32), u, word_hi);
+          if constexpr (KPT > 12) __builtin_amdgcn_sched_barrier(0);  // (all chunks' ballots at once do not fit the scalar registers)
+        }
+      }
+      if (lane < KPT) rm[row][lane] = (uint64_t)word_hi << 32 | word_lo;
+    }
+  } else {
+    for (int i = tid; i < (Hs + 1) * KPT; i += kSelThreads) {
+      const int r = i / KPT, c = i % KPT;
+      rm[r][c] = c < p.nw ? p.rowmask[((size_t)b * (Hs + 1) + r) * p.nw + c] : 0ull;
+    }
+  }
+  __syncthreads();
+
+  // ---- anchor, bit words, distances, order by (distance, token)
+  if (p.rows0 == 0) {
+    if (wave == 0) {
+      uint32_t a = 0;
+      if (p.anchor_mode == KVCRUSH_ANCHOR_MEAN) {
+        for (int r = 0; r < Hs; ++r) {
+          const int n = wave_sum(lane < KPT ? __popcll(rm[r][min(lane, KPT - 1)] & ~rm[Hs][min(lane, KPT - 1)]) : 0);
+          if (2 * n > p.N) a |= 1u << r;
+        }
+      } else if (p.anchor_mode == KVCRUSH_ANCHOR_RANDOM) {
+        uint64_t st = p.anchor_seed + (uint64_t)b;
+        a = (uint32_t)splitmix64_next(st);
+      } else if (p.anchor_mode == KVCRUSH_ANCHOR_ALTERNATING) {
+        a = 0xAAAAAAAAu;
+      } else if (p.anchor_mode == KVCRUSH_ANCHOR_EXPLICIT) {
+        a = (uint32_t)p.anchor_bits[b];
+      }  // (kAnchorZero: stays zero)
+      if (Hs < 32) a &= (1u << Hs) - 1u;
+      if (lane == 0) sh_anchor = a;
+    }
+    __syncthreads();
+    const uint32_t anchor = sh_anchor;
+    uint32_t bits[kTpt], dist[kTpt], before[kTpt];
+    bool grouped[kTpt];
+#pragma unroll
+    for (int i = 0; i < kTpt; ++i) {
+      const int t = i * kSelThreads + tid, c = i * kSelWaves + wave;  // c: the wave's chunk
+      bits[i] = dist[i] = before[i] = 0;
+      grouped[i] = false;
+      if (c >= KPT) continue;  // uniform over the wave
+      const uint32_t* half = (const uint32_t*)&rm[0][c] + (lane >> 5);
+      for (int r = 0; r < Hs; ++r) bits[i] |= ((half[r * 2 * KPT] >> (lane & 31)) & 1u) << r;
+      dist[i] = (uint32_t)__popc(bits[i] ^ anchor);
+      grouped[i] = t < S && !((half[Hs * 2 * KPT] >> (lane & 31)) & 1u);
+      if (p.bits && t < S) p.bits[(size_t)b * p.S_full + p.n_sink + t] = bits[i];
+      const uint64_t peers = match_peers(dist[i], p.dbits, grouped[i]);
+      before[i] = (uint32_t)__popcll(peers & lanemask_lt());
+      if (grouped[i] && before[i] == 0) table[dist[i] * KPT + c] = __popcll(peers);
+    }
+    if (p.Br > 0) {  // uniform
+      __syncthreads();
+      int own[kPer], local = 0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const int e = tid * kPer + j;
+        own[j] = e < kTable ? table[e] : 0;
+        local += own[j];
+      }
+      int first = block_excl_scan(local, wave_tot);
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const int e = tid * kPer + j;
+        if (e < kTable) table[e] = first;
+        first += own[j];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kTpt; ++i)
+        if (grouped[i]) {
+          const int rank = table[dist[i] * KPT + i * kSelWaves + wave] + (int)before[i];
+          member_bits[rank] = bits[i];
+          member[rank] = (uint16_t)(i * kSelThreads + tid);
+        }
+      __syncthreads();
+      // ---- representatives
+      const uint32_t N = (uint32_t)p.N, Br = (uint32_t)p.Br;
+#pragma unroll
+      for (int i = 0; i < kTpt; ++i) {
+        const uint32_t m = (uint32_t)(i * kSelThreads + tid);
+        if (m < N) {
+          const uint32_t j = ((m + 1) * Br - 1) / N;  // the bucket that holds rank m
+          const uint32_t lo = j * N / Br, hi = (j + 1) * N / Br, mine = member_bits[m];
+          uint32_t cost = 0;
+          uint32_t o = lo;
+          for (; o + 4 <= hi; o += 4) {  // four reads in flight
+            uint32_t x[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = member_bits[o + e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) cost += (uint32_t)__popc(x[e] ^ mine);
+          }
+          for (; o < hi; ++o) cost += (uint32_t)__popc(member_bits[o] ^ mine);
+          atomicMin(&best[j], cost << kTokenBits | member[m]);
+        }
+      }
+      __syncthreads();
+      for (uint32_t j = tid; j < Br; j += kSelThreads) {
+        const uint32_t t = min(best[j] & ((1u << kTokenBits) - 1u), kTokens - 1u);
+        atomicOr(&rep[t >> 5], 1u << (t & 31));
+      }
+      __syncthreads();
+    }
+  }
+
+  // ---- the ascending list
+  int32_t* idx_out = p.idx + (size_t)b * p.budget_full;
+  uint8_t* kind_out = p.kind ? p.kind + (size_t)b * p.budget_full : nullptr;
+  for (int i = tid; i < p.n_sink + p.n_recent; i += kSelThreads) {
+    const bool head = i < p.n_sink;
+    const int o = head ? i : p.budget_full - p.n_recent + (i - p.n_sink);
+    const int t = head ? i : p.S_full - p.n_recent + (i - p.n_sink);
+    idx_out[o] = t;
+    if (kind_out) kind_out[o] = 2;
+    if (p.bits) p.bits[(size_t)b * p.S_full + t] = 0ull;
+  }
+  const uint64_t rep_c = lane < KPT ? ((uint64_t)rep[2 * (min(lane, KPT - 1)) + 1] << 32 | rep[2 * (min(lane, KPT - 1))]) : 0ull;
+  const int kept_c = lane < KPT ? __popcll(rm[Hs][min(lane, KPT - 1)] | rep_c) : 0;
+  const int first_c = wave_incl_scan(kept_c) - kept_c;  // lane u: kept tokens before chunk u
+#pragma unroll
+  for (int i = 0; i < kTpt; ++i) {
+    const int c = i * kSelWaves + wave;
+    if (c >= KPT) break;
+    const uint64_t reps = (uint64_t)rep[2 * c + 1] << 32 | rep[2 * c], kept = rm[Hs][c] | reps;
+    const int o = __builtin_amdgcn_readlane(first_c, c) + __popcll(kept & lanemask_lt());
+    if (((kept >> lane) & 1ull) && o < p.budget) {
+      idx_out[p.n_sink + o] = c * KVC_WAVE + lane + p.n_sink;
+      if (kind_out) kind_out[p.n_sink + o] = (uint8_t)((reps >> lane) & 1ull);
+    }
+  }
 }
 
 // ------------------------------------------------------------- host side ---
@@ -1520,6 +1843,32 @@ SelectPlan select_plan(const kvcrush_select_args* a, bool need_bits_ws, bool uni
   return P;
 }
 
+// How a token-level call runs.  Measured as whole calls, in us, by score rows and tokens (one sequence, a quarter
+// of the tokens kept): the five launches of the general path / rows and tail apart / all in one launch
+//   8 rows, 512 tokens 21.0 / 10.1 / 8.2; 700 21.5 / 10.1 / 9.8; 1024 22.0 / 11.0 / 11.8; 2048 23.4 / 12.8 / 20.2
+//   32 rows, 512 tokens 28.1 / 11.9 / 13.7; 1024 29.0 / 13.4 / 24.8; 4096 32.8 / 24.2 / -
+//   256 sequences, 8 rows, 512 tokens 61.6 / 28.9 / 9.4; 2048 99.6 / 36.6 / 24.0; 4096 151 / 45.8 / -
+// One launch ranks sixteen rows at a time in one compute unit; apart, every row has a compute unit for itself as
+// long as there are enough, and each further round of 256 rows costs about 2.5 us.  Beyond 4096 tokens the tail
+// has more to do than one compute unit does in the time of the general path's launches.
+// Rows that make their own histogram (kOwnRows: slice_hist_kernel's launch saved, the grouping as in the general
+// path) gain 4 us with few score rows and lose once the importance row's one workgroup has to add up many: 8192
+// tokens, 8 rows 26.6 -> 24.4, 16 rows 29.7 -> 28.7, 32 rows 35.7 -> 37.4; 16384 tokens, 8 rows 30.6 -> 32.6.
+enum SelectRoute { kGeneral, kOwnRows, kTwoLaunches, kOneLaunch };
+// A plain top-n ranks the importance row alone, which a workgroup does faster than a wave beyond some hundred tokens.
+SelectRoute select_route(const kvcrush_select_args* a, const SelectPlan& P, bool plain_topk) {
+  if (P.unit > 1 || a->budget == 0 || P.S_tok == 0 || a->Hs > kFastMaxRows) return kGeneral;
+  const int N = P.n_items - P.imp_items, Br = P.budget_items - P.imp_items;
+  const double rounds = (a->Hs + 1.0) * a->B / 256;  // of rows, one on each compute unit
+  if (P.S_tok <= kTailMaxTokens && a->Hs <= kTailMaxRows && (Br == 0 || (N + Br - 1) / Br <= kTailMaxBucket)) {
+    if (plain_topk) return P.S_tok <= 768 ? kOneLaunch : kTwoLaunches;
+    const double loss = P.S_tok <= 512 ? 0.15 * a->Hs - 3 : P.S_tok <= 768 ? 0.17 * a->Hs - 1
+                        : P.S_tok <= 1024 ? 0.38 * a->Hs - 1 : 0.7 * a->Hs + 2.5;  // of one launch, in us
+    return P.S_tok <= kOneMaxTokens && loss <= 2.5 * std::max(0.0, rounds - 1) ? kOneLaunch : kTwoLaunches;
+  }
+  return P.S_tok <= 8 * kSelThreads && (long long)a->Hs * P.S_tok <= 128 * 1024 ? kOwnRows : kGeneral;
+}
+
 // LDS tables of the grouping: (bits + 1) x chunk words of a workgroup, and the scatter's
 // (bits + 1) x global waves counters (the limit stated in the header).
 bool plan_fits_lds(const SelectPlan& P) {
@@ -1609,6 +1958,23 @@ extern "C" kvcrush_status kvcrush_select_static(const kvcrush_select_args* args,
 }
 
 namespace {
+// Rows whose workgroup makes its own histogram; LDS for every key as a candidate, and for the list of a plain top-n.
+template <int KPT>
+kvcrush_status launch_own_rows(const FastParams& f, int B, hipStream_t stream) {
+  const size_t lds = std::max<size_t>(KPT * kSelThreads * 4, f.tail ? sizeof(EmitScratch) : 0);
+  return kvc::launch(row_select_kernel<KPT, true>, dim3(f.rows, B), dim3(kSelThreads), lds, stream, f);
+}
+kvcrush_status launch_own_rows(const FastParams& f, int S_tok, int B, hipStream_t stream) {
+  if (S_tok <= 2 * kSelThreads) return launch_own_rows<2>(f, B, stream);
+  if (S_tok <= 4 * kSelThreads) return launch_own_rows<4>(f, B, stream);
+  return launch_own_rows<8>(f, B, stream);
+}
+
+template <int KPT, bool ROWS>
+kvcrush_status launch_one(const OneParams& o, int B, hipStream_t stream) {
+  return kvc::launch(select_one_kernel<KPT, ROWS>, dim3(B), dim3(kSelThreads), 0, stream, o);
+}
+
 kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, int32_t* idx,
                           uint8_t* kind, uint64_t* bits, void* workspace, size_t workspace_bytes,
                           void* hip_stream) {
@@ -1658,6 +2024,7 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
   ep.W = P.W;
   ep.unit = P.unit;
 
+  const SelectRoute route = select_route(args, P, plain_topk);
   const bool fast = P.fast_rows && args->budget > 0, fast_buckets = P.fast_buckets && args->budget > 0;
   uint32_t* counters = (uint32_t*)(ws + P.counters);
   FastParams f;
@@ -1689,6 +2056,42 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
     f.tail = plain_topk ? 1 : 0;
     f.emit = ep;
   }
+  if (route == kOneLaunch || route == kTwoLaunches) {
+    OneParams o;
+    o.scores = scores + args->n_sink;
+    o.bits = bits;
+    o.anchor_bits = args->anchor_bits;
+    o.anchor_seed = args->anchor_seed;
+    o.idx = idx;
+    o.kind = kind;
+    o.Hs = Hs;
+    o.S = P.S_tok;
+    o.ld = args->score_stride ? args->score_stride : S_full;
+    o.kbit = kbit;
+    o.n_important = P.imp_items;
+    o.anchor_mode = args->anchor == KVCRUSH_ANCHOR_MEAN && 2ll * kbit <= (long long)N ? kAnchorZero : args->anchor;
+    o.dbits = 32 - __builtin_clz((unsigned)Hs);  // distances range over 0..Hs
+    o.N = N;
+    o.Br = Br;
+    o.budget = P.budget_items;
+    o.n_sink = args->n_sink;
+    o.n_recent = args->n_recent;
+    o.S_full = S_full;
+    o.budget_full = args->budget;
+    o.rows0 = plain_topk ? Hs : 0;
+    o.rowmask = rowmask_tok;
+    o.nw = P.nw_tok;
+    if (route == kOneLaunch)
+      return P.S_tok <= 8 * KVC_WAVE    ? launch_one<8, true>(o, B, stream)
+             : P.S_tok <= 12 * KVC_WAVE ? launch_one<12, true>(o, B, stream)
+             : P.S_tok <= 16 * KVC_WAVE ? launch_one<16, true>(o, B, stream)
+                                        : launch_one<32, true>(o, B, stream);
+    const kvcrush_status st = launch_own_rows(f, P.S_tok, B, stream);
+    if (st != KVCRUSH_OK || plain_topk) return st;
+    return P.S_tok <= 16 * KVC_WAVE   ? launch_one<16, false>(o, B, stream)
+           : P.S_tok <= 32 * KVC_WAVE ? launch_one<32, false>(o, B, stream)
+                                      : launch_one<64, false>(o, B, stream);
+  }
   // large tables in LDS have to be allowed per kernel before the first launch of the call
   const bool kpt16 = P.S_tok <= 16 * kSelThreads;
   const size_t row_lds = (size_t)kSelThreads * (kpt16 ? 16 : 32) * 4;  // every key may be a candidate
@@ -1700,7 +2103,10 @@ kvcrush_status select_run(const kvcrush_select_args* args, const float* scores, 
     return KVCRUSH_ERR_HIP;
 
   // ---- per-row top-k -> row bitmaps
-  if (fast) {
+  if (route == kOwnRows) {
+    const kvcrush_status st = launch_own_rows(f, P.S_tok, B, stream);
+    if (st != KVCRUSH_OK || plain_topk) return st;
+  } else if (fast) {
     kvcrush_status st = token_level ? kvc::launch(slice_hist_kernel<false>, dim3(P.nsl, f.rows, B), dim3(kSliceThreads), 0, stream, f)
                                     : kvc::launch(slice_hist_kernel<true>, dim3(P.nsl, f.rows, B), dim3(kSliceThreads), 0, stream, f);
     if (st != KVCRUSH_OK) return st;

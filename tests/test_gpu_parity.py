@@ -1448,6 +1448,35 @@ def test_gathers_clamp_indices_outside_the_sequence(kv, oracle):
     assert torch.equal(outs[2].cpu()[:, :, :6], torch.gather(sc, 2, good.long()[:, None, :].expand(B, Hkv, 6)))
 
 
+@pytest.mark.parametrize("B,Hs,S,budget,n_imp,kbit,sink,recent,anchor", [
+    # one launch: 8, 12, 16 and 32 chunks of 64 tokens to the last token, and one token more
+    (1, 1, 1, 1, 0, 0, 0, 0, "alternating"), (1, 3, 64, 20, 10, 0, 0, 0, "mean"), (2, 12, 511, 129, 60, 0, 0, 0, "random"),
+    (1, 8, 512, 128, 64, 400, 0, 0, "mean"), (3, 2, 517, 160, 120, 0, 4, 0, "alternating"), (1, 4, 768, 700, 3, 0, 0, 0, "mean"),
+    (1, 2, 769, 96, 90, 0, 0, 0, "random"), (65, 16, 1024, 300, 200, 0, 0, 0, "mean"), (65, 32, 1025, 300, 150, 0, 0, 0, "mean"),
+    (300, 3, 2048, 512, 300, 0, 0, 0, "mean"),
+    # rows and tail apart: the same edges, 32 rows, two launches of the largest kind
+    (1, 32, 512, 128, 64, 0, 0, 0, "mean"), (1, 31, 1023, 500, 17, 0, 0, 0, "random"), (2, 8, 2048, 512, 300, 1500, 0, 0, "mean"),
+    (1, 8, 2049, 512, 300, 0, 0, 0, "alternating"), (1, 32, 4096, 1024, 512, 3000, 0, 0, "mean"), (2, 5, 4101, 900, 700, 0, 2, 3, "mean"),
+    # buckets of 128 and 129 members, one row more than the tail takes, a token more
+    (1, 4, 1290, 20, 10, 0, 0, 0, "mean"), (1, 4, 1300, 20, 10, 0, 0, 0, "mean"), (1, 33, 700, 200, 100, 0, 0, 0, "mean"),
+    (2, 8, 4097, 1024, 512, 0, 0, 0, "mean"), (1, 16, 8192, 2048, 1500, 0, 0, 0, "mean"), (1, 17, 8192, 2048, 1500, 0, 0, 0, "mean"),
+    (1, 8, 8193, 2048, 1500, 0, 0, 0, "mean"),
+])
+def test_select_at_the_edges_of_its_routes(kv, oracle, B, Hs, S, budget, n_imp, kbit, sink, recent, anchor):
+    """The selection in one, two, four and five launches at the sizes where they meet (tests/test_launches.py
+    asserts which), on scores with ties at every threshold, all alike, negative and infinite."""
+    say(f"select routes B={B} Hs={Hs} S={S} budget={budget} n_imp={n_imp} kbit={kbit} ends {sink}+{recent}")
+    sc = inputs.make_scores(B, Hs, S, seed=S + Hs, ties=True)
+    ends = dict(n_sink=sink, n_recent=recent)
+    check_select(kv, oracle, sc, budget, n_imp, kbit, anchor, seed=9, **ends)
+    check_select(kv, oracle, inputs.make_scores(B, Hs, S, seed=S), budget, n_imp, kbit, anchor, seed=10, **ends)
+    check_select(kv, oracle, torch.ones_like(sc), budget, n_imp, kbit, anchor, seed=11, **ends)
+    odd = -sc
+    odd[:, :, ::5], odd[:, :, ::7], odd[:, :, 3::11] = -0.0, float("-inf"), 0.0
+    check_select(kv, oracle, odd, budget, n_imp, kbit, anchor, seed=12, **ends)
+    check_select(kv, oracle, odd, budget, budget - sink - recent, kbit, anchor, seed=13, **ends)
+
+
 @pytest.mark.parametrize("block,levels", [(64, 2), (64, 3), (128, 2), (32, 2), (1, 2)])
 def test_select_on_blocks_of_alternating_sizes(kv, oracle, block, levels):
     """Score rows made of blocks of tokens that alternate between a few magnitudes: the first radix

@@ -81,6 +81,29 @@ def test_units_on_the_static_scratch_array(record):
     assert st2 == st3 == kv.ERR_WORKSPACE and not none and not none3
 
 
+@pytest.mark.parametrize("B,Hs,S,budget,n_imp,route", [
+    # (us: general path / rows and tail apart / one launch)
+    (1, 8, 512, 128, 64, ["select_one_kernel"]),                          # 21.0 / 10.1 / 8.2
+    (2, 2, 700, 160, 120, ["select_one_kernel"]),                         # 20.4 / 9.7 / 8.9
+    (1, 32, 512, 128, 64, ["row_select_kernel", "select_one_kernel"]),    # 28.1 / 11.9 / 13.7
+    (1, 8, 2048, 512, 300, ["row_select_kernel", "select_one_kernel"]),   # 23.4 / 12.8 / 20.2
+    (256, 8, 2048, 512, 300, ["select_one_kernel"]),                      # 99.6 / 36.6 / 24.0
+    (1, 8, 4096, 1024, 512, ["row_select_kernel", "select_one_kernel"]),  # 24.9 / 17.3
+    (1, 8, 512, 128, 128, ["select_one_kernel"]), (1, 32, 4096, 99, 99, ["row_select_kernel"]),  # the important tokens alone
+    (1, 4, 1300, 20, 10, ["row_select_kernel"] + 2 * ["group"] + ["medoid_emit_kernel"]),        # buckets of 129
+    (1, 8, 8192, 2048, 1500, ["row_select_kernel"] + 2 * ["group"] + ["medoid_emit_kernel"]),    # 26.6, 24.4 without slices
+    (1, 32, 8192, 2048, 1500, ["slice_hist_kernel", "row_select_kernel"] + 2 * ["group"] + ["medoid_emit_kernel"]),  # 35.7, 37.4
+    (1, 8, 16384, 4096, 3072, ["slice_hist_kernel", "row_select_kernel"] + 2 * ["group"] + ["medoid_emit_kernel"]),  # 30.6, 32.6
+])
+def test_selection_takes_the_launches_that_measured_less(record, B, Hs, S, budget, n_imp, route):
+    a = kv.make_select_args(B, Hs, S, budget, n_imp, 0, "mean", 1)
+    need = kv.kvcrush_select_workspace(a)
+    (st, ran), (st2, none), (st3, static) = record([L.select(a, need), L.select(a, need - 1), L.select_static(a)])
+    assert st == kv.OK and st2 == kv.ERR_WORKSPACE and not none
+    assert len(ran) == len(route) and all(k == r or r == "group" and k.startswith("group_") for k, r in zip(kernels(ran), route))
+    assert st3 == kv.ERR_WORKSPACE or (st3 == kv.OK and static == ran)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype,rg,window,lse,colsum", [
     # (us, tiled / short, pass A and pass B)
     (32, 32, 8, 128, 128, 1, 1, 0, "tiled", "tiled"),     # 13 / 41, 25 / 33: many sequences of short prompts
