@@ -328,6 +328,16 @@ kvcrush_status kvcrush_scores_append(const kvcrush_shape* shape, int32_t capacit
                                      float* scores, void* workspace, size_t workspace_bytes,
                                      void* hip_stream);
 
+/* The same step on a dense cache that the new token has not been written to yet:
+ * k_new, v_new [B, Hkv, D] (packed, 16-byte aligned, not inside the cache's row S - 1)
+ * are put into row S - 1 of k and v [B, Hkv, capacity, D] by the kernels that read the
+ * keys, which saves two copies in front of them; the scores are those of
+ * kvcrush_scores_append after these copies, bit for bit. */
+kvcrush_status kvcrush_decode_step(const kvcrush_shape* shape, int32_t capacity, const void* q_new,
+                                   const void* k_new, const void* v_new, void* k, void* v,
+                                   float* scores, void* workspace, size_t workspace_bytes,
+                                   void* hip_stream);
+
 /* Eviction while decoding: once kvcrush_select (run on the valid part of the
  * score rows, see kvcrush_select_args.score_stride) has chosen `budget` tokens,
  * they and their running scores move to the front of a second cache:

@@ -22,7 +22,7 @@ EXPORTS = (
     "kvcrush_scores_workspace", "kvcrush_scores", "kvcrush_row_lse_workspace", "kvcrush_row_lse",
     "kvcrush_pool_scores",
     "kvcrush_select_workspace", "kvcrush_select", "kvcrush_select_static", "kvcrush_compact", "kvcrush_scores_append_workspace",
-    "kvcrush_scores_append", "kvcrush_compact_cache", "kvcrush_compact_block_table", "kvcrush_status_string",
+    "kvcrush_scores_append", "kvcrush_decode_step", "kvcrush_compact_cache", "kvcrush_compact_block_table", "kvcrush_status_string",
     "kvcrush_version",
 )
 
@@ -81,6 +81,8 @@ def load() -> ctypes.CDLL:
         L.kvcrush_scores_append_workspace.restype = sz
         L.kvcrush_scores_append.argtypes = [ctypes.POINTER(Shape), i32, vp, vp, vp, vp, i32, vp, vp, sz, vp]
         L.kvcrush_scores_append.restype = ctypes.c_int
+        L.kvcrush_decode_step.argtypes = [ctypes.POINTER(Shape), i32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+        L.kvcrush_decode_step.restype = ctypes.c_int
         L.kvcrush_compact_cache.argtypes = [i32] * 8 + [vp] * 8
         L.kvcrush_compact_cache.restype = ctypes.c_int
         L.kvcrush_compact_block_table.argtypes = [i32] * 4 + [vp] * 4
@@ -351,6 +353,29 @@ def kvcrush_scores_append(q_new, k_cache, scores_cache, S: int, reduce_groups: b
                                       _ptr(block_table), block_size, _ptr(scores_cache), _ptr(workspace),
                                       workspace.numel(), _stream(stream))
     _check(st, "kvcrush_scores_append")
+    return scores_cache
+
+
+def kvcrush_decode_step(q_new, k_new, v_new, k_cache, v_cache, scores_cache, S: int, reduce_groups: bool, workspace,
+                        stream=None, scale=0.0):
+    """kvcrush_scores_append on dense caches whose row S - 1 the call itself fills with k_new and v_new [B,Hkv,D]."""
+    for name, t in (("q_new", q_new), ("k_new", k_new), ("v_new", v_new), ("k_cache", k_cache), ("v_cache", v_cache),
+                    ("scores_cache", scores_cache)):
+        _dev(t, name)
+    if q_new.dim() != 3 or k_cache.dim() != 4 or scores_cache.dtype != torch.float32 \
+            or any(t.dtype != k_cache.dtype for t in (q_new, k_new, v_new, v_cache)):
+        raise ValueError("q_new [B,Hq,D] and k_cache [B,Hkv,capacity,D] of one dtype, scores_cache fp32")
+    B, Hq, D = q_new.shape
+    Hkv, cap = k_cache.shape[1], k_cache.shape[2]
+    if tuple(k_cache.shape) != (B, Hkv, cap, D) or v_cache.shape != k_cache.shape \
+            or tuple(k_new.shape) != (B, Hkv, D) or v_new.shape != k_new.shape:
+        raise ValueError("q_new, k_new, v_new and the caches disagree on B, Hkv or D")
+    if tuple(scores_cache.shape) != (B, Hkv if reduce_groups else Hq, cap):
+        raise ValueError("scores_cache must be [B,Hs,capacity]")
+    shape = Shape(B, Hq, Hkv, int(S), D, _dtype_code(q_new), int(bool(reduce_groups)), 0, float(scale))
+    st = load().kvcrush_decode_step(ctypes.byref(shape), cap, _ptr(q_new), _ptr(k_new), _ptr(v_new), _ptr(k_cache),
+                                    _ptr(v_cache), _ptr(scores_cache), _ptr(workspace), workspace.numel(), _stream(stream))
+    _check(st, "kvcrush_decode_step")
     return scores_cache
 
 

@@ -46,6 +46,10 @@ struct AppendParams {
   const int* block_table;  // null: k is dense [B,Hkv,capacity,D]; else k is a pool
                            // [n_blocks,block_size,Hkv,D] and block_table [B,capacity/block_size]
   int block_size;
+  const char* k_new;   // null, or [B,Hkv,D]: the key of token S - 1 (and its value), not yet in the cache: the
+  const char* v_new;   // workgroup that has this token reads it from here and puts it into k_slot and v_slot,
+  char* k_slot;        // which are k and v (dense caches without lengths)
+  char* v_slot;
   int B, Hq, Hkv, S, capacity, G, reduce_groups;  // S: valid tokens, or their upper bound with lengths
   int n_kb;            // kKeysPerWg-key blocks of S
   float scale_log2;    // log2(e) x softmax scale (1 / sqrt(D) unless the caller set one)
@@ -57,6 +61,16 @@ __device__ __forceinline__ const char* key_row(const AppendParams& p, int b, int
   if (!p.block_table) return p.k + ((size_t)bg * p.capacity + key) * row_bytes;
   const int blk = p.block_table[(size_t)b * (p.capacity / p.block_size) + key / p.block_size];
   return p.k + (((size_t)blk * p.block_size + key % p.block_size) * p.Hkv + g) * row_bytes;
+}
+
+// The new token's rows go to their place in the cache: `lane` of the 2 * row_bytes / 16 lanes of one wave that do it.
+__device__ __forceinline__ void store_new_token(const AppendParams& p, int bg, int S, int lane, int row_bytes) {
+  const int chunks = row_bytes / 16;
+  if (lane >= 2 * chunks) return;
+  const bool key = lane < chunks;
+  const size_t off = (size_t)(lane % chunks) * 16, src = (size_t)bg * row_bytes + off;
+  const size_t dst = ((size_t)bg * p.capacity + S - 1) * row_bytes + off;
+  *(vec16*)((key ? p.k_slot : p.v_slot) + dst) = *(const vec16*)((key ? p.k_new : p.v_new) + src);
 }
 
 template <bool BF16>
@@ -133,7 +147,9 @@ __global__ __launch_bounds__(kThreads) void append_logits_kernel(AppendParams p)
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const int key = k0 + wave * (kKeysPerWg / kWaves) + (it0 + u) * kRowsPerWave + sub;
-        kx[u] = *(const vec16*)(key_row(p, b, g, bg, min(key, S - 1), kRowBytes) + col * 16);
+        const bool fresh = p.k_new && key >= S - 1;
+        kx[u] = *(const vec16*)((fresh ? p.k_new + (size_t)bg * kRowBytes : key_row(p, b, g, bg, min(key, S - 1), kRowBytes)) +
+                                col * 16);
       }
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
@@ -166,6 +182,7 @@ __global__ __launch_bounds__(kThreads) void append_logits_kernel(AppendParams p)
     }
     __syncthreads();  // lds_logit is rewritten by the next chunk of heads
   }
+  if (p.k_new && S - 1 < k0 + kKeysPerWg && wave == 0) store_new_token(p, bg, S, lane, kRowBytes);
 }
 
 // bf16 / fp16: logits of kKeysPerWg keys x up to 32 heads per pass on the matrix cores.
@@ -217,8 +234,17 @@ __global__ __launch_bounds__(kMfmaWaves * KVC_WAVE, 4) void append_logits_mfma_k
         copy(pool, ((size_t)blk[j] * p.block_size + (row0 + row[j]) % p.block_size) * p.Hkv * C::kRowBytes + in_row[j], j);
     } else {
       const char* rows = p.k + ((size_t)bg * p.capacity + row0) * C::kRowBytes;  // uniform
+      const int last = S - 1 - row0;
+      if (p.k_new && last < 32) {  // the wave with the new token
+        const char* fresh = p.k_new + (size_t)bg * C::kRowBytes;
 #pragma unroll
-      for (int j = 0; j < kLoads; ++j) copy(rows, (uint32_t)row[j] * C::kRowBytes + in_row[j], j);
+        for (int j = 0; j < kLoads; ++j)
+          copy(row[j] == last ? fresh : rows + (uint32_t)row[j] * C::kRowBytes, in_row[j], j);
+        store_new_token(p, bg, S, lane, C::kRowBytes);
+      } else {
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) copy(rows, (uint32_t)row[j] * C::kRowBytes + in_row[j], j);
+      }
     }
   }
   const int n = lane & 31;  // result column of this lane = head inside the chunk
@@ -410,11 +436,11 @@ extern "C" size_t kvcrush_scores_append_workspace(const kvcrush_shape* shape, in
   return logits_bytes(shape) + part_bytes(shape);
 }
 
-extern "C" kvcrush_status kvcrush_scores_append(const kvcrush_shape* shape, int32_t capacity,
-                                                const int32_t* lengths, const void* q_new,
-                                                const void* k, const int32_t* block_table,
-                                                int32_t block_size, float* scores, void* workspace,
-                                                size_t workspace_bytes, void* hip_stream) {
+namespace {
+kvcrush_status append_entry(const kvcrush_shape* shape, int32_t capacity, const int32_t* lengths, const void* q_new,
+                            const void* k, const int32_t* block_table, int32_t block_size, const void* k_new,
+                            const void* v_new, void* v, float* scores, void* workspace, size_t workspace_bytes,
+                            void* hip_stream) {
   if (!append_shape_ok(shape, capacity)) return KVCRUSH_ERR_INVALID_ARG;
   if (block_table && (block_size < 1 || capacity % block_size != 0)) return KVCRUSH_ERR_INVALID_ARG;
   if (shape->D != 64 && shape->D != 128) return KVCRUSH_ERR_UNSUPPORTED;
@@ -434,6 +460,10 @@ extern "C" kvcrush_status kvcrush_scores_append(const kvcrush_shape* shape, int3
   p.lengths = lengths;
   p.block_table = block_table;
   p.block_size = block_table ? block_size : 1;
+  p.k_new = (const char*)k_new;
+  p.v_new = (const char*)v_new;
+  p.k_slot = (char*)k;
+  p.v_slot = (char*)v;
   p.B = shape->B;
   p.Hq = shape->Hq;
   p.Hkv = shape->Hkv;
@@ -452,4 +482,23 @@ extern "C" kvcrush_status kvcrush_scores_append(const kvcrush_shape* shape, int3
   if (bf16 && shape->D == 64) return launch_append<true, 64>(p, stream);
   if (!bf16 && shape->D == 128) return launch_append<false, 128>(p, stream);
   return launch_append<false, 64>(p, stream);
+}
+}  // namespace
+
+extern "C" kvcrush_status kvcrush_scores_append(const kvcrush_shape* shape, int32_t capacity,
+                                                const int32_t* lengths, const void* q_new,
+                                                const void* k, const int32_t* block_table,
+                                                int32_t block_size, float* scores, void* workspace,
+                                                size_t workspace_bytes, void* hip_stream) {
+  return append_entry(shape, capacity, lengths, q_new, k, block_table, block_size, nullptr, nullptr, nullptr, scores,
+                      workspace, workspace_bytes, hip_stream);
+}
+
+extern "C" kvcrush_status kvcrush_decode_step(const kvcrush_shape* shape, int32_t capacity, const void* q_new,
+                                              const void* k_new, const void* v_new, void* k, void* v, float* scores,
+                                              void* workspace, size_t workspace_bytes, void* hip_stream) {
+  if (!k_new || !v_new || !v) return KVCRUSH_ERR_INVALID_ARG;
+  if (!kvc::aligned16(k_new) || !kvc::aligned16(v_new) || !kvc::aligned16(v)) return KVCRUSH_ERR_INVALID_ARG;
+  return append_entry(shape, capacity, nullptr, q_new, k, nullptr, 0, k_new, v_new, v, scores, workspace, workspace_bytes,
+                      hip_stream);
 }

@@ -128,15 +128,26 @@ class DecodeCache:
         """One generated token: q_new [B,Hq,D], k_new and v_new [B,Hkv,D].  Evicts first if the buffer is full."""
         if self.n == self.capacity:
             self.evict()
-        self.k[:, :, self.n].copy_(k_new)
-        self.v[:, :, self.n].copy_(v_new)
+        k, v, scores = self._sets[self._cur]
+        # rows that the library can read where they are go into the cache with the step's own kernels; others (views,
+        # other types, tensors that autograd follows) are copied first
+        in_place = all(type(t) is torch.Tensor and t.dtype == k.dtype and t.device == k.device and t.dim() == 3
+                       and t.shape == (k.shape[0], k.shape[1], k.shape[3]) and t.is_contiguous() and not t.requires_grad
+                       and t.data_ptr() % 16 == 0 for t in (k_new, v_new))
+        if not in_place:
+            k[:, :, self.n].copy_(k_new)
+            v[:, :, self.n].copy_(v_new)
         self.n += 1
         if self._append_ws is None:
             B, Hq, D = q_new.shape
-            probe = kv.Shape(B, Hq, self.k.shape[1], self.capacity, D, kv._dtype_code(q_new), int(self.reduce_groups),
+            probe = kv.Shape(B, Hq, k.shape[1], self.capacity, D, kv._dtype_code(q_new), int(self.reduce_groups),
                              0, self.scale)
             self._append_ws = torch.empty(max(kv.kvcrush_scores_append_workspace(probe, self.capacity), 16),
                                           dtype=torch.uint8, device=q_new.device)
-        kv.kvcrush_scores_append(q_new, self.k, self.scores, self.n, self.reduce_groups, workspace=self._append_ws,
-                                 scale=self.scale)
+        if in_place:
+            kv.kvcrush_decode_step(q_new, k_new, v_new, k, v, scores, self.n, self.reduce_groups, self._append_ws,
+                                   scale=self.scale)
+        else:
+            kv.kvcrush_scores_append(q_new, k, scores, self.n, self.reduce_groups, workspace=self._append_ws,
+                                     scale=self.scale)
         return self.n

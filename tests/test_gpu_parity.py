@@ -1035,6 +1035,45 @@ def test_whole_path_replays_from_a_hip_graph(kv, oracle):
     assert rel_err(got[0], ref) <= SCORE_RTOL
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,cap,D,dtype,rg", [
+    (1, 8, 2, 1, 5, 128, "bf16", True), (2, 4, 4, 32, 40, 64, "f16", False), (1, 12, 4, 33, 33, 128, "bf16", True),
+    (3, 8, 8, 256, 300, 128, "f16", True), (1, 40, 1, 257, 260, 64, "bf16", True), (8, 32, 8, 2049, 2112, 128, "bf16", True),
+    (2, 8, 2, 1, 3, 64, "f32", True), (1, 9, 1, 257, 300, 128, "f32", False), (2, 6, 2, 600, 640, 128, "f32", True),
+])
+def test_decode_step_is_append_after_the_copies(kv, B, Hq, Hkv, S, cap, D, dtype, rg):
+    """kvcrush_decode_step puts the new token's rows where they belong, touches nothing else and leaves the scores
+    of kvcrush_scores_append on the filled cache, bit for bit; DecodeCache gives the same for rows it cannot hand on."""
+    say(f"decode step B={B} Hq={Hq} Hkv={Hkv} S={S} capacity={cap} D={D} {dtype} reduce={rg}")
+    from paper_2503_00022_amd import pipeline
+    g = torch.Generator().manual_seed(S + D)
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    k, v, kn, vn, qn = [torch.randn(*s, generator=g).to(dt).cuda() for s in
+                        ((B, Hkv, cap, D), (B, Hkv, cap, D), (B, Hkv, D), (B, Hkv, D), (B, Hq, D))]
+    sc = torch.rand(B, Hkv if rg else Hq, cap, generator=g).cuda()
+    full_k, full_v, want = k.clone(), v.clone(), sc.clone()
+    full_k[:, :, S - 1], full_v[:, :, S - 1] = kn, vn
+    kv.kvcrush_scores_append(qn, full_k, want, S, rg)
+    ws = torch.empty(kv.kvcrush_scores_append_workspace(kv.Shape(B, Hq, Hkv, S, D, kv._dtype_code(k), int(rg)), cap),
+                     dtype=torch.uint8, device="cuda")
+    for _ in range(2):                                            # (again on the cache that holds the token now)
+        got = sc.clone()
+        kv.kvcrush_decode_step(qn, kn, vn, k, v, got, S, rg, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want) and torch.equal(k, full_k) and torch.equal(v, full_v)
+    if S > 1:
+        caches = [pipeline.DecodeCache(full_k[:, :, :S - 1], full_v[:, :, :S - 1], sc[:, :, :S - 1], 1, 1, max(cap, 2),
+                                       reduce_groups=rg) for _ in range(3)]
+        spread = lambda t: torch.stack([t, t], -1)[..., 0]        # not contiguous
+        for c, (a, b) in zip(caches, [(kn, vn), (spread(kn), vn), (kn.double(), spread(vn))]):
+            if c.n < c.capacity:
+                assert c.append(qn, a, b) == S
+        torch.cuda.synchronize()
+        for c in caches:
+            if c.n == S:
+                assert torch.equal(c.k[:, :, :S], full_k[:, :, :S]) and torch.equal(c.v[:, :, :S], full_v[:, :, :S])
+                assert torch.equal(c.scores[:, :, :S], want[:, :, :S])
+
+
 def test_decode_steps_replay_from_a_hip_graph(kv, oracle):
     say("graph capture of a decoding step, replays at growing cache lengths need one graph per length")
     B, Hq, Hkv, D, cap = 2, 8, 2, 128, 512

@@ -288,6 +288,19 @@ def test_decode_entry_points_validation(lib):
     assert binding.kvcrush_select_workspace(mk(1, 8, 100, 50, 10, score_stride=128)) > 0
 
 
+def test_decode_step_validation(lib):
+    sh = lambda **kw: make_shape(dict(B=2, Hq=8, Hkv=2, S=300, D=128, dtype=1, reduce_groups=1, obs_window=0), kw)
+    need = binding.kvcrush_scores_append_workspace(sh(), 320)
+    call = lambda shape, cap=320, q=FAKE, kn=FAKE, vn=FAKE, k=FAKE, v=FAKE, sc=FAKE, ws=FAKE, n=1 << 40: \
+        lib.kvcrush_decode_step(ctypes.byref(shape), cap, q, kn, vn, k, v, sc, ws, n, None)
+    for name in ("q", "kn", "vn", "k", "v", "sc"):
+        assert call(sh(), **{name: None}) == binding.ERR_INVALID_ARG
+        assert call(sh(), **{name: ctypes.c_void_p(0x1002)}) == binding.ERR_INVALID_ARG
+    assert call(sh(), cap=100) == binding.ERR_INVALID_ARG
+    assert call(sh(D=32)) == binding.ERR_UNSUPPORTED
+    assert call(sh(), ws=None) == call(sh(), n=need - 1) == binding.ERR_WORKSPACE
+
+
 def test_pipeline_classes_validate_before_touching_the_gpu(lib):
     """The buffer-owning wrappers import without a GPU and reject a capacity that cannot hold the cache."""
     import torch
