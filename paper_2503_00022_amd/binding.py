@@ -129,9 +129,14 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# The current stream's handle without the Stream object around it (0.1 us instead of 2.7, of the 15 that a whole
+# decoding step has); read on every call.
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+    (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return ctypes.c_void_p(_current_raw_stream(torch.cuda.current_device()) if stream is None else stream.cuda_stream)
 
 
 def _check(status: int, what: str):
@@ -356,6 +361,13 @@ def kvcrush_scores_append(q_new, k_cache, scores_cache, S: int, reduce_groups: b
     return scores_cache
 
 
+def _decode_step(shape, capacity, q_new, k_new, v_new, k, v, scores, workspace, stream=None):
+    """The call itself, on addresses that the caller has checked."""
+    st = load().kvcrush_decode_step(ctypes.byref(shape), capacity, q_new, k_new, v_new, k, v, scores, workspace.data_ptr(),
+                                    workspace.numel(), _stream(stream))
+    _check(st, "kvcrush_decode_step")
+
+
 def kvcrush_decode_step(q_new, k_new, v_new, k_cache, v_cache, scores_cache, S: int, reduce_groups: bool, workspace,
                         stream=None, scale=0.0):
     """kvcrush_scores_append on dense caches whose row S - 1 the call itself fills with k_new and v_new [B,Hkv,D]."""
@@ -373,9 +385,8 @@ def kvcrush_decode_step(q_new, k_new, v_new, k_cache, v_cache, scores_cache, S: 
     if tuple(scores_cache.shape) != (B, Hkv if reduce_groups else Hq, cap):
         raise ValueError("scores_cache must be [B,Hs,capacity]")
     shape = Shape(B, Hq, Hkv, int(S), D, _dtype_code(q_new), int(bool(reduce_groups)), 0, float(scale))
-    st = load().kvcrush_decode_step(ctypes.byref(shape), cap, _ptr(q_new), _ptr(k_new), _ptr(v_new), _ptr(k_cache),
-                                    _ptr(v_cache), _ptr(scores_cache), _ptr(workspace), workspace.numel(), _stream(stream))
-    _check(st, "kvcrush_decode_step")
+    _decode_step(shape, cap, q_new.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(),
+                 scores_cache.data_ptr(), workspace, stream)
     return scores_cache
 
 

@@ -129,24 +129,30 @@ class DecodeCache:
         if self.n == self.capacity:
             self.evict()
         k, v, scores = self._sets[self._cur]
-        # rows that the library can read where they are go into the cache with the step's own kernels; others (views,
-        # other types, tensors that autograd follows) are copied first
-        in_place = all(type(t) is torch.Tensor and t.dtype == k.dtype and t.device == k.device and t.dim() == 3
-                       and t.shape == (k.shape[0], k.shape[1], k.shape[3]) and t.is_contiguous() and not t.requires_grad
-                       and t.data_ptr() % 16 == 0 for t in (k_new, v_new))
+        # Rows that the library can read where they are go into the cache with the step's own kernels; others (views,
+        # other types, tensors that autograd follows) are copied first.  The two kernels of a step take about as long
+        # as Python takes for a dozen attribute reads and calls, so every property is looked at once, here.
+        dtype, device = k.dtype, k.device
+        B, Hkv, _, D = k.shape
+        rows, ptrs = (B, Hkv, D), (k_new.data_ptr(), v_new.data_ptr())
+        in_place = (ptrs[0] | ptrs[1]) % 16 == 0 and type(k_new) is type(v_new) is torch.Tensor \
+            and k_new.dtype == v_new.dtype == q_new.dtype == dtype and k_new.device == v_new.device == q_new.device == device \
+            and k_new.shape == v_new.shape == rows and k_new.is_contiguous() and v_new.is_contiguous() \
+            and not k_new.requires_grad and not v_new.requires_grad \
+            and q_new.dim() == 3 and q_new.shape[0] == B and q_new.shape[2] == D and q_new.is_contiguous()
         if not in_place:
             k[:, :, self.n].copy_(k_new)
             v[:, :, self.n].copy_(v_new)
         self.n += 1
         if self._append_ws is None:
-            B, Hq, D = q_new.shape
-            probe = kv.Shape(B, Hq, k.shape[1], self.capacity, D, kv._dtype_code(q_new), int(self.reduce_groups),
-                             0, self.scale)
+            probe = kv.Shape(q_new.shape[0], q_new.shape[1], Hkv, self.capacity, q_new.shape[2], kv._dtype_code(q_new),
+                             int(self.reduce_groups), 0, self.scale)
             self._append_ws = torch.empty(max(kv.kvcrush_scores_append_workspace(probe, self.capacity), 16),
                                           dtype=torch.uint8, device=q_new.device)
-        if in_place:
-            kv.kvcrush_decode_step(q_new, k_new, v_new, k, v, scores, self.n, self.reduce_groups, self._append_ws,
-                                   scale=self.scale)
+        if in_place and scores.shape[1] == (Hkv if self.reduce_groups else q_new.shape[1]):
+            shape = kv.Shape(B, q_new.shape[1], Hkv, self.n, D, kv._dtype_code(k), int(self.reduce_groups), 0, self.scale)
+            kv._decode_step(shape, self.capacity, q_new.data_ptr(), *ptrs, k.data_ptr(), v.data_ptr(), scores.data_ptr(),
+                            self._append_ws)
         else:
             kv.kvcrush_scores_append(q_new, k, scores, self.n, self.reduce_groups, workspace=self._append_ws,
                                      scale=self.scale)
