@@ -111,7 +111,8 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return r;
 }
 
-template <bool BF16, int D>
+// FRESH: the new token is not in the cache yet (an instantiation of its own: the test costs the loop 3 %).
+template <bool BF16, int D, bool FRESH>
 __global__ __launch_bounds__(kThreads) void append_logits_kernel(AppendParams p) {
   constexpr int kRowBytes = D * (BF16 ? 2 : 4);
   constexpr int kLanesPerRow = kRowBytes / 16;          // 8, 16 or 32
@@ -147,7 +148,7 @@ __global__ __launch_bounds__(kThreads) void append_logits_kernel(AppendParams p)
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const int key = k0 + wave * (kKeysPerWg / kWaves) + (it0 + u) * kRowsPerWave + sub;
-        const bool fresh = p.k_new && key >= S - 1;
+        const bool fresh = FRESH && key >= S - 1;
         kx[u] = *(const vec16*)((fresh ? p.k_new + (size_t)bg * kRowBytes : key_row(p, b, g, bg, min(key, S - 1), kRowBytes)) +
                                 col * 16);
       }
@@ -182,7 +183,7 @@ __global__ __launch_bounds__(kThreads) void append_logits_kernel(AppendParams p)
     }
     __syncthreads();  // lds_logit is rewritten by the next chunk of heads
   }
-  if (p.k_new && S - 1 < k0 + kKeysPerWg && wave == 0) store_new_token(p, bg, S, lane, kRowBytes);
+  if (FRESH && S - 1 < k0 + kKeysPerWg && wave == 0) store_new_token(p, bg, S, lane, kRowBytes);
 }
 
 // bf16 / fp16: logits of kKeysPerWg keys x up to 32 heads per pass on the matrix cores.
@@ -234,17 +235,8 @@ __global__ __launch_bounds__(kMfmaWaves * KVC_WAVE, 4) void append_logits_mfma_k
         copy(pool, ((size_t)blk[j] * p.block_size + (row0 + row[j]) % p.block_size) * p.Hkv * C::kRowBytes + in_row[j], j);
     } else {
       const char* rows = p.k + ((size_t)bg * p.capacity + row0) * C::kRowBytes;  // uniform
-      const int last = S - 1 - row0;
-      if (p.k_new && last < 32) {  // the wave with the new token
-        const char* fresh = p.k_new + (size_t)bg * C::kRowBytes;
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j)
-          copy(row[j] == last ? fresh : rows + (uint32_t)row[j] * C::kRowBytes, in_row[j], j);
-        store_new_token(p, bg, S, lane, C::kRowBytes);
-      } else {
-#pragma unroll
-        for (int j = 0; j < kLoads; ++j) copy(rows, (uint32_t)row[j] * C::kRowBytes + in_row[j], j);
-      }
+      for (int j = 0; j < kLoads; ++j) copy(rows, (uint32_t)row[j] * C::kRowBytes + in_row[j], j);
     }
   }
   const int n = lane & 31;  // result column of this lane = head inside the chunk
@@ -263,6 +255,12 @@ __global__ __launch_bounds__(kMfmaWaves * KVC_WAVE, 4) void append_logits_mfma_k
   };
   load_q(0);
   wait_async_loads();  // (a wave reads only what it copied itself)
+  if (p.k_new && live && S - 1 - row0 < 32) {  // the wave with the new token: its row in place of what the cache held
+    if (lane < C::kChunksPerRow)
+      *(vec16*)(lds[wave] + lds_chunk_offset<C>(S - 1 - row0, lane)) =
+          *(const vec16*)(p.k_new + (size_t)bg * C::kRowBytes + lane * 16);
+    store_new_token(p, bg, S, lane, C::kRowBytes);
+  }
 
   const int off0 = lds_frag_offset0<C>(lane);
   const int key_base = row0 + 4 * (lane >> 5);  // + 8 * (r / 4) + r % 4
@@ -313,11 +311,13 @@ __global__ __launch_bounds__(kMfmaWaves * KVC_WAVE, 4) void append_logits_mfma_k
 
 // Bound by the logits and scores it moves, 4 * (G + 2) bytes a key and score row, and by the chain
 // pairs -> normalisers -> probabilities in front of them: a wave merges one head's pairs by itself
-// (no barrier per head), and the logits of KPT keys per thread, 256 apart, are in flight together.
-// A lane has four pairs on their way at a time: at 131072 keys and one head a row, the chain of pair loads
-// one by one took 5 us of the call's 26.  Measured: 4 sequences of up to 32768 keys, 32 heads in 8 groups
-// 17.9 -> 9.6 us (27 MB); 8 sequences of 2048 keys 7.2 -> 4.3 us.
-template <int KPT>
+// (no barrier per head), and the logits of KPT keys per thread, 256 apart, are in flight together, those of the
+// row's first kFirst heads while the pairs are merged (four, or one where a row is one head: the registers of four
+// would cost waves there, 4 to 8 % of the whole call).  A lane has four pairs on their way at a time: at 131072 keys and
+// one head a row, the chain of pair loads one by one took 5 us of the call's 26.  Measured, whole calls, without and
+// with the logits ahead: 4 sequences of up to 32768 keys, 32 heads in 8 groups (27 MB here) 67.3 -> 62.9 us, of
+// which this kernel had 9.6; a decoding step of 8 sequences of 2048 keys 14.9 -> 13.6, of which it had 4.3.
+template <int KPT, int kFirst>
 __global__ __launch_bounds__(kThreads) void append_update_kernel(AppendParams p) {
   constexpr int kHeads = 32;  // heads whose normalisers are held at once
   __shared__ float lse2[kHeads];
@@ -340,6 +340,15 @@ __global__ __launch_bounds__(kThreads) void append_update_kernel(AppendParams p)
     acc[u] = 0.0f;
     old[u] = key < S - 1 ? dst[key] : 0.0f;  // the new token's slot starts from nothing
   }
+  // the first heads' logits are on their way while the pairs are merged
+  float x[kFirst][KPT];
+#pragma unroll
+  for (int i = 0; i < kFirst; ++i)
+    if (i < n_heads) {  // uniform
+      const float* src = logits + ((size_t)b * p.Hq + h_first + i) * p.S;
+#pragma unroll
+      for (int u = 0; u < KPT; ++u) x[i][u] = src[min(key0 + u * kThreads + tid, S - 1)];
+    }
   for (int h0 = 0; h0 < n_heads; h0 += kHeads) {
     const int nh = min(kHeads, n_heads - h0);
     if (h0 > 0) __syncthreads();
@@ -371,7 +380,17 @@ __global__ __launch_bounds__(kThreads) void append_update_kernel(AppendParams p)
       if (lane == 0) lse2[i] = mt + __builtin_amdgcn_logf(l);
     }
     __syncthreads();
-    for (int i = 0; i < nh; ++i) {  // heads ascending
+    int done = 0;
+    if (h0 == 0) {
+#pragma unroll
+      for (int i = 0; i < kFirst; ++i)
+        if (i < nh) {  // uniform
+#pragma unroll
+          for (int u = 0; u < KPT; ++u) acc[u] += __builtin_amdgcn_exp2f(x[i][u] - lse2[i]);
+        }
+      done = kFirst;
+    }
+    for (int i = done; i < nh; ++i) {  // heads ascending
       const float* src = logits + ((size_t)b * p.Hq + h_first + h0 + i) * p.S;
       const float ref = lse2[i];
 #pragma unroll
@@ -412,6 +431,15 @@ bool append_shape_ok(const kvcrush_shape* s, int capacity) {
 // Keys per thread of the update: four where that still leaves four workgroups to a compute unit.
 constexpr int kUpdateKeys = 4;
 constexpr long long kUpdateWorkgroups = 1024;
+template <int FIRST>
+kvcrush_status launch_update(const AppendParams& p, hipStream_t stream) {
+  const int rows = p.B * (p.reduce_groups ? p.Hkv : p.Hq);
+  const int wide = (p.S + kThreads * kUpdateKeys - 1) / (kThreads * kUpdateKeys);
+  if ((long long)wide * rows >= kUpdateWorkgroups)
+    return kvc::launch(append_update_kernel<kUpdateKeys, FIRST>, dim3(wide, rows), dim3(kThreads), 0, stream, p);
+  return kvc::launch(append_update_kernel<1, FIRST>, dim3((p.S + kThreads - 1) / kThreads, rows), dim3(kThreads), 0, stream, p);
+}
+
 template <bool BF16, int D, bool F16 = false>
 kvcrush_status launch_append(const AppendParams& p, hipStream_t stream) {
   const dim3 grid(p.n_kb, p.B * p.Hkv);
@@ -419,14 +447,11 @@ kvcrush_status launch_append(const AppendParams& p, hipStream_t stream) {
   if constexpr (BF16) {
     st = kvc::launch(append_logits_mfma_kernel<D, F16>, grid, dim3(kMfmaWaves * KVC_WAVE), 0, stream, p);
   } else {
-    st = kvc::launch(append_logits_kernel<BF16, D>, grid, dim3(kThreads), 0, stream, p);
+    st = p.k_new ? kvc::launch(append_logits_kernel<BF16, D, true>, grid, dim3(kThreads), 0, stream, p)
+                 : kvc::launch(append_logits_kernel<BF16, D, false>, grid, dim3(kThreads), 0, stream, p);
   }
   if (st != KVCRUSH_OK) return st;
-  const int rows = p.B * (p.reduce_groups ? p.Hkv : p.Hq);
-  const int wide = (p.S + kThreads * kUpdateKeys - 1) / (kThreads * kUpdateKeys);
-  if ((long long)wide * rows >= kUpdateWorkgroups)
-    return kvc::launch(append_update_kernel<kUpdateKeys>, dim3(wide, rows), dim3(kThreads), 0, stream, p);
-  return kvc::launch(append_update_kernel<1>, dim3((p.S + kThreads - 1) / kThreads, rows), dim3(kThreads), 0, stream, p);
+  return p.reduce_groups && p.G > 1 ? launch_update<4>(p, stream) : launch_update<1>(p, stream);
 }
 
 }  // namespace
