@@ -141,23 +141,21 @@ __device__ __forceinline__ void colsum_update(const f32x16& acc, f32x16& col, fl
   }
 }
 
-// Sums every register over the 32 lanes of each half wave: each exchange halves the registers a
-// lane is responsible for (16 exchanges instead of 80), and the additions pair up as in a plain
-// butterfly.  Lane l ends up with the total of register (l / 2) % 16.
-__device__ __forceinline__ float sum_over_lanes(const f32x16& v, int lane) {
-  float a[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) a[r] = v[r];
-#pragma unroll
-  for (int n = 8; n > 0; n >>= 1) {
-    const bool upper = (lane & (2 * n)) != 0;
-#pragma unroll
-    for (int r = 0; r < n; ++r) {
-      const float keep = upper ? a[r + n] : a[r], give = upper ? a[r] : a[r + n];
-      a[r] = keep + __shfl_xor(give, 2 * n);
-    }
-  }
-  return a[0] + __shfl_xor(a[0], 1);
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ float add_dpp(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
+}
+
+// Sum over the 32 lanes of each half wave, in lanes 16 to 31 of it, by moves between neighbouring lanes that the
+// additions carry out themselves.  The 32 sums that close a piece of pass B took 4 to 5 us of it as 160 exchanges
+// through LDS: S = 4096, 32 heads 82.1 -> 77.4 us, a window of 64 at S = 16384 25.8 -> 21.1, S = 16384, 32 heads in 8
+// groups (4320 pieces) 999 -> 978.
+__device__ __forceinline__ float half_wave_sum(float v) {
+  v = add_dpp<0xB1>(v);       // quad_perm: lane ^ 1
+  v = add_dpp<0x4E>(v);       // quad_perm: lane ^ 2
+  v = add_dpp<0x141>(v);      // row_half_mirror: the other four of eight
+  v = add_dpp<0x140>(v);      // row_mirror: the other eight of sixteen
+  return add_dpp<0x142, 0xa>(v);  // row_bcast:15: lanes 0 to 15 into 16 to 31, 32 to 47 into 48 to 63
 }
 
 // sched_group_barrier classes: matrix ops, LDS reads, vector ALU incl. transcendentals
@@ -685,7 +683,7 @@ __global__ __launch_bounds__(kThreads, 2) void colsum_kernel(ScoreParams p, cons
     }
   }
 
-  // sum over the 32 query lanes of each half-wave; lanes 0 and 32 then hold the rows
+  // sum over the 32 query lanes of each half wave
   float* out;
   int t_limit;
   if (p.n_chunks == 1) {
@@ -697,14 +695,14 @@ __global__ __launch_bounds__(kThreads, 2) void colsum_kernel(ScoreParams p, cons
   }
 #pragma unroll
   for (int ms = 0; ms < 2; ++ms) {
+    float mine = 0.0f;  // lanes 16 to 31 of either half: register lane % 16
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      float v = col[ms][r];
-#pragma unroll
-      for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off);
-      const int t = 32 * ms + acc_row(r, lane);
-      if ((lane & 31) == 0 && t < t_limit) out[t] = v;
+      const float v = half_wave_sum(col[ms][r]);
+      mine = (lane & 15) == r ? v : mine;
     }
+    const int t = 32 * ms + acc_row(lane & 15, lane);
+    if ((lane & 16) != 0 && t < t_limit) out[t] = mine;
   }
 }
 
@@ -735,7 +733,10 @@ __global__ __launch_bounds__(kKeysPerWg) void colsum_reduce_kernel(ScoreParams p
 // two LDS buffers (the next tile lands while this one is worked on; no barrier in the loop).  The
 // waves' partial results meet in LDS once, at the end, in wave order, so neither the slices' merge
 // nor the partial sums' reduction needs a launch of its own.  (Whole sequences only: an observation
-// window always takes the tiled kernels.)
+// window always takes the tiled kernels.)  The column sums' tiles are transposed, C[query][key], so that a
+// lane adds up its own key's column in four registers; with a query per lane sixteen sums had to be taken over
+// 32 lanes by 31 LDS exchanges at the end, 3 us whatever the size (B = 2, S = 700, 8 heads in 2 groups 16.1 -> 13.4
+// us; 4 x 8 heads, S = 400 13.8 -> 7.2).  The tile's 32 lse then pass through LDS, four neighbouring rows a read.
 template <class C>
 constexpr int kShortWaves = C::kSubBytes > 8192 ? 4 : 8;  // (two tiles per wave in LDS: at most 128 KiB)
 
@@ -831,6 +832,7 @@ __global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void colsum
   using C = Cfg<BF16, D>;
   constexpr int W = kShortWaves<C>;
   __shared__ __attribute__((aligned(1024))) char lds[W][2][C::kSubBytes];
+  __shared__ __attribute__((aligned(16))) float lse_tile[W][2][32];  // per wave: the tile's lse in base 2
   __shared__ float part[W][32];
   const int tid = threadIdx.x, lane = kvc::lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / KVC_WAVE);
   const int S = p.S;
@@ -843,9 +845,7 @@ __global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void colsum
   const char* kh = STRIDED ? p.k + b * p.k_sb + kvh * p.k_sh : p.k + ((size_t)b * p.Hkv + kvh) * S * C::kRowBytes;
   const unsigned qrb = STRIDED ? p.q_rb : (unsigned)C::kRowBytes, krb = STRIDED ? p.k_rb : (unsigned)C::kRowBytes;
 
-  f32x16 col;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) col[r] = 0.0f;
+  float col[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // of key lane % 32
   // (head, query tile) pairs, tiles from the diagonal one (kb) on; wave w takes pairs w, w + W, ...
   // in head-major order
   const int nt = (S + 31) / 32 - kb, n_pairs = nt * n_heads;
@@ -872,22 +872,31 @@ __global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void colsum
     for (int pair = wave; pair < n_pairs; pair += W, cur ^= 1) {
       const int tile = kb + t, qi = tile * 32 + (lane & 31);
       wait_own_tile();
-      const float lse2 = qi < S ? raw * kLog2e : INFINITY;  // rows past the end contribute nothing
+      if (lane < 32) lse_tile[wave][cur][lane] = qi < S ? raw * kLog2e : INFINITY;  // rows past the end contribute nothing
       t += W;
       if (pair + W < n_pairs) fetch(cur ^ 1);
       f32x16 acc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-      for (int s = 0; s < C::kSteps; ++s) mma_step<BF16, F16>(acc, kf[s], lds_frag<C>(lds[wave][cur], off0, 0, s));
-      if (tile == kb)
-        colsum_update<true>(acc, col, p.scale_log2, lse2, (lane & 31) - 4 * (lane >> 5));
-      else
-        colsum_update<false>(acc, col, p.scale_log2, lse2, 0);
+      for (int s = 0; s < C::kSteps; ++s) mma_step<BF16, F16>(acc, lds_frag<C>(lds[wave][cur], off0, 0, s), kf[s]);
+      // lane: key lane % 32; register r: query row acc_row(r, lane), four neighbouring rows at a time
+      const float4* lse4 = (const float4*)&lse_tile[wave][cur][4 * (lane >> 5)];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 l4 = lse4[2 * g];
+        const float lse2[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[4 * g + i], p.scale_log2, -lse2[i]));
+          col[i] += tile != kb || acc_row(4 * g + i, lane) >= (lane & 31) ? e : 0.0f;
+        }
+      }
     }
   }
-  const float v = sum_over_lanes(col, lane);
-  if ((lane & 1) == 0) part[wave][acc_row((lane >> 1) & 15, lane)] = v;
+  const float half = (col[0] + col[1]) + (col[2] + col[3]);
+  const float v = half + __shfl_xor(half, 32);
+  if (lane < 32) part[wave][lane] = v;
   __syncthreads();
   if (tid < 32 && k0 + tid < S) {
     float acc = 0.0f;
