@@ -55,6 +55,34 @@ inline kvcrush_status allow_large_lds(int static_lds) {
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (KVC_WAVE - 1)); }
 
+// What the 64 lanes of a wave hold, combined by `op` (associative and commutative) and known to all of them.  The
+// moves are part of the operations (DPP) and cost no trip through LDS, which is what six __shfl_xor are: lane ^ 1 and
+// lane ^ 2, then the halves of eight and of sixteen mirrored, then lane 15 into the next sixteen and lane 31 into the
+// upper half; lane 63 ends up with everything.  `none` is op's neutral element.
+template <class Op>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v, uint32_t none, Op op) {
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));   // quad_perm [1, 0, 3, 2]
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));   // quad_perm [2, 3, 0, 1]
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));  // row_half_mirror
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));  // row_mirror
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, KVC_WAVE - 1);
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+  return wave_reduce(v, ~0u, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+}
+__device__ __forceinline__ float wave_max(float v) {
+  return __uint_as_float(wave_reduce(__float_as_uint(v), 0xFF800000u, [](uint32_t a, uint32_t b) {
+    return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+  }));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  return __uint_as_float(wave_reduce(__float_as_uint(v), 0u, [](uint32_t a, uint32_t b) {
+    return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+  }));
+}
+
 __device__ __forceinline__ uint64_t lanemask_lt() {
   return (1ull << lane_id()) - 1ull;
 }

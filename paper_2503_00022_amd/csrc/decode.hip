@@ -88,8 +88,7 @@ __device__ __forceinline__ void unpack(const vec16& x, float (&f)[BF16 ? 8 : 4])
 }
 
 __device__ __forceinline__ float block_max(float v, float* red) {
-#pragma unroll
-  for (int off = KVC_WAVE / 2; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+  v = kvc::wave_max(v);
   __syncthreads();  // `red` may still be read from the previous use
   if (kvc::lane_id() == 0) red[threadIdx.x / KVC_WAVE] = v;
   __syncthreads();
@@ -100,8 +99,7 @@ __device__ __forceinline__ float block_max(float v, float* red) {
 }
 
 __device__ __forceinline__ float block_sum(float v, float* red) {
-#pragma unroll
-  for (int off = KVC_WAVE / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  v = kvc::wave_sum(v);
   __syncthreads();
   if (kvc::lane_id() == 0) red[threadIdx.x / KVC_WAVE] = v;
   __syncthreads();
@@ -371,12 +369,8 @@ __global__ __launch_bounds__(kThreads) void append_update_kernel(AppendParams p)
         for (int u = 0; u < kAhead; ++u) l += ml[u].y * __builtin_amdgcn_exp2f(ml[u].x - mn);
         m = mn;
       }
-      float mt = m;
-#pragma unroll
-      for (int off = KVC_WAVE / 2; off > 0; off >>= 1) mt = fmaxf(mt, __shfl_xor(mt, off));
-      l *= __builtin_amdgcn_exp2f(m - mt);
-#pragma unroll
-      for (int off = KVC_WAVE / 2; off > 0; off >>= 1) l += __shfl_xor(l, off);
+      const float mt = kvc::wave_max(m);
+      l = kvc::wave_sum(l * __builtin_amdgcn_exp2f(m - mt));
       if (lane == 0) lse2[i] = mt + __builtin_amdgcn_logf(l);
     }
     __syncthreads();

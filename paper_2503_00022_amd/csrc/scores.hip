@@ -435,19 +435,15 @@ __global__ __launch_bounds__(kThreads, 2) void lse_kernel(ScoreParams p) {
 
 // lse of the rows whose keys were cut into slices: the slices' (reference, sum)
 // pairs stand for sum * 2^reference.  One wave per query row, lane s holds slice
-// s (there are at most 64); the sum over the slices is a fixed shuffle tree.
+// s (there are at most 64); the sum over the slices is a fixed tree.
 __global__ __launch_bounds__(256) void lse_combine_kernel(ScoreParams p) {
   const int lane = kvc::lane_id();
   const int r = blockIdx.x * (256 / KVC_WAVE) + threadIdx.x / KVC_WAVE, bh = blockIdx.y;  // bh = b * Hq + head
   if (r >= p.split_rows) return;
   float2 ml = make_float2(kNegBig, 0.0f);
   if (lane < p.n_split) ml = p.split_ml[((size_t)bh * p.n_split + lane) * p.split_rows + r];
-  float mt = ml.x;
-#pragma unroll
-  for (int off = KVC_WAVE / 2; off > 0; off >>= 1) mt = fmaxf(mt, __shfl_xor(mt, off));
-  float lt = ml.y * __builtin_amdgcn_exp2f(ml.x - mt);
-#pragma unroll
-  for (int off = KVC_WAVE / 2; off > 0; off >>= 1) lt += __shfl_xor(lt, off);
+  const float mt = kvc::wave_max(ml.x);
+  const float lt = kvc::wave_sum(ml.y * __builtin_amdgcn_exp2f(ml.x - mt));
   if (lane == 0) p.lse[(size_t)bh * p.S + p.split_q0 + r] = (mt + __builtin_amdgcn_logf(lt)) * kLn2;
 }
 

@@ -142,7 +142,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int* wave_tot) {
   __syncthreads();
   // (at most 16 waves: every wave scans the waves' totals itself, one per lane)
   const int tot_scan = wave_incl_scan(lane < n_waves ? wave_tot[lane] : 0);
-  const int before = __shfl(tot_scan - (lane < n_waves ? wave_tot[lane] : 0), wave);
+  const int before = __builtin_amdgcn_readlane(tot_scan - (lane < n_waves ? wave_tot[lane] : 0), __builtin_amdgcn_readfirstlane(wave));
   __syncthreads();
   return before + incl - v;
 }
@@ -691,6 +691,12 @@ __global__ __launch_bounds__(kGsThreads) void group_scatter_kernel(GroupParams p
 }
 
 // ------------------------------------------------------------------ K3 ----
+// The token of the wave's least (cost, token) pair; each lane brings one, cost in the upper half.
+__device__ __forceinline__ int nearest(unsigned long long pair) {
+  const uint32_t cost = (uint32_t)(pair >> 32), least = kvc::wave_min(cost);
+  return (int)kvc::wave_min(cost == least ? (uint32_t)pair : ~0u);
+}
+
 struct MedoidParams {
   const uint64_t* bits;   // as in GroupParams
   size_t bits_stride;
@@ -741,7 +747,7 @@ __global__ __launch_bounds__(kMedoidThreads) void medoid_kernel(MedoidParams p) 
       const uint64_t bw = (m < n && w < W) ? bits[(size_t)t * W + w] : 0ull;
       const int nb = min(64, Hs - 64 * w);
       for (int rr = 0; rr < nb; ++rr) {
-        const int c = __shfl(cnt[w], rr);
+        const int c = __builtin_amdgcn_readlane(cnt[w], rr);
         cost += ((bw >> rr) & 1ull) ? (unsigned)(n - c) : (unsigned)c;
       }
     }
@@ -750,13 +756,8 @@ __global__ __launch_bounds__(kMedoidThreads) void medoid_kernel(MedoidParams p) 
       best = key < best ? key : best;
     }
   }
-#pragma unroll
-  for (int off = KVC_WAVE / 2; off > 0; off >>= 1) {
-    const unsigned long long o = __shfl_xor(best, off);
-    best = o < best ? o : best;
-  }
+  const int t = nearest(best);
   if (lane == 0) {
-    const int t = (int)(best & 0xFFFFFFFFull);
     atomicOr((unsigned long long*)&p.repmask[(size_t)b * p.nw + (t >> 6)], 1ull << (t & 63));
   }
 }
@@ -804,7 +805,7 @@ __global__ __launch_bounds__(kMedoidThreads) void medoid_wide_kernel(MedoidParam
       const uint64_t bw = (m < n && w < W) ? bits[(size_t)t * W + w] : 0ull;
       const int nb = min(64, Hs - 64 * w);
       for (int rr = 0; rr < nb; ++rr) {
-        const int c = __shfl(cnt[o], rr);
+        const int c = __builtin_amdgcn_readlane(cnt[o], rr);
         cost += ((bw >> rr) & 1ull) ? (unsigned)(n - c) : (unsigned)c;
       }
     }
@@ -818,13 +819,8 @@ __global__ __launch_bounds__(kMedoidThreads) void medoid_wide_kernel(MedoidParam
     __syncthreads();
   }
   if (wave == 0) {
-#pragma unroll
-    for (int off = KVC_WAVE / 2; off > 0; off >>= 1) {
-      const unsigned long long o = __shfl_xor(best, off);
-      best = o < best ? o : best;
-    }
+    const int t = nearest(best);
     if (lane == 0) {
-      const int t = (int)(best & 0xFFFFFFFFull);
       atomicOr((unsigned long long*)&p.repmask[(size_t)b * p.nw + (t >> 6)], 1ull << (t & 63));
     }
   }
@@ -1339,7 +1335,7 @@ __global__ __launch_bounds__(kSelThreads) void medoid_emit_kernel(FastParams p) 
         const uint64_t bw = (m < n && w < W) ? bits[(size_t)t * W + w] : 0ull;
         const int nb = min(64, Hs - 64 * w);
         for (int rr = 0; rr < nb; ++rr) {
-          const int c = __shfl(cnt[w], rr);
+          const int c = __builtin_amdgcn_readlane(cnt[w], rr);
           cost += ((bw >> rr) & 1ull) ? (unsigned)(n - c) : (unsigned)c;
         }
       }
@@ -1348,13 +1344,8 @@ __global__ __launch_bounds__(kSelThreads) void medoid_emit_kernel(FastParams p) 
         best = key < best ? key : best;
       }
     }
-#pragma unroll
-    for (int off = KVC_WAVE / 2; off > 0; off >>= 1) {
-      const unsigned long long o = __shfl_xor(best, off);
-      best = o < best ? o : best;
-    }
+    const int t = nearest(best);
     if (lane == 0) {
-      const int t = (int)(best & 0xFFFFFFFFull);
       atomicOr((unsigned long long*)&p.repmask[(size_t)b * p.nw + (t >> 6)], 1ull << (t & 63));
     }
   }
@@ -1416,13 +1407,8 @@ __global__ __launch_bounds__(kSelThreads) void medoid_units_emit_kernel(MedoidPa
     __syncthreads();
   }
   if (sub == 0 && n > 0) {
-#pragma unroll
-    for (int off = KVC_WAVE / 2; off > 0; off >>= 1) {
-      const unsigned long long o = __shfl_xor(best, off);
-      best = o < best ? o : best;
-    }
+    const int t = nearest(best);
     if (lane == 0) {
-      const int t = (int)(best & 0xFFFFFFFFull);
       atomicOr((unsigned long long*)&p.repmask[(size_t)b * p.nw + (t >> 6)], 1ull << (t & 63));
     }
   }
