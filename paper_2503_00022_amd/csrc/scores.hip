@@ -957,9 +957,8 @@ double makespan(const Walk& w, double pair, double tail) {
 // leave compute units without one (medium prompts), they are a 384th of the launch's steps, but
 // not below 12.  Pass B alone in us, 72 steps -> this rule, bf16 with D = 128: S = 2048, 32 heads in
 // 8 groups 84 -> 44; S = 6000, 4 heads 73 -> 38; B = 8, S = 1024, 32 heads in 8 groups 84 -> 71.
-// A share between half a piece and a whole one gains nothing by the cut and pays for its second
-// prologue: S = 4096, 32 heads in 8 groups 175 uncut (both passes), 181 to 199 in pieces of 34 to 54
-// steps.  Nor does a cut pay where the whole pieces are resident together already: 64 score rows of
+// A share between half a piece and a whole one pays only where whole pieces leave the chip half
+// empty (below).  Nor does a cut pay where the whole pieces are resident together already: 64 score rows of
 // one head, S = 2048, are 512 pieces of up to 32 steps, 57 us, and 896 of up to 24, 66 us.
 constexpr int kPieceSteps = 72, kMinPieceSteps = 12, kPiecesWanted = 384;
 constexpr double kPiecePair = 1.1, kPieceTail = 0.6, kPieceMore = 2.2, kPieceCut = 1.0;  // in steps, fitted to
@@ -988,7 +987,17 @@ ColsumChoice plan_colsum(int tile, int heads_per_row, long long rows, int S, int
   };
   const ColsumChoice uncut = cut_at(kPieceSteps);
   const long long fair = seen * heads_per_row * rows / kPiecesWanted * tile / 64;
-  if (!fine || 2 * fair > kPieceSteps) return uncut;
+  if (!fine || fair > kPieceSteps) return uncut;
+  if (2 * fair > kPieceSteps) {
+    // Whole pieces that leave places of the chip empty while some units run two of them: cut for one piece a place,
+    // where that does not come to a round of a few more pieces than places behind a first round that had room (a
+    // tenth more; with 392 whole pieces and more it pays all the same).  Pass B, us, whole -> cut: S = 5564, 16 heads in
+    // 4 groups 120 -> 81 (272 -> 508 pieces); S = 4439, 32 in 8 118 -> 99 (368 -> 504); B = 3, S = 4472, 8 in 2, D = 64
+    // 94 -> 60 (276 -> 504).  Left whole: S = 4090, 32 in 8, 94, where 656 pieces take 102.
+    if (tile != 64 || uncut.walk.wgs >= kSlots) return uncut;
+    const ColsumChoice cut = cut_at((int)(seen * heads_per_row * rows / kSlots));
+    return cut.walk.wgs <= 1.1 * kSlots || uncut.walk.wgs >= 392 ? cut : uncut;
+  }
   const ColsumChoice cut = cut_at(std::max((int)fair, kMinPieceSteps));
   auto steps = [](const ColsumChoice& c) {
     return makespan(c.walk, kPiecePair, kPieceTail) + kPieceMore * (c.walk.per_unit() - 1) + (c.plan.n_chunks > 1 ? kPieceCut : 0);

@@ -569,6 +569,24 @@ def test_scores_of_medium_prompts(kv, oracle, B, Hq, Hkv, S, D, dtype, rg, windo
 EXTREME_TILED = [(32, 8, 2100, 128, "bf16"), (32, 8, 2100, 128, "f16"), (32, 8, 3300, 64, "bf16"), (32, 8, 3300, 64, "f16")]
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype,rg", [(3, 8, 2, 4472, 64, "bf16", True), (1, 12, 4, 6118, 128, "f16", False),
+                                                   (1, 32, 32, 4033, 128, "bf16", False), (1, 8, 8, 8129, 64, "bf16", True)])
+def test_scores_of_pieces_cut_and_turned(kv, oracle, B, Hq, Hkv, S, D, dtype, rg):
+    """Pass B cut for one piece a place of the chip, and launches of 449 to 512 workgroups whose second half runs in
+    turned order, ragged ends among them."""
+    say(f"pieces cut or turned B={B} Hq={Hq} Hkv={Hkv} S={S} D={D} {dtype} reduce_groups={rg}")
+    w = inputs.Workload("t", B, Hq, Hkv, S, D, dtype, max(1, S // 4), 0.5, "alternating", rg, sink_bias=True)
+    q, k, _ = inputs.make_qkv(w, S + Hq, want_v=False)
+    ref, ref_lse = oracle.scores(q, k, rg, want_lse=True, threads=THREADS)
+    bound = score_bound(q, k)
+    sc, ws = kv.kvcrush_scores(q.cuda(), k.cuda(), rg)
+    given, _ = kv.kvcrush_scores(q.cuda(), k.cuda(), rg, lse=ref_lse.cuda())
+    torch.cuda.synchronize()
+    lse_err = (kv.lse_from_workspace(ws, B, Hq, S).cpu().double() - ref_lse.double()).abs().max().item()
+    say(f"  scores off by {rel_err(sc, ref):.2e}, lse given {rel_err(given, ref):.2e}, bound {bound:.2e}; lse by {lse_err:.2e}")
+    assert rel_err(sc, ref) <= bound and rel_err(given, ref) <= bound and lse_err <= bound
+
+
 @pytest.mark.parametrize("Hq,Hkv,S,D,dtype", [(2, 1, 1500, 128, "bf16")] + EXTREME_TILED)
 def test_scores_extreme_logits(kv, oracle, Hq, Hkv, S, D, dtype):
     """Logits that grow by hundreds along the sequence: the exponentials'

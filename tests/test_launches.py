@@ -183,6 +183,23 @@ def test_pieces_of_the_column_sums(record, B, Hq, Hkv, S, rg, cut):
         assert [l.grid[0] for l in ran if "colsum_kernel" in l.kernel] == [rows * ((S + 255) // 256)]
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,rg,whole,cut", [
+    # pass B in us, whole pieces -> cut for one a place of the chip
+    (1, 16, 4, 5564, 128, 1, 272, 508),     # 120 -> 81
+    (1, 32, 8, 4439, 128, 1, 368, 504),     # 118 -> 99
+    (1, 8, 8, 8623, 128, 1, 416, 704),      # 107 -> 91
+    (1, 32, 8, 4090, 128, 1, 352, 352),     # 94: 656 pieces take 102
+    (1, 32, 32, 4096, 128, 0, 512, 512),    # every place taken by whole pieces
+])
+def test_pieces_fill_the_places_of_the_chip(record, B, Hq, Hkv, S, D, rg, whole, cut):
+    sh = kv.Shape(B, Hq, Hkv, S, D, 1, rg)
+    need = kv.kvcrush_scores_workspace(sh)
+    (st, ran), (st2, less) = record([L.scores(sh, lse=True, ws_bytes=need), L.scores(sh, lse=True, ws_bytes=need - 1)])
+    grid = lambda ls: [l.grid[0] for l in ls if "colsum_kernel" in l.kernel]
+    assert st == kv.OK and grid(ran) == [cut]
+    assert st2 == kv.ERR_WORKSPACE and not less if whole == cut else st2 == kv.OK and grid(less) == [whole]
+
+
 def test_the_sizes_of_the_tiled_tests_are_tiled(record):
     """test_gpu_parity.py's cases for the tiled kernels run those, whatever the rules become."""
     from test_gpu_parity import EXTREME_TILED, TILED_CASES
