@@ -130,12 +130,13 @@ class DecodeCache:
             self.evict()
         k, v, scores = self._sets[self._cur]
         # Rows that the library can read where they are go into the cache with the step's own kernels; others (views,
-        # other types, tensors that autograd follows) are copied first.  The two kernels of a step take about as long
-        # as Python takes for a dozen attribute reads and calls, so every property is looked at once, here.
+        # other types, tensors that autograd follows) are copied first, and so are those of a cache in host memory, whose
+        # addresses must not reach a kernel (kvcrush_scores_append refuses it).  The two kernels of a step take about as
+        # long as Python takes for a dozen attribute reads and calls, so every property is looked at once, here.
         dtype, device = k.dtype, k.device
         B, Hkv, _, D = k.shape
         rows, ptrs = (B, Hkv, D), (k_new.data_ptr(), v_new.data_ptr())
-        in_place = (ptrs[0] | ptrs[1]) % 16 == 0 and type(k_new) is type(v_new) is torch.Tensor \
+        in_place = device.type == "cuda" and (ptrs[0] | ptrs[1]) % 16 == 0 and type(k_new) is type(v_new) is torch.Tensor \
             and k_new.dtype == v_new.dtype == q_new.dtype == dtype and k_new.device == v_new.device == q_new.device == device \
             and k_new.shape == v_new.shape == rows and k_new.is_contiguous() and v_new.is_contiguous() \
             and not k_new.requires_grad and not v_new.requires_grad \

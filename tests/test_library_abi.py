@@ -317,6 +317,17 @@ def test_pipeline_classes_validate_before_touching_the_gpu(lib):
         lc.replay()
 
 
+def test_decode_cache_in_host_memory_is_refused(lib, monkeypatch):
+    """A cache and rows in host memory: an append raises, and no host address is handed to the library."""
+    import torch
+    from paper_2503_00022_amd import pipeline
+    monkeypatch.setattr(binding, "_decode_step", lambda *a, **kw: pytest.fail("host addresses given to the library"))
+    k = torch.zeros(1, 2, 8, 64, dtype=torch.bfloat16)
+    cache = pipeline.DecodeCache(k, k, torch.zeros(1, 2, 8), budget=4, n_important=2, capacity=16)
+    with pytest.raises(ValueError, match="GPU memory"):
+        cache.append(torch.zeros(1, 8, 64, dtype=torch.bfloat16), k[:, :, 0].contiguous(), k[:, :, 0].contiguous())
+
+
 def test_calibration_library_is_separate_from_the_product():
     """The benchmark's calibration kernel is built into a library of its own; the product library
     exports nothing of it."""
