@@ -1092,6 +1092,32 @@ def test_decode_step_is_append_after_the_copies(kv, B, Hq, Hkv, S, cap, D, dtype
                 assert torch.equal(c.scores[:, :, :S], want[:, :, :S])
 
 
+def decode_cache(n=40, cap=64, B=2, Hq=8, Hkv=2, D=128, seed=5):
+    """A decoding cache of n tokens on the GPU, what it was made of, and the rows of tokens to come."""
+    from paper_2503_00022_amd import pipeline
+    g = torch.Generator().manual_seed(seed)
+    mk = lambda *s: torch.randn(*s, generator=g).to(torch.bfloat16).cuda()
+    k, v, sc = mk(B, Hkv, n, D), mk(B, Hkv, n, D), torch.rand(B, Hkv, n, generator=g).cuda()
+    rows = [(mk(B, Hq, D), mk(B, Hkv, D), mk(B, Hkv, D)) for _ in range(4)]
+    return pipeline.DecodeCache(k, v, sc, 16, 8, cap), (k, v, sc), rows
+
+
+def test_refused_append_leaves_the_cache_as_long_as_it_was(kv):
+    """Queries at an odd address are refused; the next append gives what it gives without the refused one."""
+    say("append refused for its queries' address, then a valid one")
+    (refused, _, rows), (plain, _, _) = decode_cache(), decode_cache()
+    q, kn, vn = rows[0]
+    odd = torch.empty(q.numel() + 1, dtype=q.dtype, device="cuda")[1:].view(q.shape).copy_(q)
+    with pytest.raises(kv.KVCrushError):
+        refused.append(odd, *rows[1][1:])
+    assert refused.n == 40
+    assert refused.append(q, kn, vn) == plain.append(q, kn, vn) == 41
+    torch.cuda.synchronize()
+    for a, b in zip(refused._sets[refused._cur], plain._sets[plain._cur]):
+        assert torch.equal(a[:, :, :41], b[:, :, :41])
+    assert torch.equal(refused.k[:, :, 40], kn) and torch.equal(refused.v[:, :, 40], vn)
+
+
 def test_decode_steps_replay_from_a_hip_graph(kv, oracle):
     say("graph capture of a decoding step, replays at growing cache lengths need one graph per length")
     B, Hq, Hkv, D, cap = 2, 8, 2, 128, 512
