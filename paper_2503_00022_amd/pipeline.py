@@ -145,17 +145,18 @@ class DecodeCache:
             k[:, :, self.n].copy_(k_new)
             v[:, :, self.n].copy_(v_new)
         n = self.n + 1
-        if self._append_ws is None:
+        workspace = self._append_ws
+        if workspace is None:
             probe = kv.Shape(q_new.shape[0], q_new.shape[1], Hkv, self.capacity, q_new.shape[2], kv._dtype_code(q_new),
                              int(self.reduce_groups), 0, self.scale)
-            self._append_ws = torch.empty(max(kv.kvcrush_scores_append_workspace(probe, self.capacity), 16),
-                                          dtype=torch.uint8, device=q_new.device)
+            workspace = torch.empty(max(kv.kvcrush_scores_append_workspace(probe, self.capacity), 16), dtype=torch.uint8,
+                                    device=device)
         if in_place and scores.shape[1] == (Hkv if self.reduce_groups else q_new.shape[1]):
             shape = kv.Shape(B, q_new.shape[1], Hkv, n, D, kv._dtype_code(k), int(self.reduce_groups), 0, self.scale)
             kv._decode_step(shape, self.capacity, q_new.data_ptr(), *ptrs, k.data_ptr(), v.data_ptr(), scores.data_ptr(),
-                            self._append_ws)
+                            workspace)
         else:
-            kv.kvcrush_scores_append(q_new, k, scores, n, self.reduce_groups, workspace=self._append_ws,
+            kv.kvcrush_scores_append(q_new, k, scores, n, self.reduce_groups, workspace=workspace,
                                      scale=self.scale)
-        self.n = n  # (a refused call leaves the cache as long as it was)
+        self.n, self._append_ws = n, workspace  # (a refused call leaves the cache as long as it was, and no workspace)
         return n

@@ -326,7 +326,7 @@ def test_decode_cache_in_host_memory_is_refused(lib, monkeypatch):
     cache = pipeline.DecodeCache(k, k, torch.zeros(1, 2, 8), budget=4, n_important=2, capacity=16)
     with pytest.raises(ValueError, match="GPU memory"):
         cache.append(torch.zeros(1, 8, 64, dtype=torch.bfloat16), k[:, :, 0].contiguous(), k[:, :, 0].contiguous())
-    assert cache.n == 8                                    # no longer than before
+    assert cache.n == 8 and cache._append_ws is None       # no longer than before, and no workspace in host memory kept
 
 
 def test_calibration_library_is_separate_from_the_product():
