@@ -1118,6 +1118,18 @@ def test_refused_append_leaves_the_cache_as_long_as_it_was(kv):
     assert torch.equal(refused.k[:, :, 40], kn) and torch.equal(refused.v[:, :, 40], vn)
 
 
+def test_append_carries_forward_mode_tangents(kv):
+    """Rows with tangents are copied, so that the tangents arrive in the cache's tensors."""
+    say("append of dual rows")
+    from torch.autograd import forward_ad
+    cache, _, ((q, kn, vn), _, (_, tk, tv), _) = decode_cache()
+    with forward_ad.dual_level():
+        cache.append(q, forward_ad.make_dual(kn, tk), forward_ad.make_dual(vn, tv))
+        for t, row, tangent in ((cache.k, kn, tk), (cache.v, vn, tv)):
+            got = forward_ad.unpack_dual(t)
+            assert torch.equal(got.primal[:, :, 40], row) and torch.equal(got.tangent[:, :, 40], tangent)
+
+
 def test_decode_steps_replay_from_a_hip_graph(kv, oracle):
     say("graph capture of a decoding step, replays at growing cache lengths need one graph per length")
     B, Hq, Hkv, D, cap = 2, 8, 2, 128, 512
