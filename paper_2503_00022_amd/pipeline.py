@@ -141,6 +141,7 @@ class DecodeCache:
             and k_new.dtype == v_new.dtype == q_new.dtype == dtype and k_new.device == v_new.device == q_new.device == device \
             and k_new.shape == v_new.shape == rows and k_new.is_contiguous() and v_new.is_contiguous() \
             and not k_new.requires_grad and not v_new.requires_grad and forward_ad._current_level < 0 \
+            and not k.requires_grad and not v.requires_grad and (not k.is_inference() or torch.is_inference_mode_enabled()) \
             and q_new.dim() == 3 and q_new.shape[0] == B and q_new.shape[2] == D and q_new.is_contiguous()
         if not in_place:
             k[:, :, self.n].copy_(k_new)

@@ -1130,6 +1130,25 @@ def test_append_carries_forward_mode_tangents(kv):
             assert torch.equal(got.primal[:, :, 40], row) and torch.equal(got.tangent[:, :, 40], tangent)
 
 
+def test_append_to_a_cache_that_autograd_follows(kv):
+    """Once a row that requires grad is in the cache, plain rows are copied in as well, so that a slot's gradient goes to
+    the row that it holds; a cache made in inference mode is not written outside of it."""
+    say("append to caches that autograd follows, or refuses to have written")
+    cache, _, ((q, kn, vn), (q2, kn2, vn2), _, _) = decode_cache()
+    kn.requires_grad_()
+    cache.append(q, kn, vn)
+    cache.n = 40                                           # the slot is filled again
+    cache.append(q2, kn2, vn2)
+    cache.k[:, :, 40].float().sum().backward()
+    assert torch.equal(cache.k[:, :, 40].detach(), kn2) and (kn.grad is None or not kn.grad.any())
+    with torch.inference_mode():
+        cache, _, ((q, kn, vn), (q2, kn2, vn2), _, _) = decode_cache()
+        assert cache.append(q, kn, vn) == 41
+    with pytest.raises(RuntimeError, match="inference tensor"):
+        cache.append(q2, kn2, vn2)
+    assert cache.n == 41
+
+
 def test_decode_steps_replay_from_a_hip_graph(kv, oracle):
     say("graph capture of a decoding step, replays at growing cache lengths need one graph per length")
     B, Hq, Hkv, D, cap = 2, 8, 2, 128, 512
