@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import torch
 from torch.autograd import forward_ad
+from torch.autograd.graph import increment_version
 
 from . import binding as kv
 
@@ -157,6 +158,7 @@ class DecodeCache:
             shape = kv.Shape(B, q_new.shape[1], Hkv, n, D, kv._dtype_code(k), int(self.reduce_groups), 0, self.scale)
             kv._decode_step(shape, self.capacity, q_new.data_ptr(), *ptrs, k.data_ptr(), v.data_ptr(), scores.data_ptr(),
                             workspace)
+            increment_version((k, v))  # (as the copies do: a backward pass that saved the cache is to notice)
         else:
             kv.kvcrush_scores_append(q_new, k, scores, n, self.reduce_groups, workspace=workspace,
                                      scale=self.scale)

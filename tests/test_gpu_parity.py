@@ -1149,6 +1149,18 @@ def test_append_to_a_cache_that_autograd_follows(kv):
     assert cache.n == 41
 
 
+def test_append_is_seen_by_backward_passes(kv):
+    """A backward pass that saved the cache before an append raises, as after any write in place."""
+    say("append between forward and backward")
+    cache, _, ((q, kn, vn), _, _, _) = decode_cache()
+    x = torch.ones(1, device="cuda", dtype=torch.bfloat16, requires_grad=True)
+    for t in (lambda: cache.k, lambda: cache.v):
+        y = (x * t()).sum()
+        cache.append(q, kn, vn)
+        with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+            y.backward()
+
+
 def test_decode_steps_replay_from_a_hip_graph(kv, oracle):
     say("graph capture of a decoding step, replays at growing cache lengths need one graph per length")
     B, Hq, Hkv, D, cap = 2, 8, 2, 128, 512
