@@ -1142,8 +1142,10 @@ __global__ __launch_bounds__(kSelThreads) void row_select_kernel(FastParams p) {
     // leading digit: thread i owns bins 2047 - 2i and 2046 - 2i
     uint32_t c_hi = 0, c_lo = 0;
     if constexpr (OWN) {
-      if (row == Hs) {  // token importance: fp32 sum of the score rows, taken in row order
+      if (row == Hs) {  // token importance: fp32 sum of the score rows from zero, taken in row order
         int r = 1;
+#pragma unroll
+        for (int u = 0; u < KPT; ++u) v[u] = 0.0f + v[u];  // (makes a signalling NaN quiet, as every other route does)
         for (; r + 4 <= Hs; r += 4) {  // four rows' loads in flight
           float x[4][KPT];
 #pragma unroll

@@ -1603,6 +1603,19 @@ def test_select_at_the_edges_of_its_routes(kv, oracle, B, Hs, S, budget, n_imp, 
     check_select(kv, oracle, odd, budget, budget - sink - recent, kbit, anchor, seed=13, **ends)
 
 
+@pytest.mark.parametrize("S", [500, 1024, 4096, 8192, 9000, 40000])
+def test_select_ranks_sums_of_signalling_nans(kv, S):
+    """An importance is a sum, which is never a signalling NaN: with one score row, tokens rank as if every NaN had been
+    quiet, on each of the selection's routes."""
+    say(f"select on signalling NaNs S={S}")
+    raw = torch.rand(1, 1, S, generator=torch.Generator().manual_seed(S)).view(torch.int32)
+    raw[..., ::3] = 0x7F800001 + torch.arange(0, S, 3, dtype=torch.int32) % 5
+    raw[..., 1::3] = 0x7FC00000 + torch.arange(1, S, 3, dtype=torch.int32) % 3
+    quiet = torch.where((raw & 0x7FFFFFFF) > 0x7F800000, raw | 0x400000, raw)
+    got, want = [kv.kvcrush_select(x.cuda().view(torch.float32), S // 2, S // 2, 0, "mean", 3)[0].cpu() for x in (raw, quiet)]
+    assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("block,levels", [(64, 2), (64, 3), (128, 2), (32, 2), (1, 2)])
 def test_select_on_blocks_of_alternating_sizes(kv, oracle, block, levels):
     """Score rows made of blocks of tokens that alternate between a few magnitudes: the first radix
