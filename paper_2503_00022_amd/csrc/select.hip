@@ -1457,7 +1457,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))
   constexpr int kTokens = KPT * KVC_WAVE, kTpt = (kTokens + kSelThreads - 1) / kSelThreads;  // tokens a thread groups
   constexpr int kTable = (kTailMaxRows + 1) * KPT, kPer = (kTable + kSelThreads - 1) / kSelThreads;
   __shared__ float imp[ROWS ? kTokens : 1];
-  __shared__ uint64_t rm[kTailMaxRows + 1][KPT];  // row bitmaps; row Hs: important tokens
+  __shared__ __align__(8) uint32_t rm[kTailMaxRows + 1][2 * KPT];  // row bitmaps; row Hs: important tokens
   __shared__ int table[kTable];                  // grouped tokens per (distance, chunk), then their first ranks
   __shared__ uint32_t member_bits[kTokens];      // by rank in (distance, token) order
   __shared__ uint16_t member[kTokens];
@@ -1470,6 +1470,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))
   const int S = p.S, Hs = p.Hs;
   const float* __restrict__ sc = p.scores + (size_t)b * Hs * p.ld;
 
+  auto row_word = [&](int r, int c) { return (uint64_t)rm[r][2 * c + 1] << 32 | rm[r][2 * c]; };
   for (int i = tid; i < kTable; i += kSelThreads) table[i] = 0;
   for (int i = tid; i < p.Br; i += kSelThreads) best[i] = ~0u;
   if (tid < 2 * KPT) rep[tid] = 0;
@@ -1511,7 +1512,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))
     }
     __syncthreads();
 
-      for (; row <= Hs; row += kSelWaves) {
+    for (; row <= Hs; row += kSelWaves) {
       const int k = row < Hs ? p.kbit : p.n_important;
       uint32_t word_lo = 0, word_hi = 0;  // lane u ends up with the word of chunk u
       if (k == 0 || k == S) {
@@ -1568,12 +1569,17 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))
           if constexpr (KPT > 12) __builtin_amdgcn_sched_barrier(0);  // (all chunks' ballots at once do not fit the scalar registers)
         }
       }
-      if (lane < KPT) rm[row][lane] = (uint64_t)word_hi << 32 | word_lo;
+      if (lane < KPT) {
+        rm[row][2 * lane] = word_lo;
+        rm[row][2 * lane + 1] = word_hi;
+      }
     }
   } else {
     for (int i = tid; i < (Hs + 1) * KPT; i += kSelThreads) {
       const int r = i / KPT, c = i % KPT;
-      rm[r][c] = c < p.nw ? p.rowmask[((size_t)b * (Hs + 1) + r) * p.nw + c] : 0ull;
+      const uint64_t w = c < p.nw ? p.rowmask[((size_t)b * (Hs + 1) + r) * p.nw + c] : 0ull;
+      rm[r][2 * c] = (uint32_t)w;
+      rm[r][2 * c + 1] = (uint32_t)(w >> 32);
     }
   }
   __syncthreads();
@@ -1584,7 +1590,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))
       uint32_t a = 0;
       if (p.anchor_mode == KVCRUSH_ANCHOR_MEAN) {
         for (int r = 0; r < Hs; ++r) {
-          const int n = wave_sum(lane < KPT ? __popcll(rm[r][min(lane, KPT - 1)] & ~rm[Hs][min(lane, KPT - 1)]) : 0);
+          const int n = wave_sum(lane < KPT ? __popcll(row_word(r, min(lane, KPT - 1)) & ~row_word(Hs, min(lane, KPT - 1))) : 0);
           if (2 * n > p.N) a |= 1u << r;
         }
       } else if (p.anchor_mode == KVCRUSH_ANCHOR_RANDOM) {
@@ -1608,7 +1614,7 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))
       bits[i] = dist[i] = before[i] = 0;
       grouped[i] = false;
       if (c >= KPT) continue;  // uniform over the wave
-      const uint32_t* half = (const uint32_t*)&rm[0][c] + (lane >> 5);
+      const uint32_t* half = &rm[0][2 * c + (lane >> 5)];
       for (int r = 0; r < Hs; ++r) bits[i] |= ((half[r * 2 * KPT] >> (lane & 31)) & 1u) << r;
       dist[i] = (uint32_t)__popc(bits[i] ^ anchor);
       grouped[i] = t < S && !((half[Hs * 2 * KPT] >> (lane & 31)) & 1u);
@@ -1684,13 +1690,13 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))
     if (p.bits) p.bits[(size_t)b * p.S_full + t] = 0ull;
   }
   const uint64_t rep_c = lane < KPT ? ((uint64_t)rep[2 * (min(lane, KPT - 1)) + 1] << 32 | rep[2 * (min(lane, KPT - 1))]) : 0ull;
-  const int kept_c = lane < KPT ? __popcll(rm[Hs][min(lane, KPT - 1)] | rep_c) : 0;
+  const int kept_c = lane < KPT ? __popcll(row_word(Hs, min(lane, KPT - 1)) | rep_c) : 0;
   const int first_c = wave_incl_scan(kept_c) - kept_c;  // lane u: kept tokens before chunk u
 #pragma unroll
   for (int i = 0; i < kTpt; ++i) {
     const int c = i * kSelWaves + wave;
     if (c >= KPT) break;
-    const uint64_t reps = (uint64_t)rep[2 * c + 1] << 32 | rep[2 * c], kept = rm[Hs][c] | reps;
+    const uint64_t reps = (uint64_t)rep[2 * c + 1] << 32 | rep[2 * c], kept = row_word(Hs, c) | reps;
     const int o = __builtin_amdgcn_readlane(first_c, c) + __popcll(kept & lanemask_lt());
     if (((kept >> lane) & 1ull) && o < p.budget) {
       idx_out[p.n_sink + o] = c * KVC_WAVE + lane + p.n_sink;
