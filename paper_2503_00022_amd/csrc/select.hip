@@ -747,7 +747,7 @@ __global__ __launch_bounds__(kMedoidThreads) void medoid_kernel(MedoidParams p) 
       const uint64_t bw = (m < n && w < W) ? bits[(size_t)t * W + w] : 0ull;
       const int nb = min(64, Hs - 64 * w);
       for (int rr = 0; rr < nb; ++rr) {
-        const int c = __builtin_amdgcn_readlane(cnt[w], rr);
+        const int c = __shfl(cnt[w], rr);
         cost += ((bw >> rr) & 1ull) ? (unsigned)(n - c) : (unsigned)c;
       }
     }
@@ -805,7 +805,7 @@ __global__ __launch_bounds__(kMedoidThreads) void medoid_wide_kernel(MedoidParam
       const uint64_t bw = (m < n && w < W) ? bits[(size_t)t * W + w] : 0ull;
       const int nb = min(64, Hs - 64 * w);
       for (int rr = 0; rr < nb; ++rr) {
-        const int c = __builtin_amdgcn_readlane(cnt[o], rr);
+        const int c = __shfl(cnt[o], rr);
         cost += ((bw >> rr) & 1ull) ? (unsigned)(n - c) : (unsigned)c;
       }
     }
@@ -1299,7 +1299,10 @@ __global__ __launch_bounds__(kSelThreads) void row_select_kernel(FastParams p) {
 }
 
 // F3: representatives (one wave per bucket, as medoid_kernel), then the index list by the
-// workgroup that finishes the sequence's last bucket.
+// workgroup that finishes the sequence's last bucket.  With many small buckets of long vectors it is bound by the vector
+// instructions of the two loops over the bits.  The counts are handed round by shuffles, which LDS carries out beside
+// them; v_readlane is one more of them: 118 sequences of 1852 tokens, 128 rows, no important tokens 774 -> 729 us as a
+// whole call; 16 of 12000, 32 rows 219 -> 211; 16384 tokens, 8 rows, buckets of 13 30.1 either way.
 __global__ __launch_bounds__(kSelThreads) void medoid_emit_kernel(FastParams p) {
   __shared__ EmitScratch sh;
   __shared__ uint32_t sh_last;
@@ -1337,7 +1340,7 @@ __global__ __launch_bounds__(kSelThreads) void medoid_emit_kernel(FastParams p) 
         const uint64_t bw = (m < n && w < W) ? bits[(size_t)t * W + w] : 0ull;
         const int nb = min(64, Hs - 64 * w);
         for (int rr = 0; rr < nb; ++rr) {
-          const int c = __builtin_amdgcn_readlane(cnt[w], rr);
+          const int c = __shfl(cnt[w], rr);
           cost += ((bw >> rr) & 1ull) ? (unsigned)(n - c) : (unsigned)c;
         }
       }
