@@ -83,6 +83,13 @@ __device__ __forceinline__ float wave_sum(float v) {
   }));
 }
 
+// Between what some lanes of a wave store in LDS and what other lanes of it read there.  A wave's LDS accesses are
+// carried out in order, so this costs no instruction; it keeps the compiler, which sees one lane, from reordering them.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ uint64_t lanemask_lt() {
   return (1ull << lane_id()) - 1ull;
 }

@@ -869,6 +869,7 @@ __global__ __launch_bounds__((kShortWaves<Cfg<BF16, D>>) * KVC_WAVE) void colsum
       const int tile = kb + t, qi = tile * 32 + (lane & 31);
       wait_own_tile();
       if (lane < 32) lse_tile[wave][cur][lane] = qi < S ? raw * kLog2e : INFINITY;  // rows past the end contribute nothing
+      kvc::wave_fence();
       t += W;
       if (pair + W < n_pairs) fetch(cur ^ 1);
       f32x16 acc;
