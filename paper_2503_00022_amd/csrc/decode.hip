@@ -257,6 +257,7 @@ __global__ __launch_bounds__(kMfmaWaves * KVC_WAVE, 4) void append_logits_mfma_k
     if (lane < C::kChunksPerRow)
       *(vec16*)(lds[wave] + lds_chunk_offset<C>(S - 1 - row0, lane)) =
           *(const vec16*)(p.k_new + (size_t)bg * C::kRowBytes + lane * 16);
+    kvc::wave_fence();
     store_new_token(p, bg, S, lane, C::kRowBytes);
   }
 
