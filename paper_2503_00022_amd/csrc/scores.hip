@@ -952,15 +952,28 @@ double makespan(const Walk& w, double pair, double tail) {
   return (1 - w.uneven()) * alike + w.uneven() * (w.total * pair / kSlots + tail * w.longest);
 }
 
+// Order of a launch's workgroups.  A unit gets workgroup i and, where there are that many, workgroup i + 256: of
+// pieces that fall evenly from the heaviest to the lightest, the heaviest two a unit can get and the lightest two.
+// With the second 256 turned round every pair has the same sum.  S = 4096, 32 heads, 512 workgroups of 0 to 60
+// tiles: pass A 84.8 -> 74.9 us, pass B 88.6 -> 82.9; S = 8192, 8 heads: pass A 95.6 -> 84.5.  With fewer than seven
+// eighths of the slots taken or some tiles only there is nothing to gain (S = 1309, 64 heads, 384 workgroups of up to
+// 20 tiles: 28.8 turned round, 29.8).
+// Returns the first piece of the second 256 workgroups, or `pieces` where the order stays as it is.
+// falling: whether the pieces are in the order of their lengths.
+int turned_from(long long pieces, int n_bh, int q_first, double longest, bool falling) {
+  const long long n = pieces * n_bh;
+  return falling && q_first == 0 && longest >= 24 && 8 * n >= 7 * kSlots && n <= kSlots ? (kUnits + n_bh - 1) / n_bh : (int)pieces;
+}
+
 // Pass-B work pieces run about 72 tile steps each (query tiles x the heads a piece walks): 18
 // tiles of 64 queries when a score row sums a KV group of four query heads, 72 when it is one
 // head.  The count is a multiple of three (the loop's unroll).  Where pieces of that length would
 // leave compute units without one (medium prompts), they are a 384th of the launch's steps, but
 // not below 12.  Pass B alone in us, 72 steps -> this rule, bf16 with D = 128: S = 2048, 32 heads in
 // 8 groups 84 -> 44; S = 6000, 4 heads 73 -> 38; B = 8, S = 1024, 32 heads in 8 groups 84 -> 71.
-// A share between half a piece and a whole one pays only where whole pieces leave the chip half
-// empty (below).  Nor does a cut pay where the whole pieces are resident together already: 64 score rows of
-// one head, S = 2048, are 512 pieces of up to 32 steps, 57 us, and 896 of up to 24, 66 us.
+// A share between half a piece and a whole one may pay where the whole pieces leave some of the chip's 512 places empty
+// (below).  A cut does not pay where they are resident together already: 64 score rows of one head, S = 2048, are 512
+// pieces of up to 32 steps, 57 us, and 896 of up to 24, 66 us.
 constexpr int kPieceSteps = 72, kMinPieceSteps = 12, kPiecesWanted = 384;
 constexpr double kPiecePair = 1.1, kPieceTail = 0.6, kPieceMore = 2.2, kPieceCut = 1.0;  // in steps, fitted to
 // whole and cut times of 1518 shapes (S 300 to 16000, 4 to 256 heads, windows): the cut is nowhere the slower one by 2 %
@@ -969,6 +982,40 @@ struct ColsumChoice {
   ColsumPlan plan;
   Walk walk;  // steps in tiles of the query axis
 };
+
+// How long a launch of up to kWalkedMost pieces runs, in steps: its pieces walked through the chip's places.  The
+// hardware deals workgroups round 32 shader engines of eight units (eight dies of four), two places a unit; an engine's
+// first sixteen take a place each, unit by unit, every further one the place that is free first.  A piece costs its
+// steps, those on the diagonal twice, and kPieceStart; two that share a unit run at kSharedRate each.
+constexpr int kEngines = 32, kPlaces = kSlots / kEngines, kWalkedMost = kSlots * 21 / 16;
+constexpr float kPieceStart = 4.0f, kSharedRate = 0.6f;
+double walked(const ColsumChoice& c, int heads_per_row, long long rows, int n_tiles, int q_first, int tile0, int tpk) {
+  float length[kWalkedMost];
+  int n = 0;
+  for (int chunk = 0; chunk < c.plan.n_chunks; ++chunk) {
+    const int first = tile0 + chunk * c.plan.chunk_tiles, end = std::min(n_tiles, first + c.plan.chunk_tiles);
+    for (int kb = 0; kb < c.plan.n_kb && kb * tpk < end && n < kWalkedMost; ++kb) {
+      const int t0 = std::max(first, kb * tpk), diagonal = std::max(0, std::min(end, (kb + 1) * tpk) - t0);
+      length[n++] = (float)((end - t0 + diagonal) * heads_per_row) + kPieceStart;
+    }
+  }
+  const int turn = turned_from(n, (int)rows, q_first, c.walk.longest, c.plan.n_chunks == 1);
+  float busy[kEngines][kPlaces] = {};
+  for (int piece = 0, i = 0; piece < n; ++piece) {
+    const float steps = length[piece >= turn ? turn + n - 1 - piece : piece];
+    for (int r = 0; r < rows; ++r, ++i) {
+      float* place = busy[i % kEngines];
+      *(i < kSlots ? place + i / kEngines : std::min_element(place, place + kPlaces)) += steps;
+    }
+  }
+  float last = 0;
+  for (const auto& place : busy)
+    for (int u = 0; u < kPlaces / 2; ++u) {
+      const float a = std::min(place[u], place[u + kPlaces / 2]), b = std::max(place[u], place[u + kPlaces / 2]);
+      last = std::max(last, a / kSharedRate + (b - a));
+    }
+  return last;
+}
 
 // fine: false where the scratch memory at hand only holds the partial sums of whole pieces.
 ColsumChoice plan_colsum(int tile, int heads_per_row, long long rows, int S, int q_first, bool fine) {
@@ -990,14 +1037,22 @@ ColsumChoice plan_colsum(int tile, int heads_per_row, long long rows, int S, int
   const long long fair = seen * heads_per_row * rows / kPiecesWanted * tile / 64;
   if (!fine || fair > kPieceSteps) return uncut;
   if (2 * fair > kPieceSteps) {
-    // Whole pieces that leave places of the chip empty while some units run two of them: cut for one piece a place,
-    // where that does not come to a round of a few more pieces than places behind a first round that had room (a
-    // tenth more; with 392 whole pieces and more it pays all the same).  Pass B, us, whole -> cut: S = 5564, 16 heads in
-    // 4 groups 120 -> 81 (272 -> 508 pieces); S = 4439, 32 in 8 118 -> 99 (368 -> 504); B = 3, S = 4472, 8 in 2, D = 64
-    // 94 -> 60 (276 -> 504).  Left whole: S = 4090, 32 in 8, 94, where 656 pieces take 102.
+    // Whole pieces that leave places of the chip empty while some units run two of them: cut for one piece a place.
+    // The diagonal's pieces and the rounding to three tiles make it more or fewer than 512.  From 400 to 512, and from
+    // about 1.3 rounds on, the cut is the faster one (506 of 532 such shapes; 7 % slower at most).  A few more pieces than
+    // places may run alone behind a first round that had room, and few pieces may be hardly shorter than whole ones:
+    // there the walk above decides, for whole pieces if it is close.  Fitted at 1331 shapes (1 to 72 score rows of up to
+    // eight heads, S 1460 to 16350): the choice takes 0.883 of whole pieces' time, on average, the faster of the two 0.879,
+    // cutting always 0.888; it is the slower one by more than 2 % at 48 of them, by 13 % at most.  864 others came out
+    // alike; 336 with windows take 0.934 of whole pieces' time and are slower by more than 2 % at 52, by 16 % at most.
+    // Pass B, us, whole -> cut: S = 5564, 16 heads in 4 groups 120 -> 81 (272 -> 508 pieces); S = 4439, 32 in 8 118 -> 100
+    // (368 -> 504); B = 3, S = 4472, 8 in 2, D = 64 94 -> 60 (276 -> 504); S = 7720, 8 heads 93 -> 75 (392 -> 856).  Left
+    // whole: S = 5145, 20 in 5, 99 (335), where 525 pieces take 113; S = 4003, 32 in 8, 93 (352), where 528 take 103.
     if (tile != 64 || uncut.walk.wgs >= kSlots) return uncut;
     const ColsumChoice cut = cut_at((int)(seen * heads_per_row * rows / kSlots));
-    return cut.walk.wgs <= 1.1 * kSlots || uncut.walk.wgs >= 392 ? cut : uncut;
+    if (cut.walk.wgs > kWalkedMost || (cut.walk.wgs >= 400 && cut.walk.wgs <= kSlots)) return cut;
+    auto steps = [&](const ColsumChoice& c) { return walked(c, heads_per_row, rows, (int)n_tiles, q_first, (int)tile0, (int)tpk); };
+    return steps(cut) < 0.93 * steps(uncut) ? cut : uncut;
   }
   const ColsumChoice cut = cut_at(std::max((int)fair, kMinPieceSteps));
   auto steps = [](const ColsumChoice& c) {
@@ -1070,18 +1125,9 @@ LsePlan lse_plan(int B, int Hq, int Hkv, int S, bool bf16, int q_first, bool may
   return pl;
 }
 
-// Order of a launch's workgroups.  A unit gets workgroup i and, where there are that many, workgroup i + 256: of
-// pieces that fall evenly from the heaviest to the lightest, the heaviest two a unit can get and the lightest two.
-// With the second 256 turned round every pair has the same sum.  S = 4096, 32 heads, 512 workgroups of 0 to 60
-// tiles: pass A 84.8 -> 74.9 us, pass B 88.6 -> 82.9; S = 8192, 8 heads: pass A 95.6 -> 84.5.  With fewer than seven
-// eighths of the slots taken or some tiles only there is nothing to gain (S = 1309, 64 heads, 384 workgroups of up to
-// 20 tiles: 28.8 turned round, 29.8).
-// falling: whether the pieces are in the order of their lengths.
 void launch_order(ScoreParams& p, long long pieces, double longest, bool falling) {
-  const long long n = pieces * p.n_bh;
   p.n_pieces = (int)pieces;
-  p.turn = falling && p.q_first == 0 && longest >= 24 && 8 * n >= 7 * kSlots && n <= kSlots ? (kUnits + p.n_bh - 1) / p.n_bh
-                                                                                         : (int)pieces;
+  p.turn = turned_from(pieces, p.n_bh, p.q_first, longest, falling);
 }
 
 size_t split_bytes(const LsePlan& pl, int B, int Hq) {
@@ -1214,7 +1260,7 @@ kvcrush_status launch_scores(const ScoreParams& base, const float* lse_user, flo
   using C = Cfg<BF16, D>;
   ScoreParams p = base;
   const long long rows = (long long)p.B * (p.reduce_groups ? p.Hkv : p.Hq);
-  const ColsumChoice choice = plan_colsum(C::kTile, p.reduce_groups ? p.G : 1, rows, p.S, p.q_first, fine);
+  const ColsumChoice choice = plan_colsum(C::kTile, p.reduce_groups ? p.G : 1, rows, p.S, p.q_first, fine && !lse_only);
   const ColsumPlan& pl = choice.plan;
   if (!lse_only && pl.pieces * rows > kMaxGridX) return KVCRUSH_ERR_UNSUPPORTED;  // before anything is enqueued
   if (!lse_user) {

@@ -189,6 +189,11 @@ def test_pieces_of_the_column_sums(record, B, Hq, Hkv, S, rg, cut):
     (1, 32, 8, 4439, 128, 1, 368, 504),     # 118 -> 99
     (1, 8, 8, 8623, 128, 1, 416, 704),      # 107 -> 91
     (1, 32, 8, 4090, 128, 1, 352, 352),     # 94: 656 pieces take 102
+    (1, 20, 5, 5145, 128, 1, 335, 335),     # 99: 525 take 113
+    (1, 32, 8, 4003, 128, 1, 352, 352),     # 93: 528 take 103
+    (1, 24, 3, 4286, 128, 1, 249, 249),     # 100: 357 take 109
+    (1, 4, 4, 10880, 128, 1, 388, 628),     # 80 -> 74
+    (1, 8, 8, 7720, 128, 1, 392, 856),      # 93 -> 75
     (1, 32, 32, 4096, 128, 0, 512, 512),    # every place taken by whole pieces
 ])
 def test_pieces_fill_the_places_of_the_chip(record, B, Hq, Hkv, S, D, rg, whole, cut):
