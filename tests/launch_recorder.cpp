@@ -1,5 +1,5 @@
 // The HIP runtime calls of libkvcrush.so, replaced for a process without a GPU: launches are written
-// down (kernel, grid, block, dynamic LDS) instead of run.  Loaded with RTLD_GLOBAL before the library,
+// down (kernel, grid, block, dynamic LDS, and of a score kernel's parameters S, n_bh, n_pieces and turn) instead of run.  Loaded with RTLD_GLOBAL before the library,
 // so that the library's references find these definitions first.
 #include <cstddef>
 #include <cstdint>
@@ -38,10 +38,16 @@ int hipGetSymbolAddress(void** ptr, const void*) {
 }
 // As the runtime does: a launch of 2^32 threads or more along a dimension, an empty one, or one with too
 // many workgroups along y or z is refused.
-int hipLaunchKernel(const void* host, Dim3 grid, Dim3 block, void**, size_t lds, void*) {
+int hipLaunchKernel(const void* host, Dim3 grid, Dim3 block, void** args, size_t lds, void*) {
   const bool refused = !grid.x || !grid.y || !grid.z || (uint64_t)grid.x * block.x > 0xFFFFFFFFull || grid.y > 65535 || grid.z > 65535;
   char line[256];
-  snprintf(line, sizeof line, " %u %u %u %u %zu %d\n", grid.x, grid.y, grid.z, block.x, lds, refused ? 1 : 0);
+  const int n = snprintf(line, sizeof line, " %u %u %u %u %zu %d", grid.x, grid.y, grid.z, block.x, lds, refused ? 1 : 0);
+  if (kernels()[host].find("ScoreParams") != std::string::npos) {
+    const int32_t* p = (const int32_t*)((const char*)args[0] + 88);  // B, Hq, Hkv, S, G, reduce_groups, heads_per_wg, n_blocks, ...
+    snprintf(line + n, sizeof line - n, " %d %d %d %d\n", p[3], p[8], p[9], p[10]);
+  } else {
+    snprintf(line + n, sizeof line - n, "\n");
+  }
   log_text += kernels()[host] + line;
   return refused ? 9 : 0;
 }

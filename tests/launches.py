@@ -9,7 +9,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 FAKE, FAKE2 = 0x10000000, 0x70000000000      # aligned addresses, never dereferenced
-Launch = collections.namedtuple("Launch", "kernel grid block lds")
+Launch = collections.namedtuple("Launch", "kernel grid block lds order")    # order: S, n_bh, n_pieces, turn of the score kernels
 
 
 def build_recorder(folder):
@@ -44,7 +44,7 @@ def record(recorder, lib_path, calls):
     """[(status, [Launch, ...]), ...] of the calls made with the functions above."""
     out = subprocess.run([sys.executable, os.path.abspath(__file__), recorder, lib_path], input=json.dumps(calls), text=True,
                          check=True, capture_output=True).stdout
-    return [(st, [Launch(k, tuple(g), b, lds) for k, g, b, lds in ls]) for st, ls in json.loads(out)]
+    return [(st, [Launch(k, tuple(g), b, lds, tuple(o)) for k, g, b, lds, o in ls]) for st, ls in json.loads(out)]
 
 
 def _child(recorder, lib_path):
@@ -59,8 +59,8 @@ def _child(recorder, lib_path):
         st = getattr(lib, name)(*[buf if a == "struct" else ctypes.c_uint64(a) for a in args])
         launches = []
         for line in rec.recorded().decode().splitlines():
-            kernel, gx, gy, gz, bx, lds, _ = line.split()
-            launches.append([kernel, [int(gx), int(gy), int(gz)], int(bx), int(lds)])
+            kernel, gx, gy, gz, bx, lds, _, *order = line.split()
+            launches.append([kernel, [int(gx), int(gy), int(gz)], int(bx), int(lds), [int(x) for x in order]])
         result.append([st, launches])
     json.dump(result, sys.stdout)
 

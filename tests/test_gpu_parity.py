@@ -570,9 +570,10 @@ EXTREME_TILED = [(32, 8, 2100, 128, "bf16"), (32, 8, 2100, 128, "f16"), (32, 8, 
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype,rg", [(3, 8, 2, 4472, 64, "bf16", True), (1, 12, 4, 6118, 128, "f16", False),
-                                                   (1, 32, 32, 4033, 128, "bf16", False), (1, 8, 8, 8129, 64, "bf16", True)])
+                                                   (1, 32, 32, 4033, 128, "bf16", False), (1, 8, 8, 8129, 64, "bf16", True),
+                                                   (1, 37, 37, 3300, 128, "bf16", False)])   # 37 does not divide 256
 def test_scores_of_pieces_cut_and_turned(kv, oracle, B, Hq, Hkv, S, D, dtype, rg):
-    """Pass B cut for one piece a place of the chip, and launches of 449 to 512 workgroups whose second half runs in
+    """Pass B cut for one piece a place of the chip, and launches of 448 to 512 workgroups whose second half runs in
     turned order, ragged ends among them."""
     say(f"pieces cut or turned B={B} Hq={Hq} Hkv={Hkv} S={S} D={D} {dtype} reduce_groups={rg}")
     w = inputs.Workload("t", B, Hq, Hkv, S, D, dtype, max(1, S // 4), 0.5, "alternating", rg, sink_bias=True)

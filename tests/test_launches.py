@@ -90,6 +90,7 @@ def test_units_on_the_static_scratch_array(record):
     (256, 8, 2048, 512, 300, ["select_one_kernel"]),                      # 99.6 / 36.6 / 24.0
     (1, 8, 4096, 1024, 512, ["row_select_kernel", "select_one_kernel"]),  # 24.9 / 17.3
     (1, 8, 512, 128, 128, ["select_one_kernel"]), (1, 32, 4096, 99, 99, ["row_select_kernel"]),  # the important tokens alone
+    (1, 16, 8192, 99, 99, ["row_select_kernel"]), (1, 32, 8192, 99, 99, ["slice_hist_kernel", "row_select_kernel"]),
     (1, 4, 1300, 20, 10, ["row_select_kernel"] + 2 * ["group"] + ["medoid_emit_kernel"]),        # buckets of 129
     (1, 8, 8192, 2048, 1500, ["row_select_kernel"] + 2 * ["group"] + ["medoid_emit_kernel"]),    # 26.6, 24.4 without slices
     (1, 32, 8192, 2048, 1500, ["slice_hist_kernel", "row_select_kernel"] + 2 * ["group"] + ["medoid_emit_kernel"]),  # 35.7, 37.4
@@ -203,6 +204,27 @@ def test_pieces_fill_the_places_of_the_chip(record, B, Hq, Hkv, S, D, rg, whole,
     grid = lambda ls: [l.grid[0] for l in ls if "colsum_kernel" in l.kernel]
     assert st == kv.OK and grid(ran) == [cut]
     assert st2 == kv.ERR_WORKSPACE and not less if whole == cut else st2 == kv.OK and grid(less) == [whole]
+
+
+@pytest.mark.parametrize("B,H,S,window,wgs,lse_turn,colsum_turn", [
+    # a score row a head: workgroups of pass A, and the first piece of each row that runs in turned order (None: none)
+    (1, 32, 3584, 0, 448, 8, None), (1, 32, 4096, 0, 512, 8, 8), (1, 32, 4097, 0, 544, None, None),
+    (1, 3, 38100, 0, 447, None, None), (1, 37, 3300, 0, 481, 7, 7), (3, 8, 5100, 0, 480, 11, None),
+    (3, 27, 1500, 0, 486, None, 4),           # 24 tiles are the least: 20 before the last block, 24 to the whole sequence
+    (1, 32, 4096, 4000, 512, None, None),     # a window's pieces do not fall evenly
+])
+def test_order_of_the_workgroups(record, B, H, S, window, wgs, lse_turn, colsum_turn):
+    """Launches of 448 to 512 workgroups of falling lengths start the second 256 in turned order, from the first piece
+    that lies wholly behind them."""
+    sh = kv.Shape(B, H, H, S, 128, 1, 0, window)
+    (st, lse), (st2, ran) = record([L.row_lse(sh, 0), L.scores(sh, lse=True)])
+    assert st == st2 == kv.OK and lse[0].grid[0] == wgs
+    for launch, turn in ((lse[0], lse_turn), (ran[0], colsum_turn)):
+        length, n_bh, n_pieces, got = launch.order
+        assert (length, n_bh, n_pieces * n_bh) == (S, B * H, launch.grid[0])
+        assert got == (n_pieces if turn is None else turn)
+        if turn is not None:
+            assert (turn - 1) * n_bh < 256 <= turn * n_bh
 
 
 def test_the_sizes_of_the_tiled_tests_are_tiled(record):
