@@ -137,25 +137,25 @@ class DecodeCache:
         # long as Python takes for a dozen attribute reads and calls, so every property is looked at once, here.
         dtype, device = k.dtype, k.device
         B, Hkv, _, D = k.shape
-        rows, ptrs = (B, Hkv, D), (k_new.data_ptr(), v_new.data_ptr())
-        in_place = device.type == "cuda" and (ptrs[0] | ptrs[1]) % 16 == 0 and type(k_new) is type(v_new) is torch.Tensor \
+        rows, q_shape, ptrs = (B, Hkv, D), q_new.shape, (k_new.data_ptr(), v_new.data_ptr())
+        in_place = k.is_cuda and (ptrs[0] | ptrs[1]) % 16 == 0 and type(k_new) is type(v_new) is torch.Tensor \
             and k_new.dtype == v_new.dtype == q_new.dtype == dtype and k_new.device == v_new.device == q_new.device == device \
             and k_new.shape == v_new.shape == rows and k_new.is_contiguous() and v_new.is_contiguous() \
             and not k_new.requires_grad and not v_new.requires_grad and forward_ad._current_level < 0 \
             and not k.requires_grad and not v.requires_grad and (not k.is_inference() or torch.is_inference_mode_enabled()) \
-            and q_new.dim() == 3 and q_new.shape[0] == B and q_new.shape[2] == D and q_new.is_contiguous()
+            and len(q_shape) == 3 and q_shape[0] == B and q_shape[2] == D and q_new.is_contiguous()
         if not in_place:
             k[:, :, self.n].copy_(k_new)
             v[:, :, self.n].copy_(v_new)
         n = self.n + 1
         workspace = self._append_ws
         if workspace is None:
-            probe = kv.Shape(q_new.shape[0], q_new.shape[1], Hkv, self.capacity, q_new.shape[2], kv._dtype_code(q_new),
+            probe = kv.Shape(q_shape[0], q_shape[1], Hkv, self.capacity, q_shape[2], kv._dtype_code(q_new),
                              int(self.reduce_groups), 0, self.scale)
             workspace = torch.empty(max(kv.kvcrush_scores_append_workspace(probe, self.capacity), 16), dtype=torch.uint8,
                                     device=device)
-        if in_place and scores.shape[1] == (Hkv if self.reduce_groups else q_new.shape[1]):
-            shape = kv.Shape(B, q_new.shape[1], Hkv, n, D, kv._dtype_code(k), int(self.reduce_groups), 0, self.scale)
+        if in_place and scores.shape[1] == (Hkv if self.reduce_groups else q_shape[1]):
+            shape = kv.Shape(B, q_shape[1], Hkv, n, D, kv._dtype_code(k), int(self.reduce_groups), 0, self.scale)
             kv._decode_step(shape, self.capacity, q_new.data_ptr(), *ptrs, k.data_ptr(), v.data_ptr(), scores.data_ptr(),
                             workspace)
             increment_version((k, v))  # (as the copies do: a backward pass that saved the cache is to notice)
