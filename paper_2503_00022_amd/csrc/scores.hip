@@ -1161,9 +1161,13 @@ kvcrush_status launch_lse(const ScoreParams& base, float2* split_ml, hipStream_t
 // workgroups a unit win where there are many, which may as well be many short prompts as few long ones.  The
 // times are linear in the rounds of workgroups and in the steps a unit walks; `lone` is what a step costs a
 // workgroup alone on its unit, in steps of one in company.  Fitted, in us, to both kernels' times at 439 shapes a
-// row (S 16 to 7000, 4 to 4096 heads): the choice is more than 5 % off the faster at 0 to 20 of them.  Measured,
-// tiled / short: pass A, S = 512, 8 heads, fp32 43 / 10; pass B, B = 2, S = 700, 8 heads in 2 groups 32 / 17; 32
-// heads a row each, B = 32, S = 128 19 / 40 (A) and 29 / 87 (B); 4 heads, fp32, S = 3000 397 / 68 and 122 / 72.
+// row (S 16 to 7000, 4 to 4096 heads), pass B's when its kernels still closed with exchanges through LDS.  With pass A's
+// kernels the choice is more than 5 % off the faster at 4 to 54 of them, by 43 % at most (5 us against 4).  Pass B's have
+// become faster since, the short one by up to half, and the choice is more than 5 % off at 10 to 90 of them, by 58 % at
+// most, mostly where it takes the tiled kernels (tiled / short: B = 128, S = 200, 8 heads in 2 groups, D = 64 28.9 / 18.3;
+// 8 x 8 heads a row each, S = 512, D = 64 13.0 / 9.4).  Measured, tiled / short: pass A, S = 512, 8 heads, fp32
+// 43 / 10; pass B, B = 2, S = 700, 8 heads in 2 groups 28 / 15; 32 heads a row each, B = 32, S = 128 20 / 40 (A) and
+// 20 / 41 (B); 4 heads, fp32, S = 3000 393 / 67 and 116 / 70.
 struct PassCost {
   double short_fixed, short_wg, short_step, short_lone;
   double wg, step, masked, second, lone;  // second: the launch that merges slices or adds partial sums

@@ -107,15 +107,15 @@ def test_selection_takes_the_launches_that_measured_less(record, B, Hs, S, budge
 
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,dtype,rg,window,lse,colsum", [
     # (us, tiled / short, pass A and pass B)
-    (32, 32, 8, 128, 128, 1, 1, 0, "tiled", "tiled"),     # 13 / 41, 25 / 33: many sequences of short prompts
-    (128, 4, 4, 200, 128, 1, 1, 0, "tiled", "tiled"),     # 18 / 38, 23 / 83
-    (8, 32, 32, 256, 64, 2, 0, 0, "tiled", "tiled"),      # 10 / 12, 15 / 31
-    (2, 32, 8, 700, 128, 1, 1, 0, "tiled", "short"),      # 15 / 25, 33 / 22
-    (1, 8, 8, 512, 64, 0, 0, 0, "short", "short"),        # 43 / 10, 50 / 14
-    (2, 8, 2, 700, 128, 1, 1, 0, "short", "short"),       # 15 / 9, 32 / 17
-    (1, 4, 4, 3000, 128, 0, 1, 0, "short", "short"),      # 399 / 69, 123 / 73
-    (1, 4, 4, 4000, 64, 0, 1, 0, "short", "short"),       # 299 / 51, 75 / 61
-    (8, 32, 8, 1024, 128, 1, 1, 0, "tiled", "tiled"),     # 44 / 177, 67 / 115
+    (32, 32, 8, 128, 128, 1, 1, 0, "tiled", "tiled"),     # 13 / 41, 21 / 20: many sequences of short prompts
+    (128, 4, 4, 200, 128, 1, 1, 0, "tiled", "tiled"),     # 18 / 39, 19 / 40
+    (8, 32, 32, 256, 64, 2, 0, 0, "tiled", "tiled"),      # 9 / 12, 10 / 12
+    (2, 32, 8, 700, 128, 1, 1, 0, "tiled", "short"),      # 16 / 25, 29 / 16
+    (1, 8, 8, 512, 64, 0, 0, 0, "short", "short"),        # 43 / 10, 45 / 10
+    (2, 8, 2, 700, 128, 1, 1, 0, "short", "short"),       # 15 / 9, 28 / 15
+    (1, 4, 4, 3000, 128, 0, 1, 0, "short", "short"),      # 393 / 67, 116 / 70
+    (1, 4, 4, 4000, 64, 0, 1, 0, "short", "short"),       # 295 / 50, 69 / 52
+    (8, 32, 8, 1024, 128, 1, 1, 0, "tiled", "tiled"),     # 44 / 176, 63 / 91
     (1, 32, 8, 16384, 128, 1, 1, 0, "tiled", "tiled"),
     (1, 4, 2, 700, 128, 1, 1, 64, "tiled", "tiled"),      # an observation window
     (1, 1, 1, 17600, 64, 0, 0, 0, "tiled", "tiled"),      # 151525 tiles: beyond what was measured
