@@ -938,24 +938,24 @@ __global__ __launch_bounds__(kSelThreads) void emit_kernel(EmitParams p) {
 // select_plan say so, with unit_rows_kernel after F2 and medoid_units_emit_kernel as F3: 2048 pages
 // of 16 tokens, 8 score rows, 72 us through the general kernels and 46 us so).  Every step that needs
 // a view of a whole row or a whole sequence is a serial chain of short phases, so the stage is bound
-// by how many such chains follow each other and by the fixed cost of a launch.  Three launches:
+// by how many such chains follow each other and by the fixed cost of a launch.  Three kernels around the grouping:
 //
 //   F1 slice_hist_kernel   the data-parallel part, spread over the chip: per (row, slice
 //                          of 2048 tokens) the histogram of the keys' leading 11 bits; the
 //                          importance row's workgroups first add up the score rows (in
-//                          row order) and leave the sums in the workspace.
-//   F2 row_select_kernel   one workgroup per row: adds the slices' histograms, finds the
-//                          leading digit of the k-th key, settles the remaining 21 bits on
-//                          the keys held in LDS, writes the row's bitmap.  The workgroup
-//                          that finishes a sequence's LAST row goes on to group that
-//                          sequence: bit words, anchor, distances and the stable counting
-//                          sort by (distance, token), all in its LDS.
+//                          row order) and leave the sums in the workspace.  Not launched
+//                          where the rows make their own histograms (select_route).
+//   F2 row_select_kernel   one workgroup per row: adds the slices' histograms (or counts its
+//                          keys itself), finds the leading digit of the k-th key, settles the
+//                          remaining 21 bits on the keys held in LDS, writes the row's bitmap;
+//                          the only row of a plain top-n goes on to write the index list.
+//   (group_rank_kernel and group_scatter_kernel: bit words, distances, order, as above)
 //   F3 medoid_emit_kernel  one wave per bucket picks the representative; the workgroup
 //                          that finishes a sequence's LAST bucket writes the index list.
 //
 // "Last" is decided by an arrival counter in the workspace (an atomic add after a release
-// fence; the counters are zeroed by F1, ahead of their first use in F2).  Nobody waits for
-// anybody: a workgroup that is not the last simply ends.
+// fence; the counters are zeroed by F1, or by F2 where F1 is not launched, ahead of their first
+// use).  Nobody waits for anybody: a workgroup that is not the last simply ends.
 constexpr int kSliceThreads = 256;
 constexpr int kSliceTokens = 2048;  // tokens of one row handled by an F1 workgroup
 constexpr int kFastMaxRows = 128;   // score rows (two 64-bit words per token)
