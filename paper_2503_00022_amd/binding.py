@@ -372,7 +372,7 @@ def kvcrush_decode_step(q_new, k_new, v_new, k_cache, v_cache, scores_cache, S: 
                         stream=None, scale=0.0):
     """kvcrush_scores_append on dense caches whose row S - 1 the call itself fills with k_new and v_new [B,Hkv,D]."""
     for name, t in (("q_new", q_new), ("k_new", k_new), ("v_new", v_new), ("k_cache", k_cache), ("v_cache", v_cache),
-                    ("scores_cache", scores_cache)):
+                    ("scores_cache", scores_cache), ("workspace", workspace)):
         _dev(t, name)
     if q_new.dim() != 3 or k_cache.dim() != 4 or scores_cache.dtype != torch.float32 \
             or any(t.dtype != k_cache.dtype for t in (q_new, k_new, v_new, v_cache)):

@@ -329,6 +329,23 @@ def test_decode_cache_in_host_memory_is_refused(lib, monkeypatch):
     assert cache.n == 8 and cache._append_ws is None       # no longer than before, and no workspace in host memory kept
 
 
+def test_decode_step_refuses_any_tensor_in_host_memory(lib, monkeypatch):
+    """Each operand of the step, the workspace included, has to live in GPU memory."""
+    import torch
+
+    class OnGpu(torch.Tensor):          # host memory that says otherwise: nothing here gets as far as a kernel
+        device = torch.device("cuda", 0)
+
+    monkeypatch.setattr(binding, "_decode_step", lambda *a, **kw: pytest.fail("host addresses given to the library"))
+    mk = lambda *s, dtype=torch.bfloat16: torch.zeros(*s, dtype=dtype)
+    args = dict(q_new=mk(1, 8, 64), k_new=mk(1, 2, 64), v_new=mk(1, 2, 64), k_cache=mk(1, 2, 16, 64), v_cache=mk(1, 2, 16, 64),
+                scores_cache=mk(1, 2, 16, dtype=torch.float32), workspace=mk(4096, dtype=torch.uint8))
+    for name in args:
+        given = {n: t if n == name else t.as_subclass(OnGpu) for n, t in args.items()}
+        with pytest.raises(ValueError, match=f"{name} must live in GPU memory"):
+            binding.kvcrush_decode_step(**given, S=9, reduce_groups=True)
+
+
 def test_calibration_library_is_separate_from_the_product():
     """The benchmark's calibration kernel is built into a library of its own; the product library
     exports nothing of it."""
